@@ -257,7 +257,8 @@ cbp_status make_plan(const cbp_image* b1, const cbp_image* b2, int m, int n, con
   if (gfmt >= 0 && (fp->N > 32 || gram_mfma_lds_bytes(std::max(fp->Hmax, fp->Wmax), gfmt) > kLdsLimit - 2048))
     return CBP_E_UNSUPPORTED;
   if (o->learned && fp->N > 32) return CBP_E_UNSUPPORTED;   // 32 spectrum features per sample
-  if (sample_lds_bytes(fp->N) > kLdsLimit - 2048 || finalize_lds_bytes(S, o->learned != 0) > kLdsLimit - 2048 ||
+  if (sample_lds_bytes(fp->N, gfmt < 0) > kLdsLimit - 2048 ||
+      finalize_lds_bytes(S, o->learned != 0, false, gfmt < 0) > kLdsLimit - 2048 ||
       row_lds_bytes(fp->Px, fp->twx, esize) > kLdsLimit - 2048 || !col_fits(fp->Py, fp->cw, fp->twy, esize))
     return CBP_E_SHAPE;
   layout(fp, regions(fp->Hmax, fp->Wmax, kmax, S, fp->nch, esize));
@@ -454,6 +455,7 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
                          const inline_head* ih) {
   const batch_ref b = {cv.descs, cv.starts, cv.nf, cv.ctr};
   auto br = [&](int) { return b; };
+  const bool dd = cv.gram_fmt < 0;
   // the first launch (with an inline head it also stores the call's head):
   // a deblurring call's twiddle table of the kernels' row DFTs only, since
   // its row pass folds the columns; a kernel-only call's column fold
@@ -467,16 +469,16 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
   // join: the Gram needs the row evaluation (and the column pass the row spectra)
   if (cv.gram_fmt < 0) CBP_TRY(launch_gram(br(Q_GRAM), cv.grid[Q_GRAM], st));
   else CBP_TRY(launch_gram_mfma(br(Q_GRAMM), cv.grid[Q_GRAMM], cv.gram_fmt, cv.maxStride, st));
-  CBP_TRY(launch_sample(br(Q_SAMPLE), cv.grid[Q_SAMPLE], cv.maxN, st));
+  CBP_TRY(launch_sample(br(Q_SAMPLE), cv.grid[Q_SAMPLE], cv.maxN, dd, st));
   if (cv.mlp) {
     // the learned form: plain kernels (the fallback), the network's weights,
     // the learned kernels, and the judge between them
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 1, cv.finLean, st));
+    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 1, cv.finLean, dd, st));
     CBP_TRY(launch_mlp_frames(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.mlp, st));
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 1, 0, cv.finLean, st));
+    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 1, 0, cv.finLean, dd, st));
     CBP_TRY(launch_judge(br(Q_FINALIZE), cv.grid[Q_FINALIZE], st));
   } else {
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 0, cv.finLean, st));
+    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 0, cv.finLean, dd, st));
   }
   if (latent) {
     CBP_TRY(launch_kernel_dft<T>(br(Q_KRDFT), cv.grid[Q_KRDFT], st));

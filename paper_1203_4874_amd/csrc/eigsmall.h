@@ -96,6 +96,13 @@ __device__ inline double rsq_nr(double x) {
 }
 
 // ---------------------------------------------------------------- wave primitives
+// Orders the wave's LDS accesses (the solver runs in one wave, whose LDS
+// operations complete in order; the caller's workgroup may hold more waves).
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <int CTRL, int ROWMASK = 0xf>
 __device__ inline double dpp_d(double v, double old) {
   const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), CTRL, ROWMASK, 0xf, false);
@@ -245,7 +252,7 @@ __device__ inline void small_tridiag(small_ws& s, int n) {
     if (!(tail > 0.0)) {                        // column already reduced: reflector k = I
       if (l == 0) s.e[k] = {x0r, x0i};
       if (l < m) A[(size_t)(o + l) * n + k] = {0.0, 0.0};
-      __syncthreads();
+      wave_sync();
       continue;
     }
     const double s2 = ax0sq + tail;
@@ -261,7 +268,7 @@ __device__ inline void small_tridiag(small_ws& s, int n) {
       V[l] = vl;
       A[(size_t)(o + l) * n + k] = vl;          // reflector k, kept for the back-transformation
     }
-    __syncthreads();
+    wave_sync();
     // p = A' v (A' trailing m x m block; A'[c][j] = conj(A'[j][c]) read by column)
     {
       c64 p0 = {0.0, 0.0}, p1 = {0.0, 0.0};
@@ -277,12 +284,12 @@ __device__ inline void small_tridiag(small_ws& s, int n) {
       for (; j < sp.j1; ++j) p0 = p0 + cmulc(col[(size_t)j * n], V[j]);
       if (sp.grp < sp.g) part[l] = p0 + p1;
     }
-    __syncthreads();
+    wave_sync();
     const c64 pl = combine_parts(part, sp, m);
     const double K = 0.5 * wsum(l < m ? (vl.re * pl.re + vl.im * pl.im) : 0.0);  // Re(v^H p) / 2
     const c64 wl = {pl.re - K * vl.re, pl.im - K * vl.im};
     if (l < m) W[l] = wl;
-    __syncthreads();
+    wave_sync();
     // A' -= v w^H + w v^H   (lane (c, group) rewrites its rows of column c)
     if (sp.grp < sp.g) {
       const c64 cw = conj(W[sp.c]), cv = conj(V[sp.c]);
@@ -308,14 +315,14 @@ __device__ inline void small_tridiag(small_ws& s, int n) {
       }
     }
     if (l == 0) s.e[k] = alpha;
-    __syncthreads();
+    wave_sync();
   }
   if (l < n) s.a[l] = A[l * n + l].re;
   if (l == 0 && n >= 2) s.e[n - 2] = A[(n - 1) * n + n - 2];
-  __syncthreads();
+  wave_sync();
   if (l < n - 1) s.b[l] = sqrt(norm2(s.e[l]));
   if (l == n - 1) s.b[l] = 0.0;
-  __syncthreads();
+  wave_sync();
 }
 
 // ---------------------------------------------------------------- 2. bisection
@@ -444,7 +451,7 @@ __device__ inline void small_gj_inverse(small_ws& s, int n) {
       col[l] = A[l * n + k];
       row[l] = A[k * n + l];
     }
-    __syncthreads();
+    wave_sync();
     const double ip = rcp_nr(row[k].re);
     for (int e0 = 0; e0 < nn; e0 += 8 * SMALL_NT) {
       c64 av[8], cv[8], rv[8];
@@ -472,7 +479,7 @@ __device__ inline void small_gj_inverse(small_ws& s, int n) {
         }
       }
     }
-    __syncthreads();
+    wave_sync();
   }
 }
 
@@ -509,7 +516,7 @@ __device__ inline void tri_factor(small_ws& s, int n, double sigma, double pivmi
       }
     }
   }
-  __syncthreads();
+  wave_sync();
 }
 
 // X = (T - sigma I)^{-1} (real symmetric) from the factors in s.w: lane j
@@ -518,7 +525,7 @@ __device__ inline void tri_factor(small_ws& s, int n, double sigma, double pivmi
 __device__ inline void build_x(small_ws& s, int n) {
   const int l = threadIdx.x;
   double* X = s.X;
-  __syncthreads();
+  wave_sync();
   if (l < n) {
     double w = 0.0, lprev = 0.0;
     for (int k0 = 0; k0 < n; k0 += 8) {
@@ -554,7 +561,7 @@ __device__ inline void build_x(small_ws& s, int n) {
       }
     }
   }
-  __syncthreads();
+  wave_sync();
 }
 
 // out_c = sum_{j < n} f(c, j) for lane c < n, on split lanes (f reads LDS).
@@ -572,9 +579,9 @@ __device__ inline c64 split_sum(small_ws& s, int n, F f) {
   for (; j < sp.j1; ++j) a0 = a0 + f(sp.c, j);
   c64* part = (c64*)s.part;
   if (sp.grp < sp.g) part[l] = a0 + a1;
-  __syncthreads();
+  wave_sync();
   const c64 r = combine_parts(part, sp, n);
-  __syncthreads();
+  wave_sync();
   return r;
 }
 
@@ -583,9 +590,9 @@ __device__ inline c64 split_sum(small_ws& s, int n, F f) {
 __device__ inline c64 x_mul(small_ws& s, int n, c64 r) {
   const int l = threadIdx.x;
   c64* b = s.u;
-  __syncthreads();
+  wave_sync();
   if (l < n) b[l] = r;
-  __syncthreads();
+  wave_sync();
   const double* X = s.X;
   return split_sum(s, n, [&](int c, int k) __attribute__((always_inline)) {
     const double x = X[(size_t)k * n + c];
@@ -674,7 +681,7 @@ __device__ inline dd small_eig(small_ws& s, const Acc& acc, int n, bool want_dia
   const int l = threadIdx.x;
   if (n == 1) {
     if (l == 0) s.x[0] = {1.0, 0.0};
-    __syncthreads();
+    wave_sync();
     *lam1 = __builtin_nan("");
     *steps = 0;
     return want_diag ? acc.get(0, 0).re : dd{__builtin_nan(""), 0.0};
@@ -707,7 +714,7 @@ __device__ inline dd small_eig(small_ws& s, const Acc& acc, int n, bool want_dia
     xl = l < n ? c64{xl.re / nr, xl.im / nr} : c64{0.0, 0.0};
   }
   if (l < n) s.x[l] = xl;
-  __syncthreads();
+  wave_sync();
   if (max_refine == 0 && !want_diag) {
     *steps = 0;
     return dd{__builtin_nan(""), 0.0};
@@ -739,7 +746,7 @@ __device__ inline dd small_eig(small_ws& s, const Acc& acc, int n, bool want_dia
       s.part[2 * l] = ar.result();
       s.part[2 * l + 1] = ai.result();
     }
-    __syncthreads();
+    wave_sync();
     dd yre = {0.0, 0.0}, yim = {0.0, 0.0};
     if (l < n) {
       yre = s.part[2 * l];
@@ -749,7 +756,7 @@ __device__ inline dd small_eig(small_ws& s, const Acc& acc, int n, bool want_dia
         yim = dd_add(yim, s.part[2 * (g * n + l) + 1]);
       }
     }
-    __syncthreads();
+    wave_sync();
     dot2 t;
     t.init();
     t.add_prod(xl.re, yre.hi); t.add(xl.re * yre.lo);
@@ -777,9 +784,9 @@ __device__ inline dd small_eig(small_ws& s, const Acc& acc, int n, bool want_dia
     const c64 cp = l < n ? cl - xl * al : c64{0.0, 0.0};
     const double dn = sqrt(wsum(norm2(cp))) / sqrt((1.0 - al.re) * (1.0 - al.re) + al.im * al.im);
     xl = {xn.re / nrm, xn.im / nrm};
-    __syncthreads();
+    wave_sync();
     if (l < n) s.x[l] = xl;
-    __syncthreads();
+    wave_sync();
     // converged when the change of direction, or the next one predicted from
     // the linear rate dn / dprev of the last two, is below 4e-15
     done = !(dn > 4e-15) || (dprev > 0.0 && dn * dn <= 4e-15 * dprev);

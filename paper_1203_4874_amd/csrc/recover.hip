@@ -24,6 +24,9 @@
 // Assembly (Sec. 5, abstract): Khat_c = (a_j P_c + b_i Q_c) / 2, inverse
 // S x S DFT, crop to the k_c x k_c support, divide by the complex sum over
 // the support and keep the real part.
+#include <algorithm>
+
+#include "eigblock.h"
 #include "eigsmall.h"
 #include "internal.h"
 
@@ -77,13 +80,13 @@ struct scale_acc {
 
 __device__ inline bool finite_c(c64 v) { return isfinite(v.re) && isfinite(v.im); }
 
-// Both kernels to zero (each lane clears the entries it wrote): a pair whose
+// Both kernels to zero: a pair whose
 // estimate is non-finite or sums to zero is returned as zeros, so that the
 // Fourier division that follows writes a zero latent instead of spreading
 // the non-finite values.
 __device__ inline void zero_kernels(double* K1, int k1, double* K2, int k2) {
-  for (int e = threadIdx.x; e < k1 * k1; e += SMALL_NT) K1[e] = 0.0;
-  for (int e = threadIdx.x; e < k2 * k2; e += SMALL_NT) K2[e] = 0.0;
+  for (int e = threadIdx.x; e < k1 * k1; e += blockDim.x) K1[e] = 0.0;
+  for (int e = threadIdx.x; e < k2 * k2; e += blockDim.x) K2[e] = 0.0;
 }
 
 // Correlations rho for every (pass, sample, lag), summed over channels.
@@ -135,8 +138,12 @@ __global__ __launch_bounds__(64) void k_gram(batch_ref br) {
   });
 }
 
-// Smallest eigenvector of every per-sample Gram.  Items: (sample, pass),
-// one wave each.
+// Smallest eigenvector of every per-sample Gram, one wave per item (sample,
+// pass): the matrix-core forms (VAR_FP64_GRAM), which return the
+// inverse-iteration vector.  Its last digits follow the order of the
+// operations (the FP64 Gram leaves the vector 1e-8 .. 1e-6 from the
+// double-double method's), so these forms keep this solver's order; the
+// refined forms take k_sample_dd.
 __global__ __launch_bounds__(SMALL_NT) void k_sample(batch_ref br) {
   extern __shared__ __attribute__((aligned(16))) char sm_sample[];
   __shared__ c64 twq[CBP_MAX_S];
@@ -221,7 +228,100 @@ __global__ __launch_bounds__(SMALL_NT) void k_sample(batch_ref br) {
   });
 }
 
-// Scale fix, assembly, inverse DFT and normalisation.  One wave.
+// The same for the forms with a double-double Gram (FP64, MIXED): one
+// workgroup of C waves per item (eigblock.h), Newton refined.
+// Bound by the dependent chain of the reduction's n - 2 reflectors.
+template <int C>
+__global__ __launch_bounds__(64 * C) void k_sample_dd(batch_ref br) {
+  extern __shared__ __attribute__((aligned(16))) char sm_sdd[];
+  __shared__ c64 twq[CBP_MAX_S];
+  __shared__ double lmax_s;
+  for_items<Q_SAMPLE>(br, [&](const frame_desc& d, int item) __attribute__((always_inline)) {
+    const int k1 = d.k1, k2 = d.k2, S = d.S;
+    const int N = k1 + k2, NL = 2 * N - 1;
+    const int j = item % S, pass = item / S;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int r = tid >> 3, q = tid & 7;
+    cbp_diag* diag = d.diag;
+    cdd* rho = (cdd*)sm_sdd;
+    char* fixed = sm_sdd + (((size_t)NL * sizeof(cdd) + 15) & ~(size_t)15);
+    const blk_ws w = blk_carve(fixed, fixed + blk_fixed_bytes());
+    for (int t = tid; t < NL; t += nt) rho[t] = d.corr[((size_t)pass * S + j) * NL + t];
+    if (tid >= nt - 64) {   // the last wave: w_S^t for the cofactors below
+      const int t = tid - (nt - 64);
+      if (t < S) {
+        double sn, cs;
+        sincospi(-2.0 * (double)t / (double)S, &sn, &cs);
+        twq[t] = {cs, sn};
+      }
+    }
+    __syncthreads();
+    const gram_acc G{rho, k1, k2};
+    double lam1, ghi;
+    int steps;
+    const dd mu = block_eig<C>(w, G, N, diag != nullptr, &lam1, &steps, &ghi, SMALL_REFINE_MAX);
+    const size_t base = ((size_t)pass * S + j) * N;
+    if (tid < N) {
+      const c64 xi = w.x[tid];
+      d.xvec[base + tid] = xi;
+      if (diag) {
+        diag->sample_vec[pass][j][tid][0] = xi.re;
+        diag->sample_vec[pass][j][tid][1] = xi.im;
+      }
+    }
+    // this sample's share of the cofactors evaluated on the other axis (see
+    // k_sample), eight lanes per entry
+    for (int o = r; o < 2 * S; o += nt >> 3) {
+      const int c = o < S ? 0 : 1, f = o - c * S;
+      const c64* xs = c == 0 ? w.x + k2 : w.x;
+      const int len = c == 0 ? k1 : k2;
+      c64 acc = {0.0, 0.0};
+      for (int x = q; x < len; x += 8) acc = cfma(xs[x], twq[(f * x) % S], acc);
+      acc = sum8(acc);
+      const size_t SS = (size_t)S * S;
+      if (q == 0) {
+        if (pass == 0) d.pq[c * SS + (size_t)f * S + j] = acc;         // P_c[i = f][j]
+        else d.pq[(2 + c) * SS + (size_t)j * S + f] = acc;              // Q_c[i = j][jj = f]
+      }
+    }
+    if (d.feat) {
+      // the learned form's spectrum features (see k_sample)
+      const double lam = block_spectrum(w, N, ghi);
+      if (r == N - 1 && q == 0) lmax_s = lam;
+      __syncthreads();
+      const double lmax = lmax_s;
+      float* feat = d.feat + ((size_t)pass * S + j) * 32;
+      if (q == 0 && r < N && r < 32) {
+        const float f = (float)(log10(fmax(lam, 1e-14 * lmax) / lmax) * 0.1);
+        feat[r] = f;
+        if (diag) diag->sample_features[pass][j][r] = f;
+      }
+      if (tid >= N && tid < 32) {
+        feat[tid] = 1.0f;
+        if (diag) diag->sample_features[pass][j][tid] = 1.0f;
+      }
+    }
+    if (diag && tid < 64) {
+      const bool bad = wmax(tid < N && !finite_c(w.x[tid]) ? 1.0 : 0.0) > 0.0;
+      const double gmax = wmax(tid < N ? dd_val(G.get(tid, tid).re) : 0.0);
+      if (tid == 0) {
+        const double l0 = dd_val(mu);
+        diag->sample_lambda0[pass][j] = l0;
+        diag->sample_lambda1[pass][j] = lam1;
+        diag->sample_scale[pass][j] = gmax;
+        atomicMax(&diag->refine_sample, steps);
+        if (!(lam1 - l0 > 1e-13 * gmax)) atomicOr(&diag->flags, CBP_DIAG_SAMPLE_WEAK);  // NaN-safe: flags NaN too
+        if (bad || !isfinite(l0)) atomicOr(&diag->flags, CBP_DIAG_NONFINITE);
+      }
+    }
+  });
+}
+
+// Scale fix, assembly, inverse DFT and normalisation.  One workgroup of C
+// waves per frame (8 C >= 2S); DD: the forms
+// with a double-double Gram solve on the whole workgroup (eigblock.h), the
+// matrix-core forms on its first wave (eigsmall.h), the setup and the
+// assembly being spread over every wave in both.
 // Learned form (wts != NULL): wts[j] = wX_j (pass-X sample j), wts[S + i] =
 // wY_i, wts[2S] = tau.  The scale system's rows are weighted by
 // sqrt(wX_j wY_i); the spectra are averaged with weights wX_j, wY_i; each
@@ -229,31 +329,43 @@ __global__ __launch_bounds__(SMALL_NT) void k_sample(batch_ref br) {
 //   Ax = Fx^H D_u Fx, By = Fy^T D_v conj(Fy), C = Fx^H D_u Khat D_v conj(Fy),
 // u = wY, v = wX, F[i][x] = w_i^x (the separable weighted fit with per-axis
 // Tikhonov terms), then is divided by its complex sum (real part kept).
-__device__ inline __attribute__((always_inline)) bool learned_assembly(const c64* tw, int S, int k, const double* wts, c64* Kh, c64* tb, c64* xt,
-                                        double* K, cbp_diag* diag, int c);
 
-// LDS of the plain finalize: twiddles, the two diagonal blocks, the solver.
-// lean: the scale solve keeps no caller half (see finalize_frame).
+// LDS regions of the finalize in the double-double forms: twiddles, the
+// diagonal blocks, the solver's vectors, R1 (pq while H is formed, then the
+// solver's matrix, then the spectra: 4 S^2 entries) and R2 (the coupling
+// block; the learned assembly's scratch after the solve).
+__host__ __device__ inline size_t fin_dd_r2_bytes(int S, int learned) {
+  const size_t c = (size_t)S * S * sizeof(cdd), t = ((size_t)S * S + 4 * CBP_MAX_K) * sizeof(c64);
+  return learned && t > c ? t : c;
+}
+__host__ __device__ inline size_t fin_dd_bytes(int S, int learned) {
+  return (size_t)CBP_MAX_S * sizeof(c64) + 2 * (size_t)CBP_MAX_S * sizeof(dd) + blk_fixed_bytes() +
+         blk_matrix_bytes(2 * S) + fin_dd_r2_bytes(S, learned);
+}
+
+// LDS of the finalize in the matrix-core forms: twiddles, the two diagonal
+// blocks, the one-wave solver.  lean: the scale solve keeps no caller half
+// (see finalize_frame).
 __host__ __device__ inline size_t fin_base_bytes(int S, bool lean = false) {
   return (size_t)CBP_MAX_S * sizeof(c64) + 2 * (size_t)CBP_MAX_S * sizeof(dd) + small_lds_bytes(2 * S, !lean);
 }
 
 // Kernels from the per-sample scales: both kernels' normalisation (divide by
 // the complex sum over the support, keep the real part) and diagnostics;
-// F1 / F2 hold each kernel's S x S (row stride S) inverse transform.  Returns
-// true when a kernel is non-finite or sums to zero (wave-uniform).
-__device__ inline __attribute__((always_inline)) bool normalise_kernels(const c64* F1, const c64* F2, int S, int k1,
+// F1 / F2 hold each kernel's S x S (row stride S) inverse transform.  One
+// wave per kernel.  bad_s (LDS, two entries): nonzero where a kernel is
+// non-finite or sums to zero, valid after the next barrier.
+__device__ inline __attribute__((always_inline)) void normalise_kernels(const c64* F1, const c64* F2, int S, int k1,
                                                                          int k2, double* K1, double* K2,
-                                                                         cbp_diag* diag) {
-  const int tid = threadIdx.x, SS = S * S;
+                                                                         cbp_diag* diag, int* bad_s) {
+  const int tid = threadIdx.x & 63, SS = S * S, nw = blockDim.x >> 6;
   const float rS = 1.0f / (float)S;
-  bool bad = false;
-  for (int c = 0; c < 2; ++c) {
+  for (int c = threadIdx.x >> 6; c < 2; c += nw) {
     const int k = c == 0 ? k1 : k2;
     const c64* F = c == 0 ? F1 : F2;
     const float rk = 1.0f / (float)k;
     double sr = 0.0, si = 0.0, ein = 0.0, eall = 0.0;
-    for (int e = tid; e < SS; e += SMALL_NT) {
+    for (int e = tid; e < SS; e += 64) {
       int y, x;
       split_index(e, S, rS, y, x);
       const c64 v = F[e];
@@ -271,7 +383,7 @@ __device__ inline __attribute__((always_inline)) bool normalise_kernels(const c6
     const double s2 = sr * sr + si * si;
     double* K = c == 0 ? K1 : K2;
     double re2 = 0.0, im2 = 0.0;
-    for (int e = tid; e < k * k; e += SMALL_NT) {
+    for (int e = tid; e < k * k; e += 64) {
       int y, x;
       split_index(e, k, rk, y, x);
       const c64 v = F[y * S + x];
@@ -286,15 +398,24 @@ __device__ inline __attribute__((always_inline)) bool normalise_kernels(const c6
       re2 = q.re;
       im2 = q.im;
     }
-    if (tid == 0 && diag) {
-      diag->kernel_imag[c] = sqrt(im2) / fmax(sqrt(re2), 1e-300);
-      diag->kernel_outside[c] = (eall - ein) / fmax(eall, 1e-300);
-      if (!(s2 > 0.0) || !isfinite(s2)) atomicOr(&diag->flags, CBP_DIAG_KERNEL_ZERO);
-      if (!isfinite(re2)) atomicOr(&diag->flags, CBP_DIAG_NONFINITE);
+    if (tid == 0) {
+      if (diag) {
+        diag->kernel_imag[c] = sqrt(im2) / fmax(sqrt(re2), 1e-300);
+        diag->kernel_outside[c] = (eall - ein) / fmax(eall, 1e-300);
+        if (!(s2 > 0.0) || !isfinite(s2)) atomicOr(&diag->flags, CBP_DIAG_KERNEL_ZERO);
+        if (!isfinite(re2)) atomicOr(&diag->flags, CBP_DIAG_NONFINITE);
+      }
+      bad_s[c] = !(s2 > 0.0) || !isfinite(s2) || !isfinite(re2);
     }
-    bad = bad || !(s2 > 0.0) || !isfinite(s2) || !isfinite(re2);   // wave-uniform
   }
-  return bad;
+}
+
+// Both kernels to zero when either is bad (each thread clears entries that
+// the barrier orders after their writes).
+__device__ inline void drop_bad_kernels(const int* bad_s, double* K1, int k1, double* K2, int k2) {
+  __threadfence_block();
+  __syncthreads();
+  if (bad_s[0] || bad_s[1]) zero_kernels(K1, k1, K2, k2);
 }
 
 // Scale system of the one-axis fix (S x S, double-double entries in LDS).
@@ -304,6 +425,52 @@ struct cdd_mat_acc {
   __device__ cdd get(int r, int c) const { return H[r * n + c]; }
 };
 
+// The solve of a frame's scale system acc (order n, n <= 8 C): on the whole
+// workgroup (DD) or, after its rounding into w.A, on the first wave.  Returns
+// the eigenvector (LDS), valid for every thread.
+template <int C, bool DD, class Acc>
+__device__ inline __attribute__((always_inline)) const c64* scale_solve(const Acc& acc, int n, const blk_ws& bw,
+                                                                         small_ws& sw, cbp_diag* diag,
+                                                                         int max_refine, int k1, int k2, int S) {
+  const int tid = threadIdx.x;
+  double lam1 = 0.0, ghi;
+  int steps = 0;
+  dd mu = {0.0, 0.0};
+  double hmax = 0.0;
+  if (DD) {
+    if (diag && tid < 64) hmax = wmax(tid < n ? dd_val(acc.get(tid, tid).re) : 0.0);
+    mu = block_eig<C>(bw, acc, n, diag != nullptr, &lam1, &steps, &ghi, max_refine);
+  } else {
+    const float rn = 1.0f / (float)n;
+    for (int e = tid; e < n * n; e += blockDim.x) {
+      int r, c;
+      split_index(e, n, rn, r, c);
+      const cdd h = acc.get(r, c);
+      sw.A[e] = {h.re.hi, h.im.hi};
+    }
+    if (diag && tid < 64) hmax = wmax(tid < n ? dd_val(acc.get(tid, tid).re) : 0.0);
+    __syncthreads();
+    if (tid < 64) mu = small_eig(sw, acc, n, diag != nullptr, &lam1, &steps, max_refine);
+    __syncthreads();
+  }
+  const c64* x = DD ? bw.x : sw.x;
+  if (diag) {
+    if (tid == 0) {
+      diag->k1 = k1; diag->k2 = k2; diag->S = S; diag->n = k1 + k2;
+      diag->scale_lambda0 = dd_val(mu);
+      diag->scale_lambda1 = lam1;
+      diag->scale_scale = hmax;
+      diag->refine_scale = steps;
+      if (!(lam1 - dd_val(mu) > 1e-13 * hmax)) atomicOr(&diag->flags, CBP_DIAG_SCALE_WEAK);
+    }
+    for (int t = tid; t < n; t += blockDim.x) {
+      diag->scale_vec[t][0] = x[t].re;
+      diag->scale_vec[t][1] = x[t].im;
+    }
+  }
+  return x;
+}
+
 // The one-axis scale fix (the paper's scales from one evaluation order,
 // fixed by the kernels' finite support).  With the pass-X null vectors X_j
 // (u: kernel 2's slice, k2 taps; v: kernel 1's slice, k1 taps) and a_j the
@@ -312,20 +479,29 @@ struct cdd_mat_acc {
 //   H[j][j'] = sum_c (sum_{x < k_c} conj(X^c_j[x]) X^c_j'[x]) g_c(j - j'),
 //   g_c(t) = sum_{y = k_c}^{S-1} w^{t y},  w = exp(-2 pi i / S),
 // and a is its smallest eigenvector; K_c[y][x] = (1/S) sum_j a_j X^c_j[x] w_j^{-y}.
+template <int C, bool DD>
 __device__ inline __attribute__((always_inline)) void one_axis_frame(const c64* xvec, int S, int k1, int k2,
                                                                       double* K1, double* K2, cbp_diag* diag,
-                                                                      char* sm_fin, int variant) {
-  const int N = k1 + k2, SS = S * S, tid = threadIdx.x;
+                                                                      char* sm_fin, int variant, int* bad_s) {
+  const int N = k1 + k2, SS = S * S, tid = threadIdx.x, nt = blockDim.x;
   const float rS = 1.0f / (float)S;
   c64* tw = (c64*)sm_fin;                                   // S
   c64* X = tw + CBP_MAX_S;                                  // [S][N]
   char* after = (char*)(X + (((size_t)S * N + 1) & ~(size_t)1));
-  small_ws w = small_carve(after, S);
-  cdd* Hm = (cdd*)(after + small_lds_bytes(S));             // [S][S]
+  blk_ws bw = {};
+  small_ws sw = {};
+  cdd* Hm;                                                  // [S][S]
+  if (DD) {
+    bw = blk_carve(after, after + blk_fixed_bytes());
+    Hm = (cdd*)(after + blk_fixed_bytes() + blk_matrix_bytes(S));
+  } else {
+    sw = small_carve(after, S);
+    Hm = (cdd*)(after + small_lds_bytes(S));
+  }
   unit_twiddles(tw, S);
-  for (int e = tid; e < S * N; e += SMALL_NT) X[e] = xvec[e];   // pass X: [j][l]
+  for (int e = tid; e < S * N; e += nt) X[e] = xvec[e];   // pass X: [j][l]
   __syncthreads();
-  for (int e = tid; e < SS; e += SMALL_NT) {
+  for (int e = tid; e < SS; e += nt) {
     int j, jp;
     split_index(e, S, rS, j, jp);
     int t = j - jp;
@@ -357,32 +533,16 @@ __device__ inline __attribute__((always_inline)) void one_axis_frame(const c64* 
     Hm[e] = cdd{re.result(), im.result()};
   }
   __syncthreads();
-  for (int e = tid; e < SS; e += SMALL_NT) w.A[e] = {Hm[e].re.hi, Hm[e].im.hi};
   const cdd_mat_acc H{Hm, S};
-  const double hmax = wmax(tid < S ? dd_val(Hm[tid * S + tid].re) : 0.0);
+  const c64* a = scale_solve<C, DD>(H, S, bw, sw, diag, solve_refine_max(variant), k1, k2, S);
   __syncthreads();
-  double lam1;
-  int steps;
-  const dd mu = small_eig(w, H, S, diag != nullptr, &lam1, &steps, solve_refine_max(variant));
-  if (tid == 0 && diag) {
-    diag->k1 = k1; diag->k2 = k2; diag->S = S; diag->n = N;
-    diag->scale_lambda0 = dd_val(mu);
-    diag->scale_lambda1 = lam1;
-    diag->scale_scale = hmax;
-    diag->refine_scale = steps;
-    if (!(lam1 - dd_val(mu) > 1e-13 * hmax)) atomicOr(&diag->flags, CBP_DIAG_SCALE_WEAK);
-  }
-  if (diag)
-    for (int t = tid; t < S; t += SMALL_NT) {
-      diag->scale_vec[t][0] = w.x[t].re;
-      diag->scale_vec[t][1] = w.x[t].im;
-    }
-  __syncthreads();
-  // F[c][y][x] = (1/S) sum_j a_j X^c_j[x] w_j^{-y}  (into the solver's matrix region, 2 S^2 entries)
-  c64* F = w.A;    // kernel 1: the solver's matrix region (S^2 entries, free after the solve)
-  c64* F2 = w.W;   // kernel 2: its W region (S (S + 1) entries)
+  // F[c][y][x] = (1/S) sum_j a_j X^c_j[x] w_j^{-y}: kernel 1 in the solver's
+  // matrix region, kernel 2 in its W region / the system's place (S^2 entries
+  // each, free after the solve)
+  c64* F = DD ? bw.M : sw.A;
+  c64* F2 = DD ? (c64*)Hm : sw.W;
   const double rs = 1.0 / (double)S;
-  for (int e = tid; e < 2 * SS; e += SMALL_NT) {
+  for (int e = tid; e < 2 * SS; e += nt) {
     const int c = e >= SS, yx = e - c * SS;
     int y, x;
     split_index(yx, S, rS, y, x);
@@ -391,7 +551,7 @@ __device__ inline __attribute__((always_inline)) void one_axis_frame(const c64* 
     if (x < k) {
       int t = 0;
       for (int j = 0; j < S; ++j) {
-        acc = acc + (w.x[j] * X[j * N + o + x]) * conj(tw[t]);
+        acc = acc + (a[j] * X[j * N + o + x]) * conj(tw[t]);
         t += y;
         if (t >= S) t -= S;
       }
@@ -399,59 +559,70 @@ __device__ inline __attribute__((always_inline)) void one_axis_frame(const c64* 
     (c == 0 ? F : F2)[yx] = {acc.re * rs, acc.im * rs};
   }
   __syncthreads();
-  if (normalise_kernels(F, F2, S, k1, k2, K1, K2, diag)) zero_kernels(K1, k1, K2, k2);
+  normalise_kernels(F, F2, S, k1, k2, K1, K2, diag, bad_s);
+  drop_bad_kernels(bad_s, K1, k1, K2, k2);
 }
 
+// One kernel of the learned assembly: writes K and bad_s[c].
+__device__ inline __attribute__((always_inline)) void learned_assembly(const c64* tw, int S, int k, const double* wts, c64* Kh, c64* tb, c64* xt,
+                                        double* K, cbp_diag* diag, int c, int* bad_s);
+
+template <int C, bool DD>
 __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* xvec, int S, int k1, int k2, c64* pq, double* K1,
-                                      double* K2, cbp_diag* diag, char* sm_fin, const double* wts, int variant) {
+                                      double* K2, cbp_diag* diag, char* sm_fin, const double* wts, int variant, int* bad_s) {
   if (variant & VAR_ONE_AXIS) {
-    one_axis_frame(xvec, S, k1, k2, K1, K2, diag, sm_fin, variant);
+    one_axis_frame<C, DD>(xvec, S, k1, k2, K1, K2, diag, sm_fin, variant, bad_s);
     return;
   }
   // kernel 1's equations only (the k1-only scale least squares) or both kernels'
   const int nc = (variant & VAR_SCALE_K1) ? 1 : 2;
-  const int N = k1 + k2, n2 = 2 * S, SS = S * S;
-  const int tid = threadIdx.x;
-  const float rS = 1.0f / (float)S, rSS = 1.0f / (float)SS, rn2 = 1.0f / (float)n2;
+  const int n2 = 2 * S, SS = S * S;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const float rS = 1.0f / (float)S, rSS = 1.0f / (float)SS;
   c64* tw = (c64*)sm_fin;                        // S
   dd* Da = (dd*)(tw + CBP_MAX_S);                // S
   dd* Db = Da + CBP_MAX_S;                       // S
-  // The coupling block (below) is read through H by the Newton refinement
-  // and by the diagnostics' Rayleigh quotient after the solver has built X;
-  // a solve with neither reads it only before (A and hmax come from it), so
-  // it may share X's region (lean: no caller half, 9 KB less LDS at S = 17,
-  // which lets the workgroup fit on a CU beside the FFT passes' workgroups).
-  const bool lean = solve_refine_max(variant) == 0 && diag == nullptr;
-  small_ws w = small_carve((char*)(Db + CBP_MAX_S), n2, !lean);
-  // after the scale solve, its matrix region (4 S^2 entries) holds the
-  // averaged spectra / inverse DFTs (2 S^2) and the half-transformed ones (2 S^2)
-  c64* kbuf = w.A;
-  c64* tbuf = w.A + 2 * SS;
+  char* after = (char*)(Db + CBP_MAX_S);
+  // Staging: the cofactors evaluated on the other axis, pq = [P1, P2, Q1, Q2]
+  // (each [i][j], written by the sample solves), in the region of 4 S^2
+  // entries that the solver's matrix takes once they are read; the coupling
+  // block C (S^2 double-double entries) in a region the solver leaves alone.
+  // (Matrix-core forms: the region of the solver's W; a solve with neither
+  // refinement nor diagnostics reads C only before it builds X, so C may
+  // share X's region -- lean: no caller half, 9 KB less LDS at S = 17, which
+  // lets the workgroup fit on a CU beside the FFT passes' workgroups.)
+  blk_ws bw = {};
+  small_ws sw = {};
+  c64* pql;
+  cdd* cmat;
+  if (DD) {
+    char* r1 = after + blk_fixed_bytes();
+    bw = blk_carve(after, r1);
+    pql = (c64*)r1;
+    cmat = (cdd*)(r1 + blk_matrix_bytes(n2));
+  } else {
+    const bool lean = solve_refine_max(variant) == 0 && diag == nullptr;
+    sw = small_carve(after, n2, !lean);
+    pql = sw.A;
+    cmat = (cdd*)sw.W;
+  }
   unit_twiddles(tw, S);
-  // the cofactors evaluated on the other axis, pq = [P1, P2, Q1, Q2] (each
-  // [i][j], written by the sample solves), staged in the solver's matrix
-  // region (4 S^2 entries, filled with H's rounding once they are read); the
-  // coupling block C (S^2 double-double entries) goes to the W region, which
-  // the solver leaves free (or, lean, which it fills with X only after C's
-  // last read), so every read of H is an LDS read
-  c64* pql = w.A;
-  cdd* cmat = (cdd*)w.W;
-  for (int e0 = 0; e0 < 4 * SS; e0 += 8 * SMALL_NT) {   // eight loads in flight per lane
+  for (int e0 = 0; e0 < 4 * SS; e0 += 8 * nt) {   // eight loads in flight per lane
     c64 v[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const int e = e0 + tid + t * SMALL_NT;
+      const int e = e0 + tid + t * nt;
       v[t] = e < 4 * SS ? pq[e] : c64{0.0, 0.0};
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const int e = e0 + tid + t * SMALL_NT;
+      const int e = e0 + tid + t * nt;
       if (e < 4 * SS) pql[e] = v[t];
     }
   }
   __syncthreads();
   // H blocks in double-double
-  for (int e = tid; e < SS; e += SMALL_NT) {
+  for (int e = tid; e < SS; e += nt) {
     int jj, i;
     split_index(e, S, rS, jj, i);
     dot2 re, im;
@@ -469,8 +640,9 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
   }
   // diagonal blocks: Da[t] = sum over (c, i) of w |P_c[i][t]|^2, Db[t] =
   // sum over (c, j) of w |Q_c[t][j]|^2, in that order, with the entries
-  // read eight at a time (clamped indices; the extra reads are not summed)
-  for (int t = tid; t < n2; t += SMALL_NT) {
+  // read eight at a time (clamped indices; the extra reads are not summed).
+  // The threads count down so that waves with fewer entries above come first.
+  for (int t = nt - 1 - tid; t < n2; t += nt) {
     const bool isa = t < S;
     const int tt = isa ? t : t - S;
     dot2 d;
@@ -503,41 +675,20 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
     if (isa) Da[tt] = d.result();
     else Db[tt] = d.result();
   }
-  __threadfence_block();
   __syncthreads();
   const scale_acc H{Da, Db, cmat, S};
-  for (int e = tid; e < n2 * n2; e += SMALL_NT) {
-    int r, c;
-    split_index(e, n2, rn2, r, c);
-    const cdd h = H.get(r, c);
-    w.A[e] = {h.re.hi, h.im.hi};
-  }
-  const double hmax = wmax(tid < n2 ? dd_val(H.get(tid, tid).re) : 0.0);
+  const c64* x = scale_solve<C, DD>(H, n2, bw, sw, diag, solve_refine_max(variant), k1, k2, S);
+  // the solver's matrix region now takes the averaged spectra / inverse DFTs
+  // (2 S^2) and the half-transformed ones (2 S^2)
+  c64* Kh = DD ? bw.M : sw.A;
+  c64* Tm = Kh + 2 * SS;
   __syncthreads();
-  double lam1;
-  int steps;
-  const dd mu = small_eig(w, H, n2, diag != nullptr, &lam1, &steps, solve_refine_max(variant));
-  if (tid == 0 && diag) {
-    diag->k1 = k1; diag->k2 = k2; diag->S = S; diag->n = N;
-    diag->scale_lambda0 = dd_val(mu);
-    diag->scale_lambda1 = lam1;
-    diag->scale_scale = hmax;
-    diag->refine_scale = steps;
-    if (!(lam1 - dd_val(mu) > 1e-13 * hmax)) atomicOr(&diag->flags, CBP_DIAG_SCALE_WEAK);
-  }
-  if (diag)
-    for (int t = tid; t < n2; t += SMALL_NT) {
-      diag->scale_vec[t][0] = w.x[t].re;
-      diag->scale_vec[t][1] = w.x[t].im;
-    }
   // averaged spectra Kh[c][i][j]
-  c64* Kh = kbuf;
-  c64* Tm = tbuf;
-  for (int e0 = 0; e0 < 2 * SS; e0 += 4 * SMALL_NT) {
+  for (int e0 = 0; e0 < 2 * SS; e0 += 4 * nt) {
     c64 Pv[4], Qv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {   // eight loads in flight per lane (indices clamped in range)
-      const int e = min(e0 + tid + u * SMALL_NT, 2 * SS - 1);
+      const int e = min(e0 + tid + u * nt, 2 * SS - 1);
       int c, ij;
       split_index(e, SS, rSS, c, ij);
       Pv[u] = pq[(size_t)c * SS + ij];
@@ -545,7 +696,7 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int e = e0 + tid + u * SMALL_NT;
+      const int e = e0 + tid + u * nt;
       if (e >= 2 * SS) break;
       int c, ij;
       split_index(e, SS, rSS, c, ij);
@@ -555,10 +706,10 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
       c64 kv;
       if (wts) {
         const double wx = wts[jj], wy = wts[S + i], r = 1.0 / (wx + wy);
-        const c64 a = w.x[jj] * P, b = w.x[S + i] * Q;
+        const c64 a = x[jj] * P, b = x[S + i] * Q;
         kv = {(wx * a.re + wy * b.re) * r, (wx * a.im + wy * b.im) * r};
       } else {
-        const c64 v = w.x[jj] * P + w.x[S + i] * Q;
+        const c64 v = x[jj] * P + x[S + i] * Q;
         kv = {0.5 * v.re, 0.5 * v.im};
       }
       Kh[e] = kv;
@@ -571,20 +722,20 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
   __syncthreads();
   if (wts) {
     if (diag)
-      for (int t = tid; t <= n2; t += SMALL_NT) diag->sample_weights[t] = wts[t];
-    c64* xt = w.W;   // S^2 + 2 CBP_MAX_S entries from the solver's W onwards (free after the solve)
-    const bool bad1 = learned_assembly(tw, S, k1, wts, Kh, tbuf, xt, K1, diag, 0);
-    const bool bad2 = learned_assembly(tw, S, k2, wts, Kh + SS, tbuf, xt, K2, diag, 1);
-    if (bad1 || bad2) zero_kernels(K1, k1, K2, k2);
+      for (int t = tid; t <= n2; t += nt) diag->sample_weights[t] = wts[t];
+    c64* xt = DD ? (c64*)cmat : sw.W;   // S^2 + 4 CBP_MAX_K entries, free after the solve
+    learned_assembly(tw, S, k1, wts, Kh, Tm, xt, K1, diag, 0, bad_s);
+    learned_assembly(tw, S, k2, wts, Kh + SS, Tm, xt, K2, diag, 1, bad_s);
+    drop_bad_kernels(bad_s, K1, k1, K2, k2);
     return;
   }
   // inverse DFT along x: Tm[c][j][x] = sum_i Kh[c][i][j] w_i^{-x}, two
   // outputs per lane at a time (independent chains, each summed in i order)
-  for (int e = tid; e < 2 * SS; e += 2 * SMALL_NT) {
-    const int f = min(e + SMALL_NT, 2 * SS - 1);
-    int c, jx, jj, x, c2, jx2, jj2, x2;
+  for (int e = tid; e < 2 * SS; e += 2 * nt) {
+    const int f = min(e + nt, 2 * SS - 1);
+    int c, jx, jj, xx, c2, jx2, jj2, x2;
     split_index(e, SS, rSS, c, jx);
-    split_index(jx, S, rS, jj, x);
+    split_index(jx, S, rS, jj, xx);
     split_index(f, SS, rSS, c2, jx2);
     split_index(jx2, S, rS, jj2, x2);
     c64 acc = {0.0, 0.0}, acc2 = {0.0, 0.0};
@@ -593,29 +744,29 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
     for (int i = 0; i < S; ++i) {
       acc = acc + Kh[(size_t)c * SS + i * S + jj] * conj(tw[t]);
       acc2 = acc2 + Kh[(size_t)c2 * SS + i * S + jj2] * conj(tw[t2]);
-      t += x;
+      t += xx;
       if (t >= S) t -= S;
       t2 += x2;
       if (t2 >= S) t2 -= S;
     }
     Tm[e] = acc;
-    if (e + SMALL_NT < 2 * SS) Tm[f] = acc2;
+    if (e + nt < 2 * SS) Tm[f] = acc2;
   }
   __syncthreads();
   // inverse DFT along y: Kf[c][y][x] = sum_j w_j^{-y} Tm[c][j][x]   (into Kh),
   // two outputs per lane at a time as above
-  for (int e = tid; e < 2 * SS; e += 2 * SMALL_NT) {
-    const int f = min(e + SMALL_NT, 2 * SS - 1);
-    int c, yx, y, x, c2, yx2, y2, x2;
+  for (int e = tid; e < 2 * SS; e += 2 * nt) {
+    const int f = min(e + nt, 2 * SS - 1);
+    int c, yx, y, xx, c2, yx2, y2, x2;
     split_index(e, SS, rSS, c, yx);
-    split_index(yx, S, rS, y, x);
+    split_index(yx, S, rS, y, xx);
     split_index(f, SS, rSS, c2, yx2);
     split_index(yx2, S, rS, y2, x2);
     c64 acc = {0.0, 0.0}, acc2 = {0.0, 0.0};
     int t = 0, t2 = 0;
 #pragma unroll 4
     for (int jj = 0; jj < S; ++jj) {
-      acc = acc + Tm[(size_t)c * SS + jj * S + x] * conj(tw[t]);
+      acc = acc + Tm[(size_t)c * SS + jj * S + xx] * conj(tw[t]);
       acc2 = acc2 + Tm[(size_t)c2 * SS + jj * S + x2] * conj(tw[t2]);
       t += y;
       if (t >= S) t -= S;
@@ -623,24 +774,24 @@ __device__ inline __attribute__((always_inline)) void finalize_frame(const c64* 
       if (t2 >= S) t2 -= S;
     }
     Kh[e] = acc;
-    if (e + SMALL_NT < 2 * SS) Kh[f] = acc2;
+    if (e + nt < 2 * SS) Kh[f] = acc2;
   }
   __syncthreads();
-  if (normalise_kernels(Kh, Kh + SS, S, k1, k2, K1, K2, diag)) zero_kernels(K1, k1, K2, k2);
+  normalise_kernels(Kh, Kh + SS, S, k1, k2, K1, K2, diag, bad_s);
+  drop_bad_kernels(bad_s, K1, k1, K2, k2);
 }
 
-// Returns true when the kernel is non-finite or sums to zero (wave-uniform).
-__device__ inline __attribute__((always_inline)) bool learned_assembly(const c64* tw, int S, int k, const double* wts, c64* Kh, c64* tb, c64* xt,
-                                        double* K, cbp_diag* diag, int c) {
-  const int tid = threadIdx.x, kk = k * k;
+__device__ inline __attribute__((always_inline)) void learned_assembly(const c64* tw, int S, int k, const double* wts, c64* Kh, c64* tb, c64* xt,
+                                        double* K, cbp_diag* diag, int c, int* bad_s) {
+  const int tid = threadIdx.x, nt = blockDim.x, kk = k * k;
   const float rS = 1.0f / (float)S, rk = 1.0f / (float)k;
   const double tau = wts[2 * S];
-  c64* Ax = tb;             // k x k
+  c64* Ax = tb;             // k x k, By after it
   c64* By = tb + kk;        // k x k
   c64* T1 = xt;             // k x S, later Z1 (k x k)
   c64* Cm = Kh;             // k x k, over Khat once T1 is formed
   // F[i][x] = w_i^x = tw[(i x) mod S];  u_i = wY_i,  v_j = wX_j
-  for (int e = tid; e < kk; e += SMALL_NT) {
+  for (int e = tid; e < kk; e += nt) {
     int p, q;
     split_index(e, k, rk, p, q);
     c64 a = {0.0, 0.0}, b = {0.0, 0.0};
@@ -656,7 +807,7 @@ __device__ inline __attribute__((always_inline)) bool learned_assembly(const c64
     By[e] = b;
   }
   // T1[x][j] = sum_i conj(F[i][x]) u_i Khat[i][j]
-  for (int e = tid; e < k * S; e += SMALL_NT) {
+  for (int e = tid; e < k * S; e += nt) {
     int x, jj;
     split_index(e, S, rS, x, jj);
     c64 acc = {0.0, 0.0};
@@ -668,7 +819,7 @@ __device__ inline __attribute__((always_inline)) bool learned_assembly(const c64
   }
   __syncthreads();
   // C[x][y] = sum_j T1[x][j] v_j conj(F[j][y])
-  for (int e = tid; e < kk; e += SMALL_NT) {
+  for (int e = tid; e < kk; e += nt) {
     int x, y;
     split_index(e, k, rk, x, y);
     c64 acc = {0.0, 0.0};
@@ -679,16 +830,38 @@ __device__ inline __attribute__((always_inline)) bool learned_assembly(const c64
     Cm[e] = acc;
   }
   __syncthreads();
-  // (Ax + tau I)^{-1}, (By + tau I)^{-1} in place (Hermitian positive definite)
-  small_ws g;
-  g.w = xt + (size_t)S * S;
-  g.u = g.w + CBP_MAX_S;
-  g.A = Ax;
-  small_gj_inverse(g, k);
-  g.A = By;
-  small_gj_inverse(g, k);
+  // (Ax + tau I)^{-1}, (By + tau I)^{-1} in place (Hermitian positive
+  // definite; Gauss-Jordan without pivoting, both matrices in step)
+  {
+    c64* col = xt + (size_t)S * S;      // [2][k]
+    c64* row = col + 2 * CBP_MAX_K;     // [2][k]
+    const float rkk = 1.0f / (float)kk;
+    for (int t = 0; t < k; ++t) {
+      if (tid < 2 * k) {
+        const int mi = tid >= k, i = tid - mi * k;
+        col[tid] = Ax[mi * kk + i * k + t];
+        row[tid] = Ax[mi * kk + t * k + i];
+      }
+      __syncthreads();
+      const double ipa = rcp_nr(row[t].re), ipb = rcp_nr(row[k + t].re);
+      for (int e = tid; e < 2 * kk; e += nt) {
+        int mi, ij, i, jj;
+        split_index(e, kk, rkk, mi, ij);
+        split_index(ij, k, rk, i, jj);
+        const double ip = mi ? ipb : ipa;
+        const c64 cv = col[mi * k + i], rv = row[mi * k + jj];
+        c64 v;
+        if (i == t && jj == t) v = {ip, 0.0};
+        else if (i == t) v = ip * rv;
+        else if (jj == t) v = -ip * cv;
+        else v = Ax[e] - ip * (cv * rv);
+        Ax[e] = v;
+      }
+      __syncthreads();
+    }
+  }
   // Z1 = Ax^{-1} C (into T1), Z = Z1 By^{-1} (into Cm)
-  for (int e = tid; e < kk; e += SMALL_NT) {
+  for (int e = tid; e < kk; e += nt) {
     int x, y;
     split_index(e, k, rk, x, y);
     c64 acc = {0.0, 0.0};
@@ -696,7 +869,7 @@ __device__ inline __attribute__((always_inline)) bool learned_assembly(const c64
     T1[e] = acc;
   }
   __syncthreads();
-  for (int e = tid; e < kk; e += SMALL_NT) {
+  for (int e = tid; e < kk; e += nt) {
     int x, y;
     split_index(e, k, rk, x, y);
     c64 acc = {0.0, 0.0};
@@ -704,44 +877,50 @@ __device__ inline __attribute__((always_inline)) bool learned_assembly(const c64
     Cm[e] = acc;
   }
   __syncthreads();
-  // K[y][x] = Z[x][y] / sum(Z), real part
-  double sr = 0.0, si = 0.0;
-  for (int e = tid; e < kk; e += SMALL_NT) { sr += Cm[e].re; si += Cm[e].im; }
-  sr = wsum(sr);
-  si = wsum(si);
-  const double s2 = sr * sr + si * si;
-  double re2 = 0.0, im2 = 0.0;
-  for (int e = tid; e < kk; e += SMALL_NT) {
-    int y, x;
-    split_index(e, k, rk, y, x);
-    const c64 v = Cm[x * k + y];
-    const double kr = (v.re * sr + v.im * si) / s2;
-    const double ki = (v.im * sr - v.re * si) / s2;
-    K[e] = kr;
-    re2 += kr * kr;
-    im2 += ki * ki;
-  }
-  re2 = wsum(re2);
-  im2 = wsum(im2);
-  if (tid == 0 && diag) {
-    diag->kernel_imag[c] = sqrt(im2) / fmax(sqrt(re2), 1e-300);
-    diag->kernel_outside[c] = 0.0;
-    if (!(s2 > 0.0) || !isfinite(s2)) atomicOr(&diag->flags, CBP_DIAG_KERNEL_ZERO);
-    if (!isfinite(re2)) atomicOr(&diag->flags, CBP_DIAG_NONFINITE);
+  // K[y][x] = Z[x][y] / sum(Z), real part (one wave)
+  if (tid < 64) {
+    double sr = 0.0, si = 0.0;
+    for (int e = tid; e < kk; e += 64) { sr += Cm[e].re; si += Cm[e].im; }
+    sr = wsum(sr);
+    si = wsum(si);
+    const double s2 = sr * sr + si * si;
+    double re2 = 0.0, im2 = 0.0;
+    for (int e = tid; e < kk; e += 64) {
+      int y, x;
+      split_index(e, k, rk, y, x);
+      const c64 v = Cm[x * k + y];
+      const double kr = (v.re * sr + v.im * si) / s2;
+      const double ki = (v.im * sr - v.re * si) / s2;
+      K[e] = kr;
+      re2 += kr * kr;
+      im2 += ki * ki;
+    }
+    re2 = wsum(re2);
+    im2 = wsum(im2);
+    if (tid == 0) {
+      if (diag) {
+        diag->kernel_imag[c] = sqrt(im2) / fmax(sqrt(re2), 1e-300);
+        diag->kernel_outside[c] = 0.0;
+        if (!(s2 > 0.0) || !isfinite(s2)) atomicOr(&diag->flags, CBP_DIAG_KERNEL_ZERO);
+        if (!isfinite(re2)) atomicOr(&diag->flags, CBP_DIAG_NONFINITE);
+      }
+      bad_s[c] = !(s2 > 0.0) || !isfinite(s2) || !isfinite(re2);
+    }
   }
   __syncthreads();
-  return !(s2 > 0.0) || !isfinite(s2) || !isfinite(re2);
 }
 
 // Items: one per frame.  plain_only: the plain method's kernels into the
 // learned form's fallback slots (d.Kalt), ignoring the network's weights.
-__global__ __launch_bounds__(SMALL_NT) void k_finalize(batch_ref br, int plain_only) {
+template <int C, bool DD>
+__global__ __launch_bounds__(64 * C) void k_finalize(batch_ref br, int plain_only) {
   extern __shared__ __attribute__((aligned(16))) char sm_fin[];
+  __shared__ int bad_s[2];
   for_items<Q_FINALIZE>(br, [&](const frame_desc& d, int) __attribute__((always_inline)) {
     double* K1 = plain_only ? d.Kalt : d.K1;
     double* K2 = plain_only ? d.Kalt + CBP_MAX_K * CBP_MAX_K : d.K2;
-    finalize_frame(d.xvec, d.S, d.k1, d.k2, d.pq, K1, K2, plain_only ? nullptr : d.diag, sm_fin,
-                   plain_only ? nullptr : d.wts, d.variant);
+    finalize_frame<C, DD>(d.xvec, d.S, d.k1, d.k2, d.pq, K1, K2, plain_only ? nullptr : d.diag, sm_fin,
+                          plain_only ? nullptr : d.wts, d.variant, bad_s);
   });
 }
 
@@ -851,25 +1030,22 @@ __global__ void k_diag_init(batch_ref br) {
 
 }  // namespace
 
-// LDS of the finalize: the plain part (the coupling block lives in the
-// solver's W region) and, for the learned assembly, T1 / Z1 (S^2) and the
-// inversion's two vectors, taken from the same W region (2S (2S + 1)
-// entries, the last region of the solver's LDS) plus what they need beyond
-// it.
-size_t finalize_lds_bytes(int S, int learned, bool lean) {
+// LDS of the finalize.  Matrix-core forms: the plain part (the coupling
+// block lives in the solver's W region) and, for the learned assembly, T1 /
+// Z1 (S^2) and the inversions' vectors, taken from the same W region (2S
+// (2S + 1) entries, the last region of the solver's LDS) plus what they need
+// beyond it.
+size_t finalize_lds_bytes(int S, int learned, bool lean, bool dd) {
+  if (dd) return fin_dd_bytes(S, learned);
   const size_t base = fin_base_bytes(S, lean);
-  const size_t need = ((size_t)S * S + 2 * CBP_MAX_S) * sizeof(c64);
+  const size_t need = ((size_t)S * S + 4 * CBP_MAX_K) * sizeof(c64);
   const size_t have = lean ? (size_t)(2 * S) * (2 * S) * sizeof(double) : (size_t)(2 * S) * (2 * S + 1) * sizeof(c64);
   return learned && need > have ? base + (need - have) : base;
 }
 
-size_t sample_lds_bytes(int N) {
-  return ((((size_t)(2 * N - 1) * sizeof(cdd)) + 15) & ~(size_t)15) + small_lds_bytes(N, false);
-}
-
-void set_recover_attrs() {
-  hipFuncSetAttribute((const void*)k_sample, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  hipFuncSetAttribute((const void*)k_finalize, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+size_t sample_lds_bytes(int N, bool dd) {
+  const size_t rho = (((size_t)(2 * N - 1) * sizeof(cdd)) + 15) & ~(size_t)15;
+  return rho + (dd ? blk_fixed_bytes() + blk_matrix_bytes(N) : small_lds_bytes(N, false));
 }
 
 hipError_t launch_diag_init(const batch_ref& br, int grid, hipStream_t st) {
@@ -889,9 +1065,40 @@ hipError_t launch_gram(const batch_ref& br, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_sample(const batch_ref& br, int grid, int maxN, hipStream_t st) {
+// Waves of the double-double solves of a launch whose largest order is n:
+// eight rows per wave, so the smallest built instance that holds it (more
+// waves would only wait at the barriers: order 20 takes 26 us on three waves
+// and 33 on four); a solve's result does not depend on which one runs it.
+template <template <int> class K>
+static void pick_waves(int n, dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int arg) {
+  if (n <= 16) K<2>::run(grid, lds, st, br, arg);
+  else if (n <= 24) K<3>::run(grid, lds, st, br, arg);
+  else if (n <= 32) K<4>::run(grid, lds, st, br, arg);
+  else if (n <= 40) K<5>::run(grid, lds, st, br, arg);
+  else K<8>::run(grid, lds, st, br, arg);
+}
+
+template <int C>
+struct run_sample_dd {
+  static const void* kernel() { return (const void*)k_sample_dd<C>; }
+  static void run(dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int) {
+    hipLaunchKernelGGL(k_sample_dd<C>, grid, dim3(64 * C), lds, st, br);
+  }
+};
+
+template <int C>
+struct run_finalize_dd {
+  static const void* kernel() { return (const void*)k_finalize<C, true>; }
+  static void run(dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int plain_only) {
+    hipLaunchKernelGGL((k_finalize<C, true>), grid, dim3(64 * C), lds, st, br, plain_only);
+  }
+};
+
+hipError_t launch_sample(const batch_ref& br, int grid, int maxN, bool dd, hipStream_t st) {
   prof_begin(PH_SAMPLE, st);
-  hipLaunchKernelGGL(k_sample, dim3(grid), dim3(SMALL_NT), sample_lds_bytes(maxN), st, br);
+  const size_t lds = sample_lds_bytes(maxN, dd);
+  if (dd) pick_waves<run_sample_dd>(maxN, dim3(grid), lds, st, br, 0);
+  else hipLaunchKernelGGL(k_sample, dim3(grid), dim3(SMALL_NT), lds, st, br);
   prof_end(PH_SAMPLE, st);
   return hipGetLastError();
 }
@@ -901,13 +1108,23 @@ hipError_t launch_judge(const batch_ref& br, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, int plain_only, bool lean,
+hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, int plain_only, bool lean, bool dd,
                            hipStream_t st) {
   prof_begin(PH_FINALIZE, st);
-  hipLaunchKernelGGL(k_finalize, dim3(grid), dim3(SMALL_NT), finalize_lds_bytes(maxS, learned, lean), st, br,
-                     plain_only);
+  const size_t lds = finalize_lds_bytes(maxS, learned, lean, dd);
+  if (dd) pick_waves<run_finalize_dd>(2 * maxS, dim3(grid), lds, st, br, plain_only);
+  else hipLaunchKernelGGL((k_finalize<4, false>), dim3(grid), dim3(256), lds, st, br, plain_only);
   prof_end(PH_FINALIZE, st);
   return hipGetLastError();
+}
+
+void set_recover_attrs() {
+  const void* fns[] = {(const void*)k_sample, (const void*)k_finalize<4, false>,
+                       run_sample_dd<2>::kernel(), run_sample_dd<3>::kernel(), run_sample_dd<4>::kernel(),
+                       run_sample_dd<5>::kernel(), run_sample_dd<8>::kernel(),
+                       run_finalize_dd<2>::kernel(), run_finalize_dd<3>::kernel(), run_finalize_dd<4>::kernel(),
+                       run_finalize_dd<5>::kernel(), run_finalize_dd<8>::kernel()};
+  for (const void* f : fns) hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
 }  // namespace cbp
