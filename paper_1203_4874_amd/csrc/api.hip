@@ -471,14 +471,13 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
   else CBP_TRY(launch_gram_mfma(br(Q_GRAMM), cv.grid[Q_GRAMM], cv.gram_fmt, cv.maxStride, st));
   CBP_TRY(launch_sample(br(Q_SAMPLE), cv.grid[Q_SAMPLE], cv.maxN, dd, st));
   if (cv.mlp) {
-    // the learned form: plain kernels (the fallback), the network's weights,
-    // the learned kernels, and the judge between them
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 1, cv.finLean, dd, st));
+    // the learned form: the network's weights, the plain kernels (the
+    // fallback) and the learned ones, and the judge between them
     CBP_TRY(launch_mlp_frames(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.mlp, st));
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 1, 0, cv.finLean, dd, st));
+    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 1, cv.finLean, dd, st));
     CBP_TRY(launch_judge(br(Q_FINALIZE), cv.grid[Q_FINALIZE], st));
   } else {
-    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, 0, cv.finLean, dd, st));
+    CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, cv.finLean, dd, st));
   }
   if (latent) {
     CBP_TRY(launch_kernel_dft<T>(br(Q_KRDFT), cv.grid[Q_KRDFT], st));

@@ -398,8 +398,8 @@ hipError_t launch_gram_expand(const batch_ref& br, int grid, double* out, hipStr
 hipError_t launch_sample(const batch_ref& br, int grid, int maxN, bool dd, hipStream_t st);
 // lean: every frame's scale solve runs without refinement or diagnostics
 // (matrix-core forms: its coupling block shares the solver's X region)
-hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, int plain_only, bool lean, bool dd,
-                           hipStream_t st);
+// learned: both the plain (fallback) and the learned kernels of every frame
+hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, bool lean, bool dd, hipStream_t st);
 // the learned form's judge: keeps the plain kernels where their per-sample
 // residual objective is smaller (items of Q_FINALIZE)
 hipError_t launch_judge(const batch_ref& br, int grid, hipStream_t st);

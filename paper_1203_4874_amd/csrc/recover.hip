@@ -910,17 +910,22 @@ __device__ inline __attribute__((always_inline)) void learned_assembly(const c64
   __syncthreads();
 }
 
-// Items: one per frame.  plain_only: the plain method's kernels into the
-// learned form's fallback slots (d.Kalt), ignoring the network's weights.
+// Items: one per frame.  learned: the launch holds two workgroups per item,
+// the first half taking the plain method's kernels into the learned form's
+// fallback slots (d.Kalt), the second the network's weights and d.K1 / d.K2:
+// the two solves of a frame run side by side instead of one after the other.
 template <int C, bool DD>
-__global__ __launch_bounds__(64 * C) void k_finalize(batch_ref br, int plain_only) {
+__global__ __launch_bounds__(64 * C) void k_finalize(batch_ref br, int learned) {
   extern __shared__ __attribute__((aligned(16))) char sm_fin[];
   __shared__ int bad_s[2];
-  for_items<Q_FINALIZE>(br, [&](const frame_desc& d, int) __attribute__((always_inline)) {
-    double* K1 = plain_only ? d.Kalt : d.K1;
-    double* K2 = plain_only ? d.Kalt + CBP_MAX_K * CBP_MAX_K : d.K2;
-    finalize_frame<C, DD>(d.xvec, d.S, d.k1, d.k2, d.pq, K1, K2, plain_only ? nullptr : d.diag, sm_fin,
-                          plain_only ? nullptr : d.wts, d.variant, bad_s);
+  const int G = learned ? (int)gridDim.x >> 1 : (int)gridDim.x;
+  const bool alt = learned && (int)blockIdx.x < G;
+  const int b = (int)blockIdx.x - (learned && !alt ? G : 0);
+  for_items_part<Q_FINALIZE>(br, b, G, [&](const frame_desc& d, int) __attribute__((always_inline)) {
+    double* K1 = alt ? d.Kalt : d.K1;
+    double* K2 = alt ? d.Kalt + CBP_MAX_K * CBP_MAX_K : d.K2;
+    finalize_frame<C, DD>(d.xvec, d.S, d.k1, d.k2, d.pq, K1, K2, alt ? nullptr : d.diag, sm_fin,
+                          alt ? nullptr : d.wts, d.variant, bad_s);
   });
 }
 
@@ -932,55 +937,71 @@ __global__ __launch_bounds__(64 * C) void k_finalize(batch_ref br, int plain_onl
 // the learned ones when their J is smaller, or when the frame is noisy (the
 // regime where the network does not gain).  Items: one per frame.
 constexpr float LEARNED_NOISY_F0 = -1.0f;
-__global__ __launch_bounds__(64) void k_judge(batch_ref br) {
+// One wave per (kernel set, pass, sample), sixteen in flight, the kernels in
+// LDS; the 2S terms of a set are then added in order.  (One wave per frame
+// took them one after the other: 330 us for 16 256x256 frames, 27 now.)
+// k1 + k2 <= 32 (the learned form).
+constexpr int JUDGE_WAVES = 16;
+constexpr int JUDGE_MAX_N = 32;
+__global__ __launch_bounds__(64 * JUDGE_WAVES) void k_judge(batch_ref br) {
   __shared__ c64 tw[CBP_MAX_S];
-  __shared__ c64 xs[CBP_MAX_N];
+  __shared__ c64 xs[JUDGE_WAVES][JUDGE_MAX_N];
+  __shared__ cdd rho[JUDGE_WAVES][2 * JUDGE_MAX_N - 1];
+  __shared__ double Ks[2][JUDGE_MAX_N * JUDGE_MAX_N];   // k1^2 + k2^2 <= (k1 + k2)^2
+  __shared__ double term[2][2 * CBP_MAX_S];
+  __shared__ double Js[2];
   for_items<Q_FINALIZE>(br, [&](const frame_desc& d, int) __attribute__((always_inline)) {
     const int S = d.S, k1 = d.k1, k2 = d.k2, N = k1 + k2, NL = 2 * N - 1;
-    const int l = threadIdx.x;
+    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+    const int n1 = k1 * k1, n12 = n1 + k2 * k2;
     unit_twiddles(tw, S);
-    __syncthreads();
-    double J[2];
-    for (int set = 0; set < 2; ++set) {
-      const double* A1 = set ? d.K1 : d.Kalt;
-      const double* A2 = set ? d.K2 : d.Kalt + CBP_MAX_K * CBP_MAX_K;
-      double acc = 0.0;
-      for (int pass = 0; pass < 2; ++pass)
-        for (int j = 0; j < S; ++j) {
-          if (l < N) {
-            const bool u = l < k2;
-            const double* K = u ? A2 : A1;
-            const int k = u ? k2 : k1, c = u ? l : l - k2;
-            c64 sacc = {0.0, 0.0};
-            int t = 0;
-            for (int r = 0; r < k; ++r) {
-              const double kv = pass == 0 ? K[r * k + c] : K[c * k + r];   // along y (pass X) or x (pass Y)
-              sacc = sacc + c64{kv * tw[t].re, kv * tw[t].im};
-              t += j;
-              if (t >= S) t -= S;
-            }
-            xs[l] = sacc;
-          }
-          __syncthreads();
-          const gram_acc G{d.corr + ((size_t)pass * S + j) * NL, k1, k2};
-          double num = 0.0, nx = 0.0;
-          if (l < N) {
-            c64 y = {0.0, 0.0};
-            for (int q = 0; q < N; ++q) {
-              const cdd g = G.get(l, q);
-              y = y + c64{dd_val(g.re), dd_val(g.im)} * xs[q];
-            }
-            const c64 xl = xs[l];
-            num = xl.re * y.re + xl.im * y.im;   // Re(conj(x_l) y_l)
-            nx = norm2(xl);
-          }
-          num = wsum(num);
-          nx = wsum(nx);
-          acc += num / nx;
-          __syncthreads();
-        }
-      J[set] = acc;
+    for (int e = tid; e < n12; e += blockDim.x) {
+      Ks[0][e] = e < n1 ? d.Kalt[e] : d.Kalt[CBP_MAX_K * CBP_MAX_K + e - n1];
+      Ks[1][e] = e < n1 ? d.K1[e] : d.K2[e - n1];
     }
+    __syncthreads();
+    for (int t = wv; t < 4 * S; t += JUDGE_WAVES) {
+      const int set = t / (2 * S), pj = t - set * 2 * S, pass = pj / S, j = pj - pass * S;
+      for (int i = l; i < NL; i += 64) rho[wv][i] = d.corr[(size_t)pj * NL + i];
+      if (l < N) {
+        const bool u = l < k2;
+        const double* K = u ? Ks[set] + n1 : Ks[set];
+        const int k = u ? k2 : k1, c = u ? l : l - k2;
+        c64 sacc = {0.0, 0.0};
+        int tt = 0;
+        for (int r = 0; r < k; ++r) {
+          const double kv = pass == 0 ? K[r * k + c] : K[c * k + r];   // along y (pass X) or x (pass Y)
+          sacc = sacc + c64{kv * tw[tt].re, kv * tw[tt].im};
+          tt += j;
+          if (tt >= S) tt -= S;
+        }
+        xs[wv][l] = sacc;
+      }
+      wave_sync();
+      const gram_acc G{rho[wv], k1, k2};
+      double num = 0.0, nx = 0.0;
+      if (l < N) {
+        c64 y = {0.0, 0.0};
+        for (int q = 0; q < N; ++q) {
+          const cdd g = G.get(l, q);
+          y = y + c64{dd_val(g.re), dd_val(g.im)} * xs[wv][q];
+        }
+        const c64 xl = xs[wv][l];
+        num = xl.re * y.re + xl.im * y.im;   // Re(conj(x_l) y_l)
+        nx = norm2(xl);
+      }
+      num = wsum(num);
+      nx = wsum(nx);
+      if (l == 0) term[set][pj] = num / nx;
+      wave_sync();
+    }
+    __syncthreads();
+    if (tid < 2) {
+      double acc = 0.0;
+      for (int t = 0; t < 2 * S; ++t) acc += term[tid][t];
+      Js[tid] = acc;
+    }
+    __syncthreads();
     // the network's weights are used only on frames without a noise floor:
     // when more than half of the 2S samples have lambda_0 / lambda_max above
     // 1e-10 (spectrum feature f_0 > -1) the plain kernels are kept
@@ -988,14 +1009,15 @@ __global__ __launch_bounds__(64) void k_judge(batch_ref br) {
     const bool noisy = wsum(f0 > LEARNED_NOISY_F0 ? 1.0 : 0.0) > (double)S;
     // NaN-safe: the learned kernels are kept only when their objective is a
     // number no larger than the plain one's
-    const bool fallback = noisy || !(J[1] <= J[0]);
-    if (fallback) {
-      for (int e = l; e < k1 * k1; e += 64) d.K1[e] = d.Kalt[e];
-      for (int e = l; e < k2 * k2; e += 64) d.K2[e] = d.Kalt[CBP_MAX_K * CBP_MAX_K + e];
-    }
-    if (l == 0 && d.diag) {
-      d.diag->judge[0] = J[0];
-      d.diag->judge[1] = J[1];
+    const bool fallback = noisy || !(Js[1] <= Js[0]);
+    if (fallback)
+      for (int e = tid; e < n12; e += blockDim.x) {
+        if (e < n1) d.K1[e] = Ks[0][e];
+        else d.K2[e - n1] = Ks[0][e];
+      }
+    if (tid == 0 && d.diag) {
+      d.diag->judge[0] = Js[0];
+      d.diag->judge[1] = Js[1];
       if (fallback) atomicOr(&d.diag->flags, CBP_DIAG_FALLBACK);
     }
   });
@@ -1089,8 +1111,8 @@ struct run_sample_dd {
 template <int C>
 struct run_finalize_dd {
   static const void* kernel() { return (const void*)k_finalize<C, true>; }
-  static void run(dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int plain_only) {
-    hipLaunchKernelGGL((k_finalize<C, true>), grid, dim3(64 * C), lds, st, br, plain_only);
+  static void run(dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int learned) {
+    hipLaunchKernelGGL((k_finalize<C, true>), grid, dim3(64 * C), lds, st, br, learned);
   }
 };
 
@@ -1104,16 +1126,16 @@ hipError_t launch_sample(const batch_ref& br, int grid, int maxN, bool dd, hipSt
 }
 
 hipError_t launch_judge(const batch_ref& br, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(k_judge, dim3(grid), dim3(64), 0, st, br);
+  hipLaunchKernelGGL(k_judge, dim3(grid), dim3(64 * JUDGE_WAVES), 0, st, br);
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, int plain_only, bool lean, bool dd,
-                           hipStream_t st) {
+hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned, bool lean, bool dd, hipStream_t st) {
   prof_begin(PH_FINALIZE, st);
   const size_t lds = finalize_lds_bytes(maxS, learned, lean, dd);
-  if (dd) pick_waves<run_finalize_dd>(2 * maxS, dim3(grid), lds, st, br, plain_only);
-  else hipLaunchKernelGGL((k_finalize<4, false>), dim3(grid), dim3(256), lds, st, br, plain_only);
+  const dim3 g(learned ? 2 * grid : grid);
+  if (dd) pick_waves<run_finalize_dd>(2 * maxS, g, lds, st, br, learned);
+  else hipLaunchKernelGGL((k_finalize<4, false>), g, dim3(256), lds, st, br, learned);
   prof_end(PH_FINALIZE, st);
   return hipGetLastError();
 }
