@@ -417,7 +417,6 @@ dev_state* get_dev() {
     set_recover_attrs();
     set_fft_attrs();
     set_gram_mfma_attrs();
-    set_size_attrs();
     set_encoder_attrs();
     f.ready = true;
   }
@@ -1124,14 +1123,7 @@ cbp_status cbp_estimate_kernel_sizes(const cbp_image* b1, const cbp_image* b2, c
   const cbp_status s = build_batch(reqs, &o, kDefaultTuning, status, &bb, true);
   if (s != CBP_OK) return s;
   if (status[0] != CBP_OK) return status[0];
-  // the probe's items: (candidate, pass, sample)
-  const int items = c.n * 2 * S;
-  int* starts = (int*)(bb.head.data() + head_desc_bytes(1));
-  starts[Q_SIZE_PROBE * 2] = 0;
-  starts[Q_SIZE_PROBE * 2 + 1] = items;
-  chunk_view& cv = bb.chunks[0];
-  cv.items[Q_SIZE_PROBE] = items;
-  cv.grid[Q_SIZE_PROBE] = grid_for(items, 0);
+  const chunk_view& cv = bb.chunks[0];
   int nmax = 1;
   for (int i = 0; i < c.n; ++i) nmax = std::max(nmax, 2 * c.k1[i] - d);
   const int NL = 2 * (K1 + (K1 - d)) - 1;
@@ -1154,7 +1146,7 @@ cbp_status cbp_estimate_kernel_sizes(const cbp_image* b1, const cbp_image* b2, c
     }
     CBP_TRY(launch_eval_cols(br, cv.grid[Q_EVAL_COLS], st));
     CBP_TRY(launch_gram(br, cv.grid[Q_GRAM], st));
-    CBP_TRY(launch_size_probe(br, cv.grid[Q_SIZE_PROBE], c, nmax, NL, rat, st));
+    CBP_TRY(launch_size_probe(br, c, S, nmax, NL, rat, st));
     CBP_TRY(launch_size_decide(c, S, rat, result, st));
     return hipSuccess;
   };

@@ -251,8 +251,9 @@ __device__ inline double block_spectrum(const blk_ws& s, int n, double ghi) {
 // ---------------------------------------------------------------- 1. reduction
 // Steps k = o - 1 of the Householder reduction with o >> 3 == I0 (the columns
 // of groups i >= I0 are live).  v0 holds column k of the rows >= o, zero
-// elsewhere, on entry; el collects e_k in lane k of every wave.
-template <int C, int I0>
+// elsewhere, on entry; el collects e_k in lane k of every wave.  Q: accumulate the
+// unitary in w.
+template <int C, int I0, bool Q>
 __device__ inline __attribute__((always_inline)) void block_reflectors(const blk_ws& s, int n, c64* a, c64* w, c64& el) {
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, r = tid >> 3, q = tid & 7;
   const int o1 = min(8 * I0 + 8, n - 1);
@@ -283,14 +284,16 @@ __device__ inline __attribute__((always_inline)) void block_reflectors(const blk
 #pragma unroll
     for (int i = I0; i < C; ++i) {
       p = cfma(a[i], u[i], p);
-      z = cfma(w[i], u[i], z);
+      if (Q) z = cfma(w[i], u[i], z);
     }
     p = sum8(p);
     p = {beta * p.re, beta * p.im};
     s.v1[r] = p;
     s.part[wv] = sum_rows(cdotr(ur, p));
-    z = sum8(z);
-    z = {beta * z.re, beta * z.im};
+    if (Q) {
+      z = sum8(z);
+      z = {beta * z.re, beta * z.im};
+    }
     __syncthreads();
     c64 wc[C];
 #pragma unroll
@@ -307,10 +310,60 @@ __device__ inline __attribute__((always_inline)) void block_reflectors(const blk
         *at = csel(r > o, a[I0], c64{0.0, 0.0});
       }
     }
+    if (Q) {
 #pragma unroll
-    for (int i = I0; i < C; ++i) w[i] = cfms_bc(z, u[i], w[i]);
+      for (int i = I0; i < C; ++i) w[i] = cfms_bc(z, u[i], w[i]);
+    }
   }
-  if constexpr (I0 + 1 < C) block_reflectors<C, I0 + 1>(s, n, a, w, el);
+  if constexpr (I0 + 1 < C) block_reflectors<C, I0 + 1, Q>(s, n, a, w, el);
+}
+
+// Tridiagonal form of the matrix with entries a (thread (r, q): columns q + 8
+// i): its diagonal and complex off-diagonal to the lanes of every wave.
+template <int C, bool Q>
+__device__ inline __attribute__((always_inline)) void block_tridiag(const blk_ws& s, int n, c64* a, c64* w, c64& el,
+                                                                    double& al) {
+  const int tid = threadIdx.x, l = tid & 63, r = tid >> 3, q = tid & 7;
+  if (tid < 64) {
+    s.v0[tid] = {0.0, 0.0};
+    s.v1[tid] = {0.0, 0.0};
+  }
+  __syncthreads();
+  if (q == 0) s.v0[r] = csel(r > 0, a[0], c64{0.0, 0.0});
+  el = {0.0, 0.0};
+  block_reflectors<C, 0, Q>(s, n, a, w, el);
+  __syncthreads();
+  // v0: column n - 2, whose last entry is e_(n-2)
+  if (n > 1 && l == n - 2) el = s.v0[n - 1];
+  double* dg = (double*)s.v1;
+#pragma unroll
+  for (int i = 0; i < C; ++i)
+    if (q + 8 * i == r) dg[r] = a[i].re;
+  __syncthreads();
+  al = l < n ? dg[l] : 0.0;
+}
+
+// lambda_min / lambda_max of the Hermitian positive semidefinite matrix with
+// entries a (see block_tridiag), as small_extreme_ratio: the midpoints of
+// their brackets, the first wave bisecting one and the second the other.
+// Valid in every thread; 0 for a zero matrix.
+template <int C>
+__device__ inline __attribute__((always_inline)) double block_extreme_ratio(const blk_ws& s, int n, c64* a) {
+  const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+  c64 el;
+  double al, glo, ghi, tn, lo, hi;
+  block_tridiag<C, false>(s, n, a, a, el, al);
+  int ex;
+  scale_tridiag(s, n, al, l < n - 1 ? sqrt(cnorm2(el)) : 0.0, &ex, &glo, &ghi, &tn);
+  __syncthreads();
+  if (wv < 2) {
+    bisect_minors(s, n, wv == 0 ? 1 : n, glo, ghi, tn, &lo, &hi);
+    if (n == 1) lo = hi = s.ab[0].x;
+    s.part[wv] = 0.5 * (lo + hi);
+  }
+  __syncthreads();
+  const double lmin = fmax(s.part[0], 0.0), lmax = s.part[1];
+  return lmax > 0.0 ? lmin / lmax : 0.0;
 }
 
 // ---------------------------------------------------------------- the solver
@@ -328,7 +381,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
   *lam1 = __builtin_nan("");
   *steps = 0;
   c64 w[C];
-  c64 el = {0.0, 0.0};     // e_l in lane l
+  c64 el;                  // e_l in lane l
   double al_;              // a_l in lane l
   {
     c64 a[C];
@@ -342,22 +395,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
       }
       w[i] = {r == c ? 1.0 : 0.0, 0.0};
     }
-    if (tid < 64) {
-      s.v0[tid] = {0.0, 0.0};
-      s.v1[tid] = {0.0, 0.0};
-    }
-    __syncthreads();
-    if (q == 0) s.v0[r] = csel(r > 0, a[0], c64{0.0, 0.0});
-    block_reflectors<C, 0>(s, n, a, w, el);
-    __syncthreads();
-    // v0: column n - 2, whose last entry is e_(n-2); the diagonal to lanes
-    if (n > 1 && l == n - 2) el = s.v0[n - 1];
-    double* dg = (double*)s.v1;
-#pragma unroll
-    for (int i = 0; i < C; ++i)
-      if (q + 8 * i == r) dg[r] = a[i].re;
-    __syncthreads();
-    al_ = l < n ? dg[l] : 0.0;
+    block_tridiag<C, true>(s, n, a, w, el, al_);
   }
   const double bl_ = l < n - 1 ? sqrt(cnorm2(el)) : 0.0;
   int ex;

@@ -23,7 +23,7 @@ namespace cbp {
 // Work queues, one per kernel.
 enum queue_id {
   Q_DIAG = 0, Q_FOLD, Q_EVAL_COLS, Q_EVAL_ROWS, Q_ROW_FWD, Q_GRAM, Q_GRAMM, Q_SAMPLE, Q_FINALIZE, Q_COL,
-  Q_ROW_INV, Q_TWID, Q_SIZE_PROBE, Q_KRDFT, Q_COUNT
+  Q_ROW_INV, Q_TWID, Q_KRDFT, Q_COUNT
 };
 
 // Frames per batched launch (the item prefix sums of one launch sit in LDS).
@@ -116,7 +116,6 @@ inline int queue_items(int q, const frame_plan& p) {
     case Q_COL: return ((p.hx + p.cw - 1) / p.cw) * p.nch;
     case Q_ROW_INV: return ((p.m + 1) / 2) * p.nch;
     case Q_TWID: return (p.Px + 255) / 256;
-    case Q_SIZE_PROBE: return 0;   // set by the size-estimation entry point (candidates x 2S)
     case Q_KRDFT: return (p.hx * 2 * CBP_MAX_K + 255) / 256;
   }
   return 0;
@@ -445,17 +444,14 @@ struct size_cands {
   int d;                 // k1 - k2 = H1 - H2
   int k1[CBP_MAX_K];
 };
-hipError_t launch_size_probe(const batch_ref& br, int grid, const size_cands& c, int nmax, int NLmax, double* ratios,
+hipError_t launch_size_probe(const batch_ref& br, const size_cands& c, int S, int nmax, int NL, double* ratios,
                              hipStream_t st);
 hipError_t launch_size_decide(const size_cands& c, int S, const double* ratios, cbp_size_result* out,
                               hipStream_t st);
-size_t size_probe_lds_bytes(int nmax, int NLmax);
-void set_size_attrs();
 
 // encoder.hip: the encoder's kernel draws, the blur and the 8-bit streams.
 hipError_t launch_draw_pairs(unsigned long long seed, long long frame0, int nframes, int k1, int k2, int S,
                              double* K1s, double* K2s, int* attempts, double* min_ratio, hipStream_t st);
-size_t draw_pairs_lds_bytes(int k1, int k2);
 void set_encoder_attrs();
 template <typename T>
 hipError_t launch_blur(const T* L, int64_t lp, int64_t lcs, int m, int n, int nch, const double* K1, int k1,

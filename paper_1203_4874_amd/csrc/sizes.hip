@@ -12,14 +12,15 @@
 // its entries are the same block-Toeplitz correlations (recover.hip), so one
 // set of double-double correlations serves every candidate.
 //
-// k_size_probe: one wave per (candidate, pass, sample): G(k) from the
-//   correlations (rounded to FP64), Householder tridiagonalisation, Sturm
-//   multisection for the smallest and the largest eigenvalue.
-// k_size_decide: one wave: per candidate the median over the 2S samples of
-//   log10(max(s, 1e-13)); the estimate is the candidate with the largest
+// k_size_probe: one workgroup per (candidate, pass, sample): G(k) from the
+//   correlations (rounded to FP64), Householder tridiagonalisation on
+//   ceil(n / 8) waves (eigblock.h), Sturm multisection for the smallest and the
+//   largest eigenvalue.
+// k_size_decide: per candidate (one wave each) the median over the 2S samples
+//   of log10(max(s, 1e-13)); the estimate is the candidate with the largest
 //   drop from the previous candidate's score (0 before the first); a largest
 //   drop below 2 decades means no candidate made the systems singular.
-#include "eigsmall.h"
+#include "eigblock.h"
 #include "internal.h"
 
 namespace cbp {
@@ -50,52 +51,71 @@ __device__ inline cdd trial_gram(const cdd* rho, int K1, int K2, int n1, int r, 
   return v;
 }
 
-__global__ __launch_bounds__(SMALL_NT) void k_size_probe(batch_ref br, size_cands cands, double* ratios) {
-  extern __shared__ __attribute__((aligned(16))) char sm_probe[];
-  for_items<Q_SIZE_PROBE>(br, [&](const frame_desc& d, int item) __attribute__((always_inline)) {
-    const int S = d.S, K1 = d.k1, K2 = d.k2;
-    const int NL = 2 * (K1 + K2) - 1;
-    const int ci = item / (2 * S), rest = item - ci * 2 * S;
-    const int pass = rest / S, j = rest - pass * S;
-    const int k = cands.k1[ci];
-    const int n2 = k, n1 = k - cands.d, n = n1 + n2;
-    const int l = threadIdx.x;
-    cdd* rho = (cdd*)sm_probe;
-    small_ws w = small_probe_carve(sm_probe + (((size_t)NL * sizeof(cdd) + 15) & ~(size_t)15), n);
-    for (int t = l; t < NL; t += SMALL_NT) rho[t] = d.corr[((size_t)pass * S + j) * NL + t];
-    __syncthreads();
-    for (int e = l; e < n * n; e += SMALL_NT) {
-      const int r = e / n, c = e - r * n;
-      const cdd g = trial_gram(rho, K1, K2, n1, r, c);
-      w.A[e] = {g.re.hi, g.im.hi};
-    }
-    __syncthreads();
-    const double r = small_extreme_ratio(w, n);
-    if (l == 0) ratios[((size_t)ci * 2 + pass) * S + j] = r;
-  });
+// s of one system on its C waves (see block_extreme_ratio).
+template <int C>
+__device__ inline double probe_ratio(const blk_ws& w, const cdd* rho, int K1, int K2, int n1, int n) {
+  const int r = (int)threadIdx.x >> 3, q = threadIdx.x & 7;
+  c64 a[C];
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    const int c = q + 8 * i;
+    const bool in = r < n && c < n;
+    const cdd g = trial_gram(rho, K1, K2, n1, in ? r : 0, in ? c : 0);
+    a[i] = csel(in, c64{g.re.hi, g.im.hi}, c64{0.0, 0.0});
+  }
+  return block_extreme_ratio<C>(w, n, a);
 }
 
-// One wave: scores, drops and the decision.  ratios [ncand][2][S].
-__global__ __launch_bounds__(SMALL_NT) void k_size_decide(size_cands cands, int S, const double* ratios,
-                                                           cbp_size_result* out) {
-  __shared__ double v[CBP_MAX_K][2 * CBP_MAX_S];
+// Workgroups of 64 waves_max threads, one per item (candidate, pass, sample)
+// of the launch's one frame, the largest candidates (the longest solves)
+// first.  The waves beyond ceil(n / 8) of an item end at once (a barrier waits
+// for the surviving waves), so small candidates cost what they need.  Bound by
+// the reflectors' dependent chain; one wave per item took 256 us for the nine
+// odd candidates 9 .. 25 with S = 25, this split 97.
+__global__ __launch_bounds__(64 * BLK_MAX_WAVES) void k_size_probe(batch_ref br, size_cands cands, double* ratios) {
+  extern __shared__ __attribute__((aligned(16))) char sm_probe[];
+  const frame_desc& d = br.descs[0];
+  const int S = d.S, K1 = d.k1, K2 = d.k2, NL = 2 * (K1 + K2) - 1;
+  const int ci = cands.n - 1 - (int)blockIdx.x / (2 * S), pj = (int)blockIdx.x % (2 * S);
+  const int k = cands.k1[ci], n1 = k - cands.d, n = n1 + k;
+  const int C = n <= 16 ? 2 : n <= 24 ? 3 : n <= 32 ? 4 : n <= 40 ? 5 : 8;
+  if ((int)threadIdx.x >= 64 * C) return;
+  cdd* rho = (cdd*)sm_probe;
+  for (int t = threadIdx.x; t < NL; t += 64 * C) rho[t] = d.corr[(size_t)pj * NL + t];
+  char* fixed = sm_probe + (((size_t)NL * sizeof(cdd) + 15) & ~(size_t)15);
+  const blk_ws w = blk_carve(fixed, nullptr);
+  __syncthreads();
+  double r;
+  if (C == 2) r = probe_ratio<2>(w, rho, K1, K2, n1, n);
+  else if (C == 3) r = probe_ratio<3>(w, rho, K1, K2, n1, n);
+  else if (C == 4) r = probe_ratio<4>(w, rho, K1, K2, n1, n);
+  else if (C == 5) r = probe_ratio<5>(w, rho, K1, K2, n1, n);
+  else r = probe_ratio<8>(w, rho, K1, K2, n1, n);
+  if (threadIdx.x == 0) ratios[(size_t)ci * 2 * S + pj] = r;
+}
+
+// Scores (one wave per candidate: a lane's value has as many smaller ones --
+// or equal ones in lower lanes -- as its rank), drops and the decision.
+// ratios [ncand][2][S].
+constexpr int DECIDE_WAVES = 16;
+__global__ __launch_bounds__(64 * DECIDE_WAVES) void k_size_decide(size_cands cands, int S, const double* ratios,
+                                                                    cbp_size_result* out) {
+  __shared__ double mid[CBP_MAX_K][2];
   __shared__ double score[CBP_MAX_K];
   const int l = threadIdx.x, nc = cands.n, m = 2 * S;
-  if (l < nc) {
-    // this lane's candidate: floored logs, insertion sort, median
-    double* x = v[l];
-    for (int t = 0; t < m; ++t) {
-      const double r = ratios[(size_t)l * m + t];
-      const double y = log10(fmax(r, kSizeFloor));
-      int u = t;
-      while (u > 0 && x[u - 1] > y) {
-        x[u] = x[u - 1];
-        --u;
-      }
-      x[u] = y;
+  for (int c = threadIdx.x >> 6; c < nc; c += DECIDE_WAVES) {
+    const int i = threadIdx.x & 63;
+    const double y = i < m ? log10(fmax(ratios[(size_t)c * m + i], kSizeFloor)) : 0.0;
+    int rank = 0;
+    for (int u = 0; u < m; ++u) {
+      const double v = readlane_d(y, u);
+      rank += (v < y || (v == y && u < i)) ? 1 : 0;
     }
-    score[l] = (m & 1) ? x[m / 2] : 0.5 * (x[m / 2 - 1] + x[m / 2]);
+    if (i < m && rank == m / 2 - 1) mid[c][0] = y;   // m = 2S: the middle two
+    if (i < m && rank == m / 2) mid[c][1] = y;
   }
+  __syncthreads();
+  if (l < nc) score[l] = 0.5 * (mid[l][0] + mid[l][1]);
   __syncthreads();
   if (l == 0) {
     int best = 0;
@@ -127,25 +147,20 @@ __global__ __launch_bounds__(SMALL_NT) void k_size_decide(size_cands cands, int 
 
 }  // namespace
 
-size_t size_probe_lds_bytes(int nmax, int NLmax) {
-  return (((size_t)NLmax * sizeof(cdd) + 15) & ~(size_t)15) + small_probe_lds_bytes(nmax);
+size_t size_probe_lds_bytes(int NL) {
+  return (((size_t)NL * sizeof(cdd) + 15) & ~(size_t)15) + blk_fixed_bytes();
 }
 
-void set_size_attrs() {
-  hipFuncSetAttribute((const void*)k_size_probe, hipFuncAttributeMaxDynamicSharedMemorySize,
-                      (int)size_probe_lds_bytes(CBP_MAX_N, 2 * CBP_MAX_N - 1));
-}
-
-hipError_t launch_size_probe(const batch_ref& br, int grid, const size_cands& c, int nmax, int NLmax, double* ratios,
+hipError_t launch_size_probe(const batch_ref& br, const size_cands& c, int S, int nmax, int NL, double* ratios,
                              hipStream_t st) {
-  const size_t lds = size_probe_lds_bytes(nmax, NLmax);
-  hipLaunchKernelGGL(k_size_probe, dim3(grid), dim3(SMALL_NT), lds, st, br, c, ratios);
+  const int waves = nmax <= 16 ? 2 : nmax <= 24 ? 3 : nmax <= 32 ? 4 : nmax <= 40 ? 5 : 8;
+  hipLaunchKernelGGL(k_size_probe, dim3(c.n * 2 * S), dim3(64 * waves), size_probe_lds_bytes(NL), st, br, c, ratios);
   return hipGetLastError();
 }
 
 hipError_t launch_size_decide(const size_cands& c, int S, const double* ratios, cbp_size_result* out,
                               hipStream_t st) {
-  hipLaunchKernelGGL(k_size_decide, dim3(1), dim3(SMALL_NT), 0, st, c, S, ratios, out);
+  hipLaunchKernelGGL(k_size_decide, dim3(1), dim3(64 * DECIDE_WAVES), 0, st, c, S, ratios, out);
   return hipGetLastError();
 }
 
