@@ -342,7 +342,7 @@ __device__ inline int sturm_count(const double* a, const double* b, int n, doubl
 // 64 probes per round.  Returns ||T|| (Gershgorin bound) in *tn.
 __device__ inline void small_bisect(const small_ws& s, int n, int target, double* lo_out, double* hi_out,
                                     double* tn_out) {
-  const int l = threadIdx.x;
+  const int l = threadIdx.x & 63;   // (any wave of the workgroup)
   double glo = 1.7976931348623157e308, ghi = -1.7976931348623157e308, bmax = 0.0;
   if (l < n) {
     const double bl = l > 0 ? s.b[l - 1] : 0.0, br = s.b[l];

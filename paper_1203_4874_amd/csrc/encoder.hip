@@ -2,15 +2,17 @@
 // sensor noise) and the multi-level 8-bit streams (Sec. 3, multi-level
 // security).
 //
-// k_draw_pairs: one wave per frame draws the frame's kernel pair from the
-//   counter-based generator Philox4x64-10 (Salmon, Moraes, Dror and Shaw,
+// k_draw_first, k_draw_probe, k_draw_again: draw each frame's kernel pair from
+//   the counter-based generator Philox4x64-10 (Salmon, Moraes, Dror and Shaw,
 //   SC 2011) -- entry e of kernel s, attempt a, is word e mod 4 of
 //   Philox(counter (e / 4, s, a, 0), key (seed, frame)), u = ((w >> 11) + 1/2)
 //   2^-53, normalised to sum 1 in entry order -- and redraws (a + 1) while at
 //   some sample w_j of either evaluation order the Sylvester system of the two
 //   kernel slices, [C_{k2-1}(p) | -C_{k1-1}(q)], has lambda_min / lambda_max
 //   of its Gram below 1e-12 (the slices nearly share a root, so the pair is
-//   not safely coprime).
+//   not safely coprime).  Nearly every pair passes at its first draw, so that
+//   draw's 2S solves run as one workgroup each; only the frames that failed one
+//   go on, one wave per frame.
 // k_blur: B_s = L (x) K_s, full linear convolution of every channel with
 //   both kernels, from LDS tiles of the latent (16 x 64 outputs per
 //   workgroup, four rows per thread; each input column of the tile read once
@@ -18,6 +20,8 @@
 // k_quantize / k_dequantize: the 8-bit stream of a level without the b
 //   least significant bits, q = clamp(rint(255 B), 0, 255) & (255 << b), and
 //   the receiver's q / 255.
+#include <algorithm>
+
 #include "eigsmall.h"
 #include "internal.h"
 
@@ -70,7 +74,7 @@ __device__ inline double draw_entry(unsigned long long seed, unsigned long long 
 // on lane 0, then the division.
 __device__ inline void draw_kernel(double* K, int k, unsigned long long seed, unsigned long long frame, int stream,
                                    int attempt, double* sum_slot) {
-  for (int e = threadIdx.x; e < k * k; e += SMALL_NT) K[e] = draw_entry(seed, frame, stream, attempt, e);
+  for (int e = threadIdx.x; e < k * k; e += blockDim.x) K[e] = draw_entry(seed, frame, stream, attempt, e);
   __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
@@ -79,94 +83,170 @@ __device__ inline void draw_kernel(double* K, int k, unsigned long long seed, un
   }
   __syncthreads();
   const double s = *sum_slot;
-  for (int e = threadIdx.x; e < k * k; e += SMALL_NT) K[e] = K[e] / s;
+  for (int e = threadIdx.x; e < k * k; e += blockDim.x) K[e] = K[e] / s;
   __syncthreads();
 }
 
-// LDS of k_draw_pairs: two kernels, two slices, the correlations, a sum slot
-// and the reduction workspace of order k1 + k2 - 2.
+// LDS of a probe: two kernels, two slices, the correlations, a sum slot and
+// the reduction workspace of order k1 + k2 - 2.
 __host__ __device__ inline size_t draw_lds_bytes(int k1, int k2) {
   const int n = k1 + k2 - 2 > 1 ? k1 + k2 - 2 : 1;
   return (size_t)(k1 * k1 + k2 * k2 + 2) * sizeof(double) + 2 * (size_t)CBP_MAX_K * sizeof(c64) +
          (size_t)(2 * CBP_MAX_N) * sizeof(c64) + small_probe_lds_bytes(n) + 16;
 }
 
-__global__ __launch_bounds__(SMALL_NT) void k_draw_pairs(unsigned long long seed, long long frame0, int k1, int k2,
+struct draw_lds {
+  double* K1;
+  double* K2;
+  double* sum_slot;
+  c64* p;
+  c64* q;
+  c64* rho;   // [rho_pp (k1), rho_qq (k2), rho_pq (k1 + k2 - 1)]
+  small_ws w;
+};
+
+__device__ inline draw_lds draw_carve(char* base, int k1, int k2) {
+  const int n = k1 + k2 - 2;
+  draw_lds d;
+  d.K1 = (double*)base;
+  d.K2 = d.K1 + k1 * k1;
+  d.sum_slot = d.K2 + k2 * k2;
+  d.p = (c64*)(((size_t)(d.sum_slot + 2) + 15) & ~(size_t)15);
+  d.q = d.p + CBP_MAX_K;
+  d.rho = d.q + CBP_MAX_K;
+  d.w = small_probe_carve((char*)(d.rho + 2 * CBP_MAX_N), n > 1 ? n : 1);
+  return d;
+}
+
+// The Gram of the Sylvester system of the kernel slices at sample j of a pass
+// (pass 0 evaluates along y, a polynomial in x; pass 1 along x) into w.A.
+__device__ inline void sylvester_gram(const draw_lds& d, int k1, int k2, int S, int pass, int j) {
+  const int l = threadIdx.x, nt = blockDim.x;
+  const int n1 = k2 - 1, n2 = k1 - 1, n = n1 + n2;
+  if (l < k1 + k2) {
+    const bool first = l < k1;
+    const int k = first ? k1 : k2, t = first ? l : l - k1;
+    const double* K = first ? d.K1 : d.K2;
+    c64 acc = {0.0, 0.0};
+    for (int r = 0; r < k; ++r) {
+      double sn, cs;
+      sincospi(-2.0 * (double)((j * r) % S) / (double)S, &sn, &cs);
+      const double kv = pass == 0 ? K[r * k + t] : K[t * k + r];
+      acc = acc + c64{kv * cs, kv * sn};
+    }
+    (first ? d.p : d.q)[t] = acc;
+  }
+  __syncthreads();
+  // correlations rho_pp(l) (l < k1), rho_qq(l) (l < k2), rho_pq(l), l in [-(n2 - 1), n1 - 1]
+  for (int t = l; t < k1 + k2 + n - 1; t += nt) {
+    const c64* x;
+    const c64* y;
+    int lag, lx, ly;
+    if (t < k1) { x = d.p; y = d.p; lag = t; lx = k1; ly = k1; }
+    else if (t < k1 + k2) { x = d.q; y = d.q; lag = t - k1; lx = k2; ly = k2; }
+    else { x = d.p; y = d.q; lag = t - (k1 + k2) - (n2 - 1); lx = k1; ly = k2; }
+    c64 acc = {0.0, 0.0};
+    for (int s0 = max(0, -lag); s0 < lx && s0 + lag < ly; ++s0) acc = acc + cmulc(x[s0], y[s0 + lag]);
+    d.rho[t] = acc;
+  }
+  __syncthreads();
+  for (int e = l; e < n * n; e += nt) {
+    const int r = e / n, c = e - r * n;
+    const bool ra = r < n1, ca = c < n1;
+    const int pr = ra ? r : r - n1, pc = ca ? c : c - n1;
+    c64 v;
+    if (ra == ca) {
+      // rho_pp has k1 lags, rho_qq k2; longer lags are zero
+      const int lag = pr - pc, al = lag < 0 ? -lag : lag;
+      v = al < (ra ? k1 : k2) ? d.rho[(ra ? 0 : k1) + al] : c64{0.0, 0.0};
+      if (lag < 0) v.im = -v.im;
+    } else {
+      const int cross = k1 + k2 + (n2 - 1);
+      v = ra ? d.rho[cross + pr - pc] : conj(d.rho[cross + pc - pr]);
+      v = c64{-v.re, -v.im};
+    }
+    d.w.A[e] = v;
+  }
+  __syncthreads();
+}
+
+constexpr int DRAW_FAILED = 0x40000000;   // in attempts[f] between the launches
+
+// Attempt 0 of every frame.  One workgroup per kernel (2 f + stream - 1),
+// bound by the ordered sum of its entries.
+__global__ __launch_bounds__(256) void k_draw_first(unsigned long long seed, long long frame0, int k1, int k2,
+                                                    double* K1s, double* K2s, int* attempts, double* min_ratio) {
+  __shared__ double K[CBP_MAX_K * CBP_MAX_K];
+  __shared__ double sum_slot;
+  const int f = blockIdx.x >> 1, s = 1 + (blockIdx.x & 1);
+  const int k = s == 1 ? k1 : k2;
+  draw_kernel(K, k, seed, (unsigned long long)(frame0 + f), s, 0, &sum_slot);
+  double* out = s == 1 ? K1s + (size_t)f * k1 * k1 : K2s + (size_t)f * k2 * k2;
+  for (int e = threadIdx.x; e < k * k; e += blockDim.x) out[e] = K[e];
+  if (s == 1 && threadIdx.x == 0) {
+    attempts[f] = 0;
+    if (min_ratio) min_ratio[f] = 1.0;
+  }
+}
+
+// One workgroup of two waves per (frame, pass, sample): the first reduces the
+// Gram to tridiagonal form, then each bisects one extreme eigenvalue.  The
+// frame's smallest ratio collects in min_ratio (non-negative doubles order as
+// their bits), a ratio at or below the limit marks attempts[f].  Bound by the
+// one-wave reduction's chain (its operation order is the ratio's last digits);
+// 102 us for 30 pairs of 15x15 / 17x17 kernels, whose 1020 systems took one
+// wave per frame 3.4 ms.
+__global__ __launch_bounds__(128) void k_draw_probe(int k1, int k2, int S, const double* K1s, const double* K2s,
+                                                    int* attempts, double* min_ratio) {
+  extern __shared__ __attribute__((aligned(16))) char sm_draw[];
+  const int f = blockIdx.x / (2 * S), t = blockIdx.x - f * 2 * S, pass = t / S, j = t - pass * S;
+  const int n = k1 + k2 - 2, tid = threadIdx.x;
+  draw_lds d = draw_carve(sm_draw, k1, k2);
+  for (int e = tid; e < k1 * k1; e += 128) d.K1[e] = K1s[(size_t)f * k1 * k1 + e];
+  for (int e = tid; e < k2 * k2; e += 128) d.K2[e] = K2s[(size_t)f * k2 * k2 + e];
+  __syncthreads();
+  sylvester_gram(d, k1, k2, S, pass, j);
+  if (tid < 64) small_tridiag(d.w, n);
+  __syncthreads();
+  double lo, hi, tn;
+  small_bisect(d.w, n, tid < 64 ? 1 : n, &lo, &hi, &tn);
+  if ((tid & 63) == 0) d.sum_slot[tid >> 6] = 0.5 * (lo + hi);
+  __syncthreads();
+  if (tid == 0) {
+    const double lmin = fmax(d.sum_slot[0], 0.0), lmax = d.sum_slot[1];
+    const double r = lmax > 0.0 ? lmin / lmax : 0.0;
+    if (r <= kSylvMin) atomicOr(&attempts[f], DRAW_FAILED);
+    if (min_ratio && r < 1.0) atomicMin((unsigned long long*)&min_ratio[f], (unsigned long long)__double_as_longlong(r));
+  }
+}
+
+// Attempts 1, 2, ... of the frames whose first pair failed, one wave each.
+__global__ __launch_bounds__(SMALL_NT) void k_draw_again(unsigned long long seed, long long frame0, int k1, int k2,
                                                           int S, double* K1s, double* K2s, int* attempts,
                                                           double* min_ratio) {
   extern __shared__ __attribute__((aligned(16))) char sm_draw[];
   const int f = blockIdx.x, l = threadIdx.x;
+  if (!(attempts[f] & DRAW_FAILED)) return;
   const unsigned long long frame = (unsigned long long)(frame0 + f);
-  double* K1 = (double*)sm_draw;
-  double* K2 = K1 + k1 * k1;
-  double* sum_slot = K2 + k2 * k2;
-  c64* p = (c64*)(((size_t)(sum_slot + 2) + 15) & ~(size_t)15);
-  c64* q = p + CBP_MAX_K;
-  c64* rho = q + CBP_MAX_K;                     // [rho_pp (k1), rho_qq (k2), rho_pq (k1 + k2 - 1)]
-  const int n1 = k2 - 1, n2 = k1 - 1, n = n1 + n2;
-  small_ws w = small_probe_carve((char*)(rho + 2 * CBP_MAX_N), n > 1 ? n : 1);
+  draw_lds d = draw_carve(sm_draw, k1, k2);
+  const int n = k1 + k2 - 2;
   int found = -1;
   double worst = 1.0;
-  for (int a = 0; a < kMaxAttempts && found < 0; ++a) {
-    draw_kernel(K1, k1, seed, frame, 1, a, sum_slot);
-    draw_kernel(K2, k2, seed, frame, 2, a, sum_slot);
+  for (int a = 1; a < kMaxAttempts && found < 0; ++a) {
+    draw_kernel(d.K1, k1, seed, frame, 1, a, d.sum_slot);
+    draw_kernel(d.K2, k2, seed, frame, 2, a, d.sum_slot);
     worst = 1.0;
-    for (int pass = 0; pass < 2 && n > 0; ++pass)
+    for (int pass = 0; pass < 2; ++pass)
       for (int j = 0; j < S; ++j) {
-        // slices: pass 0 evaluates along y (a polynomial in x), pass 1 along x
-        if (l < k1 + k2) {
-          const bool first = l < k1;
-          const int k = first ? k1 : k2, t = first ? l : l - k1;
-          const double* K = first ? K1 : K2;
-          c64 acc = {0.0, 0.0};
-          for (int r = 0; r < k; ++r) {
-            double sn, cs;
-            sincospi(-2.0 * (double)((j * r) % S) / (double)S, &sn, &cs);
-            const double kv = pass == 0 ? K[r * k + t] : K[t * k + r];
-            acc = acc + c64{kv * cs, kv * sn};
-          }
-          (first ? p : q)[t] = acc;
-        }
-        __syncthreads();
-        // correlations rho_pp(l) (l < k1), rho_qq(l) (l < k2), rho_pq(l), l in [-(n2 - 1), n1 - 1]
-        for (int t = l; t < k1 + k2 + n - 1; t += SMALL_NT) {
-          const c64* x;
-          const c64* y;
-          int lag, lx, ly;
-          if (t < k1) { x = p; y = p; lag = t; lx = k1; ly = k1; }
-          else if (t < k1 + k2) { x = q; y = q; lag = t - k1; lx = k2; ly = k2; }
-          else { x = p; y = q; lag = t - (k1 + k2) - (n2 - 1); lx = k1; ly = k2; }
-          c64 acc = {0.0, 0.0};
-          for (int s0 = max(0, -lag); s0 < lx && s0 + lag < ly; ++s0) acc = acc + cmulc(x[s0], y[s0 + lag]);
-          rho[t] = acc;
-        }
-        __syncthreads();
-        for (int e = l; e < n * n; e += SMALL_NT) {
-          const int r = e / n, c = e - r * n;
-          const bool ra = r < n1, ca = c < n1;
-          const int pr = ra ? r : r - n1, pc = ca ? c : c - n1;
-          c64 v;
-          if (ra == ca) {
-            // rho_pp has k1 lags, rho_qq k2; longer lags are zero
-            const int lag = pr - pc, al = lag < 0 ? -lag : lag;
-            v = al < (ra ? k1 : k2) ? rho[(ra ? 0 : k1) + al] : c64{0.0, 0.0};
-            if (lag < 0) v.im = -v.im;
-          } else {
-            const int cross = k1 + k2 + (n2 - 1);
-            v = ra ? rho[cross + pr - pc] : conj(rho[cross + pc - pr]);
-            v = c64{-v.re, -v.im};
-          }
-          w.A[e] = v;
-        }
-        __syncthreads();
-        const double r = small_extreme_ratio(w, n);
+        sylvester_gram(d, k1, k2, S, pass, j);
+        const double r = small_extreme_ratio(d.w, n);
         worst = fmin(worst, r);
         __syncthreads();
       }
     if (worst > kSylvMin) found = a;
   }
-  for (int e = l; e < k1 * k1; e += SMALL_NT) K1s[(size_t)f * k1 * k1 + e] = K1[e];
-  for (int e = l; e < k2 * k2; e += SMALL_NT) K2s[(size_t)f * k2 * k2 + e] = K2[e];
+  for (int e = l; e < k1 * k1; e += SMALL_NT) K1s[(size_t)f * k1 * k1 + e] = d.K1[e];
+  for (int e = l; e < k2 * k2; e += SMALL_NT) K2s[(size_t)f * k2 * k2 + e] = d.K2[e];
   if (l == 0) {
     attempts[f] = found;
     if (min_ratio) min_ratio[f] = worst;
@@ -264,16 +344,20 @@ __global__ void k_dequantize(const unsigned char* src, int64_t sp, int64_t scs, 
 hipError_t launch_draw_pairs(unsigned long long seed, long long frame0, int nframes, int k1, int k2, int S,
                              double* K1s, double* K2s, int* attempts, double* min_ratio, hipStream_t st) {
   const size_t lds = draw_lds_bytes(k1, k2);
-  hipLaunchKernelGGL(k_draw_pairs, dim3(nframes), dim3(SMALL_NT), lds, st, seed, frame0, k1, k2, S, K1s, K2s,
-                     attempts, min_ratio);
+  hipLaunchKernelGGL(k_draw_first, dim3(2 * (unsigned)nframes), dim3(256), 0, st, seed, frame0, k1, k2, K1s, K2s, attempts,
+                     min_ratio);
+  if (k1 + k2 > 2) {   // two 1 x 1 kernels have no Sylvester system
+    hipLaunchKernelGGL(k_draw_probe, dim3((unsigned)nframes * 2 * S), dim3(128), lds, st, k1, k2, S, K1s, K2s,
+                       attempts, min_ratio);
+    hipLaunchKernelGGL(k_draw_again, dim3(nframes), dim3(SMALL_NT), lds, st, seed, frame0, k1, k2, S, K1s, K2s,
+                       attempts, min_ratio);
+  }
   return hipGetLastError();
 }
 
-size_t draw_pairs_lds_bytes(int k1, int k2) { return draw_lds_bytes(k1, k2); }
-
 void set_encoder_attrs() {
-  hipFuncSetAttribute((const void*)k_draw_pairs, hipFuncAttributeMaxDynamicSharedMemorySize,
-                      (int)draw_lds_bytes(CBP_MAX_K, CBP_MAX_K));
+  for (const void* f : {(const void*)k_draw_probe, (const void*)k_draw_again})
+    hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)draw_lds_bytes(CBP_MAX_K, CBP_MAX_K));
 }
 
 template <typename T>
