@@ -13,10 +13,8 @@
 //   not safely coprime).  Nearly every pair passes at its first draw, so that
 //   draw's 2S solves run as one workgroup each; only the frames that failed one
 //   go on, one wave per frame.
-// k_blur: B_s = L (x) K_s, full linear convolution of every channel with
-//   both kernels, from LDS tiles of the latent (16 x 64 outputs per
-//   workgroup, four rows per thread; each input column of the tile read once
-//   per kernel column).
+// k_blur: B_s = L (x) K_s, full linear convolution of every channel with one
+//   of the kernels, register-tiled from LDS tiles of the latent.
 // k_quantize / k_dequantize: the 8-bit stream of a level without the b
 //   least significant bits, q = clamp(rint(255 B), 0, 255) & (255 << b), and
 //   the receiver's q / 255.
@@ -254,61 +252,137 @@ __global__ __launch_bounds__(SMALL_NT) void k_draw_again(unsigned long long seed
 }
 
 // ---------------------------------------------------------------- blur
-constexpr int kTY = 16, kTX = 64;
+// B_s[y][x] = sum_{a,b} L[y-a][x-b] K_s[a][b].  A workgroup of 256 threads
+// makes a 64 x 64 tile of one stream's channel from the latent's tile and
+// halo in LDS; a thread makes 4 rows x 4 adjacent columns.  For each kernel
+// row a it holds the row's K taps in registers (one broadcast read per four)
+// and, per output row, the K + 3 latent values its four columns need (16-byte
+// reads), so an LDS read serves 4 K FMAs / ((K + 3) / 4) -- about 14 of them --
+// and the kernel is bound by the vector FP32 FMAs (78 TFLOP/s without packed
+// instructions).  K is a template argument: the taps and the window are
+// registers.  1080p RGB, 15x15 and 17x17: 642 us (one tap at a time, 10
+// TFLOP/s) -> 105 us (61).
+constexpr int kTX = 64, kTY = 64, kBR = 4;
 
-// Items: (tile x, tile y, channel, stream).  B_s[y][x] = sum_{a,b} L[y-a][x-b] K_s[a][b].
 template <typename T>
-__global__ __launch_bounds__(256) void k_blur(const T* L, int64_t lp, int64_t lcs, int m, int n, int nch,
-                                              const double* K1, int k1, const double* K2, int k2, T* B1,
-                                              int64_t p1, int64_t cs1, T* B2, int64_t p2, int64_t cs2, int ntx,
-                                              int nty1, int ntx1, int nty2, int ntx2) {
-  __shared__ T Ks[CBP_MAX_K * CBP_MAX_K];
-  __shared__ T tile[(kTY + CBP_MAX_K - 1) * (kTX + CBP_MAX_K - 1)];
-  (void)ntx;
-  const int per1 = nty1 * ntx1 * nch;
-  int item = blockIdx.x;
-  const int stream = item >= per1;
-  if (stream) item -= per1;
-  const int ntxs = stream ? ntx2 : ntx1, ntys = stream ? nty2 : nty1;
-  const int tx0 = item % ntxs, rest = item / ntxs;
-  const int ty0 = rest % ntys, ch = rest / ntys;
-  const int k = stream ? k2 : k1;
-  const double* K = stream ? K2 : K1;
-  T* B = stream ? B2 : B1;
-  const int64_t bp = stream ? p2 : p1, bcs = stream ? cs2 : cs1;
-  const int H = m + k - 1, W = n + k - 1;
+struct blur_args {
+  const T* L;
+  int64_t lp, lcs;
+  int m, n, nch;
+  const double* K;
+  T* B;
+  int64_t bp, bcs;
+  int k, ntx, nty;
+};
+
+// Row stride of the LDS tile (elements): the width rounded up to 16 bytes.
+template <typename T, int K>
+constexpr int blur_ld() { return (kTX + K - 1 + 3) & ~3; }
+
+// LDS of a tile: the latent's rows and the taps (padded to whole reads).
+template <typename T, int K>
+constexpr int blur_lds() { return ((kTY + K - 1) * blur_ld<T, K>() + K * ((K + 3) & ~3)) * (int)sizeof(T); }
+
+template <typename T, int K>
+__device__ inline void blur_tile(const blur_args<T>& g, int item, char* sm) {
+  constexpr int LD = blur_ld<T, K>(), TH = kTY + K - 1, TW = kTX + K - 1, KP = (K + 3) & ~3;
+  constexpr int V = 16 / (int)sizeof(T);                  // elements per 16-byte read
+  constexpr int NV = (K + 3 + V - 1) / V;                 // reads of a window of K + 3
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  T* tile = (T*)sm;
+  T* Ks = tile + TH * LD;
+  const int tid = threadIdx.x;
+  const int tx0 = item % g.ntx, rest = item / g.ntx;
+  const int ty0 = rest % g.nty, ch = rest / g.nty;
   const int y0 = ty0 * kTY, x0 = tx0 * kTX;
-  const int tw = kTX + k - 1, th = kTY + k - 1;
-  for (int e = threadIdx.x; e < k * k; e += 256) Ks[e] = (T)K[e];
-  const T* Lc = L + (int64_t)ch * lcs;
-  for (int e = threadIdx.x; e < th * tw; e += 256) {
-    const int i = e / tw, jj = e - i * tw;
-    const int y = y0 - (k - 1) + i, x = x0 - (k - 1) + jj;
-    tile[e] = (y >= 0 && y < m && x >= 0 && x < n) ? Lc[(int64_t)y * lp + x] : T(0);
+  // taps of kernel row a in the order of the window: Ks[a][t] = K[a][K - 1 - t]
+  for (int e = tid; e < K * KP; e += 256) {
+    const int a = e / KP, t = e - a * KP;
+    Ks[e] = t < K ? (T)g.K[a * K + K - 1 - t] : T(0);
   }
-  __syncthreads();
-  const int tx = threadIdx.x & 63, tyg = threadIdx.x >> 6;   // 64 columns x 4 row groups of 4 rows
-  T acc[4] = {T(0), T(0), T(0), T(0)};
-  for (int b = 0; b < k; ++b) {
-    // the tile column this thread's outputs read for kernel column b: rows
-    // 4 tyg + i, i < k + 3; output row r takes row i with kernel row
-    // a = r + k - 1 - i (each tile value read once per kernel column)
-    const T* col = tile + (4 * tyg) * tw + (tx - b + k - 1);
-    for (int i = 0; i < k + 3; ++i) {
-      const T v = col[i * tw];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int a = r + k - 1 - i;
-        if (a >= 0 && a < k) acc[r] += v * Ks[a * k + b];
-      }
+  const T* Lc = g.L + (int64_t)ch * g.lcs;
+  // the tile, four rows at a time (a wave per row), zero outside the latent
+  {
+    const int c = tid & 63, x = x0 - (K - 1) + c;
+    const bool in0 = x >= 0 && x < g.n, in1 = c + 64 < TW && x + 64 < g.n;   // x + 64 >= 0
+#pragma unroll 4
+    for (int i = tid >> 6; i < TH; i += 4) {
+      const int y = y0 - (K - 1) + i;
+      const bool iny = y >= 0 && y < g.m;
+      const T* row = Lc + (int64_t)y * g.lp + x;
+      const T v0 = iny && in0 ? row[0] : T(0), v1 = iny && in1 ? row[64] : T(0);
+      tile[i * LD + c] = v0;
+      if (c + 64 < LD) tile[i * LD + c + 64] = v1;
     }
   }
-  T* Bc = B + (int64_t)ch * bcs;
+  __syncthreads();
+  const int tx = (tid & 15) * 4, ty = (tid >> 4) * kBR;
+  T acc[kBR][4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int y = y0 + 4 * tyg + r, x = x0 + tx;
-    if (y < H && x < W) Bc[(int64_t)y * bp + x] = acc[r];
+  for (int r = 0; r < kBR; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] = T(0);
+#pragma unroll 1
+  for (int a = 0; a < K; ++a) {
+    T k[KP];
+#pragma unroll
+    for (int v = 0; v < KP / V; ++v) {
+      const vec q = *(const vec*)(Ks + a * KP + v * V);
+#pragma unroll
+      for (int u = 0; u < V; ++u) k[v * V + u] = q[u];
+    }
+#pragma unroll
+    for (int r = 0; r < kBR; ++r) {
+      const T* row = tile + (ty + r + K - 1 - a) * LD + tx;
+      T w[NV * V];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const vec q = *(const vec*)(row + v * V);
+#pragma unroll
+        for (int u = 0; u < V; ++u) w[v * V + u] = q[u];
+      }
+#pragma unroll
+      for (int t = 0; t < K; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] += k[t] * w[c + t];
+    }
   }
+  const int H = g.m + K - 1, W = g.n + K - 1;
+  T* Bc = g.B + (int64_t)ch * g.bcs;
+#pragma unroll
+  for (int r = 0; r < kBR; ++r) {
+    const int y = y0 + ty + r;
+    if (y < H)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (x0 + tx + c < W) Bc[(int64_t)y * g.bp + x0 + tx + c] = acc[r][c];
+  }
+}
+
+template <typename T, int K>
+__global__ __launch_bounds__(256) void k_blur(blur_args<T> g) {
+  __shared__ __attribute__((aligned(16))) char sm[blur_lds<T, K>()];
+  blur_tile<T, K>(g, (int)blockIdx.x, sm);
+}
+
+// Both streams in one launch, for kernels of at most kBlurPair: their tiles
+// are short, and on small frames the second launch costs more than the
+// tiles (64x64, 3x3 / 5x5: 14.1 us in two launches, 11.7 in one), while the
+// registers of the largest instance still leave three waves per SIMD.
+constexpr int kBlurPair = 8;
+
+template <typename T, int K>
+__device__ inline __attribute__((always_inline)) void blur_any(const blur_args<T>& g, int item, char* sm) {
+  if (g.k == K) blur_tile<T, K>(g, item, sm);
+  else if constexpr (K > 1) blur_any<T, K - 1>(g, item, sm);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_blur_pair(blur_args<T> g1, blur_args<T> g2) {
+  __shared__ __attribute__((aligned(16))) char sm[blur_lds<T, kBlurPair>()];
+  const int n1 = g1.ntx * g1.nty * g1.nch, b = (int)blockIdx.x;
+  if (b < n1) blur_any<T, kBlurPair>(g1, b, sm);
+  else blur_any<T, kBlurPair>(g2, b - n1, sm);
 }
 
 // ---------------------------------------------------------------- 8-bit streams
@@ -360,15 +434,32 @@ void set_encoder_attrs() {
     hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)draw_lds_bytes(CBP_MAX_K, CBP_MAX_K));
 }
 
+namespace {
+
+template <typename T, int K>
+void blur_stream(int k, const blur_args<T>& g, hipStream_t st) {
+  if (k == K) hipLaunchKernelGGL((k_blur<T, K>), dim3(g.ntx * g.nty * g.nch), dim3(256), 0, st, g);
+  else if constexpr (K > 1) blur_stream<T, K - 1>(k, g, st);
+}
+
+}  // namespace
+
 template <typename T>
 hipError_t launch_blur(const T* L, int64_t lp, int64_t lcs, int m, int n, int nch, const double* K1, int k1,
                        const double* K2, int k2, T* B1, int64_t p1, int64_t cs1, T* B2, int64_t p2, int64_t cs2,
                        hipStream_t st) {
-  const int nty1 = (m + k1 - 1 + kTY - 1) / kTY, ntx1 = (n + k1 - 1 + kTX - 1) / kTX;
-  const int nty2 = (m + k2 - 1 + kTY - 1) / kTY, ntx2 = (n + k2 - 1 + kTX - 1) / kTX;
-  const int grid = (nty1 * ntx1 + nty2 * ntx2) * nch;
-  hipLaunchKernelGGL(k_blur<T>, dim3(grid), dim3(256), 0, st, L, lp, lcs, m, n, nch, K1, k1, K2, k2, B1, p1, cs1,
-                     B2, p2, cs2, 0, nty1, ntx1, nty2, ntx2);
+  blur_args<T> g[2];
+  for (int s = 0; s < 2; ++s) {
+    const int k = s ? k2 : k1;
+    g[s] = {L, lp, lcs, m, n, nch, s ? K2 : K1, s ? B2 : B1, s ? p2 : p1, s ? cs2 : cs1, k,
+            (n + k - 1 + kTX - 1) / kTX, (m + k - 1 + kTY - 1) / kTY};
+  }
+  if (std::max(k1, k2) <= kBlurPair) {
+    const int grid = (g[0].ntx * g[0].nty + g[1].ntx * g[1].nty) * nch;
+    hipLaunchKernelGGL(k_blur_pair<T>, dim3(grid), dim3(256), 0, st, g[0], g[1]);
+  } else {
+    for (int s = 0; s < 2; ++s) blur_stream<T, CBP_MAX_K>(g[s].k, g[s], st);
+  }
   return hipGetLastError();
 }
 
