@@ -20,6 +20,8 @@
 //   the receiver's q / 255.
 #include <algorithm>
 
+#include <type_traits>
+
 #include "eigsmall.h"
 #include "internal.h"
 
@@ -386,30 +388,96 @@ __global__ __launch_bounds__(256) void k_blur_pair(blur_args<T> g1, blur_args<T>
 }
 
 // ---------------------------------------------------------------- 8-bit streams
+// Both are copies with a conversion, bound by HBM.  Dense images (no gap
+// between rows and channels, 16-byte aligned bases) are one run of elements:
+// a workgroup converts 4096 of them, a thread in groups of 16 bytes of pixels
+// with neighbouring lanes on neighbouring groups, without an index division.  1080p RGB FP32: quantise 18.5 us and dequantise 19.7
+// (one element per thread and step, two 64-bit divisions each) -> 7.8 and 7.8 (4 TB/s).
+// Other images go row by row, four elements of a row per thread.
 template <typename T>
-__global__ void k_quantize(const T* src, int64_t sp, int64_t scs, unsigned char* dst, int64_t dp, int64_t dcs,
-                           int H, int W, int nch, int drop) {
-  const int64_t total = (int64_t)H * W * nch;
-  const unsigned int mask = (0xFFu << drop) & 0xFFu;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(e % W);
-    const int64_t r = e / W;
-    const int y = (int)(r % H), c = (int)(r / H);
-    const T v = rint(src[(int64_t)c * scs + (int64_t)y * sp + x] * T(255));
-    const T cl = v < T(0) ? T(0) : (v > T(255) ? T(255) : v);
-    dst[(int64_t)c * dcs + (int64_t)y * dp + x] = (unsigned char)((unsigned int)cl & mask);
+__device__ inline unsigned int quantize_one(T x, unsigned int mask) {
+  const T v = rint(x * T(255));
+  const T cl = v < T(0) ? T(0) : (v > T(255) ? T(255) : v);
+  return (unsigned int)cl & mask;
+}
+
+// A group of V = 16 / sizeof(T) elements as bytes.
+template <typename T>
+using level_bytes = typename std::conditional<sizeof(T) == 4, unsigned int, unsigned short>::type;
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_quantize_dense(const T* src, unsigned char* dst, int64_t total,
+                                                        unsigned int mask) {
+  constexpr int V = 16 / (int)sizeof(T), NI = 16 / V;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  const int64_t e0 = (int64_t)blockIdx.x * 4096 + threadIdx.x * V;   // group i: e0 + 256 V i
+  if ((int64_t)blockIdx.x * 4096 + 4096 <= total) {
+    vec v[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) v[i] = *(const vec*)(src + e0 + i * 256 * V);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      unsigned int w = 0;
+#pragma unroll
+      for (int j = 0; j < V; ++j) w |= quantize_one<T>(v[i][j], mask) << (8 * j);
+      *(level_bytes<T>*)(dst + e0 + i * 256 * V) = (level_bytes<T>)w;
+    }
+  } else {
+    for (int64_t e = (int64_t)blockIdx.x * 4096 + threadIdx.x; e < total; e += 256)
+      dst[e] = (unsigned char)quantize_one<T>(src[e], mask);
   }
 }
 
 template <typename T>
-__global__ void k_dequantize(const unsigned char* src, int64_t sp, int64_t scs, T* dst, int64_t dp, int64_t dcs,
-                             int H, int W, int nch) {
-  const int64_t total = (int64_t)H * W * nch;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(e % W);
-    const int64_t r = e / W;
-    const int y = (int)(r % H), c = (int)(r / H);
-    dst[(int64_t)c * dcs + (int64_t)y * dp + x] = (T)src[(int64_t)c * scs + (int64_t)y * sp + x] / T(255);
+__global__ __launch_bounds__(256) void k_dequantize_dense(const unsigned char* src, T* dst, int64_t total) {
+  constexpr int V = 16 / (int)sizeof(T), NI = 16 / V;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  const int64_t e0 = (int64_t)blockIdx.x * 4096 + threadIdx.x * V;
+  if ((int64_t)blockIdx.x * 4096 + 4096 <= total) {
+    level_bytes<T> w[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) w[i] = *(const level_bytes<T>*)(src + e0 + i * 256 * V);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      vec v;
+#pragma unroll
+      for (int j = 0; j < V; ++j) v[j] = (T)(((unsigned int)w[i] >> (8 * j)) & 0xFFu) / T(255);
+      *(vec*)(dst + e0 + i * 256 * V) = v;
+    }
+  } else {
+    for (int64_t e = (int64_t)blockIdx.x * 4096 + threadIdx.x; e < total; e += 256) dst[e] = (T)src[e] / T(255);
+  }
+}
+
+// Rows of a pitched image: blockIdx.y + gridDim.y i counts rows over the
+// channels, blockIdx.x covers 1024 elements of a row.
+template <typename T>
+__global__ __launch_bounds__(256) void k_quantize(const T* src, int64_t sp, int64_t scs, unsigned char* dst, int64_t dp,
+                                                  int64_t dcs, int H, int W, int nch, unsigned int mask) {
+  for (int64_t row = blockIdx.y; row < (int64_t)H * nch; row += gridDim.y) {
+    const int c = (int)(row / H), y = (int)(row - (int64_t)c * H);
+    const T* s = src + (int64_t)c * scs + (int64_t)y * sp;
+    unsigned char* d = dst + (int64_t)c * dcs + (int64_t)y * dp;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int x = (int)blockIdx.x * 1024 + i * 256 + (int)threadIdx.x;
+      if (x < W) d[x] = (unsigned char)quantize_one<T>(s[x], mask);
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_dequantize(const unsigned char* src, int64_t sp, int64_t scs, T* dst,
+                                                    int64_t dp, int64_t dcs, int H, int W, int nch) {
+  for (int64_t row = blockIdx.y; row < (int64_t)H * nch; row += gridDim.y) {
+    const int c = (int)(row / H), y = (int)(row - (int64_t)c * H);
+    const unsigned char* s = src + (int64_t)c * scs + (int64_t)y * sp;
+    T* d = dst + (int64_t)c * dcs + (int64_t)y * dp;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int x = (int)blockIdx.x * 1024 + i * 256 + (int)threadIdx.x;
+      if (x < W) d[x] = (T)s[x] / T(255);
+    }
   }
 }
 
@@ -463,12 +531,30 @@ hipError_t launch_blur(const T* L, int64_t lp, int64_t lcs, int m, int n, int nc
   return hipGetLastError();
 }
 
+namespace {
+
+// No gap between rows and channels (a one-channel image's stride is unused).
+bool dense(int64_t pitch, int64_t cs, int H, int W, int nch) {
+  return pitch == W && (nch == 1 || cs == (int64_t)H * W);
+}
+bool aligned16(const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; }
+dim3 row_grid(int H, int W, int nch) {
+  return dim3((W + 1023) / 1024, (unsigned)std::min<int64_t>((int64_t)H * nch, 65535));
+}
+
+}  // namespace
+
 template <typename T>
 hipError_t launch_quantize(const T* src, int64_t sp, int64_t scs, unsigned char* dst, int64_t dp, int64_t dcs, int H,
                            int W, int nch, int drop, hipStream_t st) {
   const int64_t total = (int64_t)H * W * nch;
-  const int grid = (int)std::min<int64_t>((total + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_quantize<T>, dim3(grid), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch, drop);
+  const unsigned int mask = (0xFFu << drop) & 0xFFu;
+  if (dense(sp, scs, H, W, nch) && dense(dp, dcs, H, W, nch) && aligned16(src, dst) && total < (int64_t)1 << 40)
+    hipLaunchKernelGGL(k_quantize_dense<T>, dim3((unsigned)((total + 4095) / 4096)), dim3(256), 0, st, src, dst, total,
+                       mask);
+  else
+    hipLaunchKernelGGL(k_quantize<T>, row_grid(H, W, nch), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch,
+                       mask);
   return hipGetLastError();
 }
 
@@ -476,8 +562,11 @@ template <typename T>
 hipError_t launch_dequantize(const unsigned char* src, int64_t sp, int64_t scs, T* dst, int64_t dp, int64_t dcs,
                              int H, int W, int nch, hipStream_t st) {
   const int64_t total = (int64_t)H * W * nch;
-  const int grid = (int)std::min<int64_t>((total + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_dequantize<T>, dim3(grid), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch);
+  if (dense(sp, scs, H, W, nch) && dense(dp, dcs, H, W, nch) && aligned16(src, dst) && total < (int64_t)1 << 40)
+    hipLaunchKernelGGL(k_dequantize_dense<T>, dim3((unsigned)((total + 4095) / 4096)), dim3(256), 0, st, src, dst,
+                       total);
+  else
+    hipLaunchKernelGGL(k_dequantize<T>, row_grid(H, W, nch), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch);
   return hipGetLastError();
 }
 
