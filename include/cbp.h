@@ -411,8 +411,8 @@ cbp_status cbp_last_tuning(cbp_tuning* out);
  * Parameters (FP32, device, packed): W1 [128][32], b1 [128], W2 [128][128],
  * b2 [128], W3 [2][128], b3 [2] -- cbp_mlp_param_count() floats.
  * Training state (device, cbp_mlp_state_size(max_rows) bytes, caller-owned):
- * master weights, Adam moments, bf16 copies and the activations of up to
- * max_rows rows.  Features X: device FP32 [n][32]; targets T: device FP32
+ * master weights, Adam moments, bf16 copies and the partial gradients of
+ * steps over up to max_rows rows.  Features X: device FP32 [n][32]; targets T: device FP32
  * [n][2] = (log w*, log tau*); loss: device FP32, the mean over rows of
  * (log softplus(o1) - log w*)^2 + (o2 - log tau*)^2.  All calls are
  * asynchronous on `stream`. */

@@ -409,8 +409,8 @@ class PreparedBatch:
 
 class MlpState:
     """Training state of the learned form's network (device memory owned
-    here): FP32 master weights, Adam moments, bf16 copies and the activations
-    of up to max_rows rows.  Every step runs in the library's kernels."""
+    here): FP32 master weights, Adam moments, bf16 copies and the partial
+    gradients of steps over up to max_rows rows.  Every step runs in the library's kernels."""
 
     def __init__(self, max_rows: int, device="cuda"):
         torch = _torch()

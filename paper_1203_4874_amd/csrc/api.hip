@@ -1280,10 +1280,8 @@ cbp_status cbp_mlp_train_step(void* state, int32_t max_rows, const float* X, con
                               int32_t step, float* loss, void* stream) {
   if (!state || !X || !T || !loss || n < 1 || n > max_rows || step < 1 || !(lr > 0.0f)) return CBP_E_INVALID;
   (void)hipGetLastError();
-  hipStream_t st = (hipStream_t)stream;
-  if (note("mlp_gradients", mlp_gradients(state, max_rows, X, T, n, loss, nullptr, st)) != hipSuccess)
-    return CBP_E_DEVICE;
-  return note("mlp_adam_step", mlp_adam_step(state, max_rows, lr, step, st)) == hipSuccess ? CBP_OK : CBP_E_DEVICE;
+  return note("mlp_train_step", mlp_train_step(state, max_rows, X, T, n, lr, step, loss, (hipStream_t)stream)) ==
+                 hipSuccess ? CBP_OK : CBP_E_DEVICE;
 }
 
 cbp_status cbp_mlp_export(const void* state, int32_t max_rows, void* blob, void* stream) {

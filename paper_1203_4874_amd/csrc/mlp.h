@@ -41,7 +41,8 @@ hipError_t mlp_save_state(const void* state, int rows, float* out, hipStream_t s
 hipError_t mlp_load_state(void* state, int rows, const float* in, hipStream_t st);
 hipError_t mlp_gradients(void* state, int rows, const float* X, const float* T, int n, float* loss,
                          float* grads, hipStream_t st);
-hipError_t mlp_adam_step(void* state, int rows, float lr, int step, hipStream_t st);
+hipError_t mlp_train_step(void* state, int rows, const float* X, const float* T, int n, float lr, int step,
+                          float* loss, hipStream_t st);
 hipError_t mlp_export(const void* state, int rows, void* blob, hipStream_t st);
 hipError_t mlp_forward_blob(const void* blob, const float* X, int n, float* out, hipStream_t st);
 

@@ -16,6 +16,8 @@
 // (k contiguous in LDS).  Lane l supplies row l % 32 of A (and of B) at
 // k = k0 + 8 (l / 32) .. + 7; accumulator v of lane l is
 // D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
+#include <algorithm>
+
 #include "mlp.h"
 
 #include "internal.h"
@@ -60,9 +62,7 @@ constexpr int LDH = MLP_HIDDEN + 8;
 
 // ------------------------------------------------------------------ forward
 // One workgroup (4 waves) per block of 64 rows.  Layer 1 and 2 on the matrix
-// cores; the 2-output head on the vector units in FP32.  With train != 0 the
-// activations are kept for the backward pass: H1, H2 (bf16, [n][128]) and the
-// pre-activation signs.
+// cores; the 2-output head on the vector units in FP32.
 struct fwd_args {
   const float* X;
   int n;
@@ -73,8 +73,6 @@ struct fwd_args {
   const float* b2;
   const float* b3;
   float* out;                // [n][2]
-  unsigned short* H1;        // [n][128] (train)
-  unsigned short* H2;        // [n][128] (train)
 };
 
 // LDS of one 64-row block.
@@ -87,18 +85,27 @@ struct fwd_lds {
   float out[RB][MLP_OUT];
 };
 
-// Forward of rows [0, nrows) of X (nrows <= 64) into L.out; with H1 / H2 not
-// NULL the bf16 activations are stored there (row-major, 128 per row).
+// A bf16 matrix [rows][cols] (cols a multiple of 8, 16-byte aligned) into LDS
+// rows of stride ld, eight entries per access, by 256 threads.
+__device__ inline void stage_bf16(unsigned short* dst, int ld, const unsigned short* src, int rows, int cols) {
+  const int per = cols >> 3;
+  for (int e = threadIdx.x; e < rows * per; e += 256) {
+    const int r = e / per, c = (e - r * per) * 8;
+    *(v4u*)(dst + r * ld + c) = *(const v4u*)(src + (size_t)r * cols + c);
+  }
+}
+
+// Forward of rows [0, nrows) of X (nrows <= 64) into L.out.
 __device__ inline void mlp_block(fwd_lds& L, const float* X, int nrows, const unsigned short* W1,
                                  const unsigned short* W2, const float* W3, const float* b1, const float* b2,
-                                 const float* b3, unsigned short* H1, unsigned short* H2) {
+                                 const float* b3) {
   const int tid = threadIdx.x, w = tid >> 6;
   for (int e = tid; e < RB * MLP_FEAT; e += 256) {
     const int r = e / MLP_FEAT, f = e % MLP_FEAT;
     L.xs[r * LD1 + f] = r < nrows ? to_bf16(X[(size_t)r * MLP_FEAT + f]) : (unsigned short)0;
   }
-  for (int e = tid; e < MLP_HIDDEN * MLP_FEAT; e += 256) L.w1s[(e / MLP_FEAT) * LD1 + e % MLP_FEAT] = W1[e];
-  for (int e = tid; e < MLP_HIDDEN * MLP_HIDDEN; e += 256) L.w2s[(e / MLP_HIDDEN) * LDH + e % MLP_HIDDEN] = W2[e];
+  stage_bf16(L.w1s, LD1, W1, MLP_HIDDEN, MLP_FEAT);
+  stage_bf16(L.w2s, LDH, W2, MLP_HIDDEN, MLP_HIDDEN);
   __syncthreads();
   // layer 1: 64 x 128 = 2 x 4 tiles of 32 x 32 over the 4 waves
   for (int t = w; t < 8; t += 4) {
@@ -112,11 +119,6 @@ __device__ inline void mlp_block(fwd_lds& L, const float* X, int nrows, const un
     }
   }
   __syncthreads();
-  if (H1)
-    for (int e = tid; e < RB * MLP_HIDDEN; e += 256) {
-      const int r = e / MLP_HIDDEN, h = e % MLP_HIDDEN;
-      if (r < nrows) H1[(size_t)r * MLP_HIDDEN + h] = L.hs[r * LDH + h];
-    }
   // layer 2
   for (int t = w; t < 8; t += 4) {
     const int ti = t >> 2, tj = t & 3;
@@ -129,11 +131,6 @@ __device__ inline void mlp_block(fwd_lds& L, const float* X, int nrows, const un
     }
   }
   __syncthreads();
-  if (H2)
-    for (int e = tid; e < RB * MLP_HIDDEN; e += 256) {
-      const int r = e / MLP_HIDDEN, h = e % MLP_HIDDEN;
-      if (r < nrows) H2[(size_t)r * MLP_HIDDEN + h] = to_bf16(L.h2f[r][h]);
-    }
   // head: 2 outputs per row, 128-term FP32 dot products on the vector units
   if (tid < MLP_OUT * RB) {
     const int r = tid >> 1, o = tid & 1;
@@ -148,8 +145,7 @@ __global__ __launch_bounds__(256) void k_mlp_forward(fwd_args a) {
   __shared__ __attribute__((aligned(16))) fwd_lds L;
   const int r0 = blockIdx.x * RB;
   const int nrows = min(RB, a.n - r0);
-  mlp_block(L, a.X + (size_t)r0 * MLP_FEAT, nrows, a.W1, a.W2, a.W3, a.b1, a.b2, a.b3,
-            a.H1 ? a.H1 + (size_t)r0 * MLP_HIDDEN : nullptr, a.H2 ? a.H2 + (size_t)r0 * MLP_HIDDEN : nullptr);
+  mlp_block(L, a.X + (size_t)r0 * MLP_FEAT, nrows, a.W1, a.W2, a.W3, a.b1, a.b2, a.b3);
   if (threadIdx.x < MLP_OUT * RB) {
     const int r = threadIdx.x >> 1, o = threadIdx.x & 1;
     if (r < nrows) a.out[(size_t)(r0 + r) * MLP_OUT + o] = L.out[r][o];
@@ -179,7 +175,7 @@ __global__ __launch_bounds__(256) void k_mlp_frames(batch_ref br, const mlp_blob
       }
       return;
     }
-    mlp_block(L, d.feat, n, blob->W1, blob->W2, blob->W3, blob->b1, blob->b2, blob->b3, nullptr, nullptr);
+    mlp_block(L, d.feat, n, blob->W1, blob->W2, blob->W3, blob->b1, blob->b2, blob->b3);
     if (t < n) {
       const double o1 = L.out[t][0], o2 = L.out[t][1];
       const double sp = o1 > 30.0 ? o1 : log1p(exp(o1));
@@ -199,165 +195,310 @@ __global__ __launch_bounds__(256) void k_mlp_frames(batch_ref br, const mlp_blob
   });
 }
 
-// ------------------------------------------------------------------ loss and head backward
-// Per row: o = (o1, o2), loss_r = (log softplus(o1) - t1)^2 + (o2 - t2)^2,
-// dO = d(mean loss)/dO; dH2 = dO W3, dZ2 = dH2 * [H2 > 0] (bf16, [n][128]).
-// Per-block partial sums of the loss, dW3 and db3 (fixed order).
-__global__ __launch_bounds__(256) void k_mlp_loss(const float* out, const float* T, int n, const float* W3,
-                                                  const unsigned short* H2, unsigned short* dZ2, float* part) {
-  __shared__ float dos[RB][2];
-  __shared__ float red[256];
-  const int tid = threadIdx.x, r0 = blockIdx.x * RB;
-  float lsum = 0.0f;
-  if (tid < RB) {
-    const int r = r0 + tid;
-    float d1 = 0.0f, d2 = 0.0f;
-    if (r < n) {
-      const float o1 = out[(size_t)r * 2], o2 = out[(size_t)r * 2 + 1];
-      const float sp = o1 > 20.0f ? o1 : log1pf(expf(o1));
-      const float sg = 1.0f / (1.0f + expf(-o1));
-      const float r1 = logf(sp) - T[(size_t)r * 2], r2 = o2 - T[(size_t)r * 2 + 1];
-      lsum = r1 * r1 + r2 * r2;
-      d1 = 2.0f * r1 / (float)n * sg / sp;
-      d2 = 2.0f * r2 / (float)n;
-    }
-    dos[tid][0] = d1;
-    dos[tid][1] = d2;
-  }
-  __syncthreads();
-  for (int e = tid; e < RB * MLP_HIDDEN; e += 256) {
-    const int rr = e / MLP_HIDDEN, h = e % MLP_HIDDEN, r = r0 + rr;
-    if (r < n) {
-      const unsigned short hb = H2[(size_t)r * MLP_HIDDEN + h];
-      const float g = dos[rr][0] * W3[h] + dos[rr][1] * W3[MLP_HIDDEN + h];
-      dZ2[(size_t)r * MLP_HIDDEN + h] = from_bf16(hb) > 0.0f ? to_bf16(g) : (unsigned short)0;
-    }
-  }
-  // partials: [0] loss, [1 .. 256] dW3, [257, 258] db3
-  float* p = part + (size_t)blockIdx.x * (2 + 2 * MLP_HIDDEN + 1);
-  red[tid] = tid < RB ? lsum : 0.0f;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) p[0] = red[0];
-  // dW3[o][h] = sum_r dO[r][o] H2[r][h]
-  {
-    const int o = tid >> 7, h = tid & 127;
-    float s = 0.0f;
-    for (int rr = 0; rr < RB; ++rr)
-      if (r0 + rr < n) s = fmaf(dos[rr][o], from_bf16(H2[(size_t)(r0 + rr) * MLP_HIDDEN + h]), s);
-    p[1 + o * MLP_HIDDEN + h] = s;
-  }
-  if (tid < 2) {
-    float s = 0.0f;
-    for (int rr = 0; rr < RB; ++rr) s += dos[rr][tid];
-    p[1 + 2 * MLP_HIDDEN + tid] = s;
-  }
-}
+// ------------------------------------------------------------------ training step
+// k_mlp_step: forward, loss, backward and the weight gradients of blocks of 64
+// rows, everything between the features and the gradient partials in LDS and
+// registers (activations and deltas used to make three trips through memory
+// between four launches).  Per row: o = (o1, o2), loss_r = (log softplus(o1) -
+// t1)^2 + (o2 - t2)^2, dO = d(mean loss)/dO; dZ2 = (dO W3) * [H2 > 0], dZ1 =
+// (dZ2 W2) * [H1 > 0] in bf16 (as the forward's activations); dW2 = dZ2^T H1
+// and dW1 = dZ1^T X on the matrix cores from transposed copies (r contiguous)
+// that the epilogues write beside the row-major ones (four consecutive rows of
+// an accumulator are one 8-byte store).  A workgroup takes the row blocks b, b
+// + G, ... and writes its sums once: part[b][MLP_PART], in parameter order,
+// then the loss.  Latency-bound at one block per workgroup (8192 rows: 128
+// workgroups, about ten barriers).
+// k_mlp_update: the partials summed over workgroups in order into the
+// gradient (and the loss), then, in a training step, Adam on the FP32 master
+// weights and the bf16 copies (W1, W2, W2^T).
+// 8192 rows: 17 launches, 323 us -> two, 21.5 + 4.1 us.
+constexpr int MLP_PART = (MLP_NPARAM + 1 + 63) & ~63;
+constexpr int MLP_STEP_WG = 256;            // workgroups at most
+constexpr int LDT = RB + 8;                 // stride of the transposed copies
 
-// ------------------------------------------------------------------ row-blocked backward
-// dZ1 = (dZ2 W2) * [H1 > 0] for a block of 64 rows (bf16), using W2^T.
-__global__ __launch_bounds__(256) void k_mlp_back_h1(const unsigned short* dZ2, const unsigned short* W2t,
-                                                     const unsigned short* H1, int n, unsigned short* dZ1) {
-  __shared__ __attribute__((aligned(16))) unsigned short ds_[RB * LDH];
-  __shared__ __attribute__((aligned(16))) unsigned short wt[MLP_HIDDEN * LDH];
-  const int tid = threadIdx.x, w = tid >> 6, r0 = blockIdx.x * RB;
-  for (int e = tid; e < RB * MLP_HIDDEN; e += 256) {
-    const int r = e / MLP_HIDDEN, h = e % MLP_HIDDEN;
-    ds_[r * LDH + h] = r0 + r < n ? dZ2[(size_t)(r0 + r) * MLP_HIDDEN + h] : (unsigned short)0;
-  }
-  for (int e = tid; e < MLP_HIDDEN * MLP_HIDDEN; e += 256) wt[(e / MLP_HIDDEN) * LDH + e % MLP_HIDDEN] = W2t[e];
-  __syncthreads();
-  for (int t = w; t < 8; t += 4) {
-    const int ti = t >> 2, tj = t & 3;
-    v16f acc = {};
-    tile_abt(ds_ + ti * 32 * LDH, LDH, wt + tj * 32 * LDH, LDH, MLP_HIDDEN, acc);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = r0 + ti * 32 + tile_row(v), h = tj * 32 + tile_col();
-      if (r < n) {
-        const bool on = from_bf16(H1[(size_t)r * MLP_HIDDEN + h]) > 0.0f;
-        dZ1[(size_t)r * MLP_HIDDEN + h] = on ? to_bf16(acc[v]) : (unsigned short)0;
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------------ weight gradients
-// G[M][N] partial over a chunk of rows: G[i][j] = sum_r A[r][i] B[r][j], with
-// A [n][M] and B [n][N] row-major over r, each either bf16 (Ab / Bb) or FP32
-// rounded to bf16 on load (Af / Bf).  One wave per (32 x 32 tile of G, chunk
-// of 256 rows); the chunk is transposed into LDS so the matrix-core operands
-// have r contiguous.  Partials [chunk][M][N] FP32.
-struct wgrad_args {
-  const unsigned short* Ab;
-  const float* Af;
-  int M;
-  const unsigned short* Bb;
-  const float* Bf;
-  int N;
+struct step_args {
+  const float* X;
+  const float* T;
   int n;
-  float* part;
+  const unsigned short* W1;   // bf16 [128][32]
+  const unsigned short* W2;   // bf16 [128][128]
+  const unsigned short* W2t;  // its transpose
+  const float* p;             // FP32 parameters (biases, head)
+  float* part;                // [gridDim.x][MLP_PART]
 };
 
-__global__ __launch_bounds__(64) void k_mlp_wgrad(wgrad_args g) {
-  constexpr int CH = 256;
-  __shared__ __attribute__((aligned(16))) unsigned short at[32 * (CH + 8)];
-  __shared__ __attribute__((aligned(16))) unsigned short bt[32 * (CH + 8)];
-  const int tilesN = g.N / 32;
-  const int ti = blockIdx.x / tilesN, tj = blockIdx.x % tilesN;
-  const int c = blockIdx.y, rbase = c * CH;
-  const int l = threadIdx.x;
-  for (int e = l; e < 32 * CH; e += 64) {
-    const int rr = e / 32, i = e % 32, r = rbase + rr;
-    unsigned short va = 0, vb = 0;
-    if (r < g.n) {
-      const size_t ia = (size_t)r * g.M + ti * 32 + i, ib = (size_t)r * g.N + tj * 32 + i;
-      va = g.Ab ? g.Ab[ia] : to_bf16(g.Af[ia]);
-      vb = g.Bb ? g.Bb[ib] : to_bf16(g.Bf[ib]);
+struct step_lds {
+  unsigned short xs[RB * LD1];
+  unsigned short xt[MLP_FEAT * LDT];
+  unsigned short w1s[MLP_HIDDEN * LD1];
+  unsigned short w2s[MLP_HIDDEN * LDH];                                  // W2, then W2^T
+  unsigned short hs[MLP_HIDDEN * LDT > RB * LDH ? MLP_HIDDEN * LDT : RB * LDH];   // H1 [r][h], then dZ1^T [h][r]
+  unsigned short ht[MLP_HIDDEN * LDT];                                   // H1^T
+  unsigned short h2[RB * LDH];                                           // H2 [r][h], then dZ2
+  unsigned short d2t[MLP_HIDDEN * LDT];                                  // dZ2^T
+  float w3[MLP_OUT * MLP_HIDDEN];
+  float dos[RB][2];
+  float red[4][MLP_HIDDEN];
+  float loss[RB];
+};
+
+// Four bf16 values of consecutive rows as one 8-byte store.
+__device__ inline void store4(unsigned short* p, const unsigned short* v) {
+  *(uint2*)p = uint2{(unsigned int)v[0] | (unsigned int)v[1] << 16, (unsigned int)v[2] | (unsigned int)v[3] << 16};
+}
+
+__global__ __launch_bounds__(256) void k_mlp_step(step_args a) {
+  __shared__ __attribute__((aligned(16))) step_lds L;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int nb = (a.n + RB - 1) / RB;
+  // both layouts of the second layer in registers (128 x 16 groups of eight)
+  v4u r2[8], r2t[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int e = tid + 256 * i;
+    r2[i] = ((const v4u*)a.W2)[e];
+    r2t[i] = ((const v4u*)a.W2t)[e];
+  }
+  auto put_w2 = [&](const v4u* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = tid + 256 * i;
+      *(v4u*)(L.w2s + (e >> 4) * LDH + (e & 15) * 8) = v[i];
     }
-    at[i * (CH + 8) + rr] = va;
-    bt[i * (CH + 8) + rr] = vb;
+  };
+  stage_bf16(L.w1s, LD1, a.W1, MLP_HIDDEN, MLP_FEAT);
+  if (tid < MLP_OUT * MLP_HIDDEN) L.w3[tid] = a.p[MLP_OFF_W3 + tid];
+  v16f g2[4], g1 = {};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) g2[t] = v16f{};
+  const int h = tid & 127, hf = tid >> 7;          // this thread's hidden unit and half of the rows
+  float db1 = 0.0f, db2 = 0.0f, dw30 = 0.0f, dw31 = 0.0f, db3 = 0.0f, loss = 0.0f;
+  const float w30 = a.p[MLP_OFF_W3 + h], w31 = a.p[MLP_OFF_W3 + MLP_HIDDEN + h];
+  for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+    const int r0 = b * RB, nrows = min(RB, a.n - r0);
+    put_w2(r2);
+    // features: eight per thread, row tid / 4
+    {
+      const int r = tid >> 2, f0 = (tid & 3) * 8;
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = r < nrows ? a.X[(size_t)(r0 + r) * MLP_FEAT + f0 + i] : 0.0f;
+      unsigned short q[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        q[i] = to_bf16(x[i]);
+        L.xt[(f0 + i) * LDT + r] = q[i];
+      }
+      store4(L.xs + r * LD1 + f0, q);
+      store4(L.xs + r * LD1 + f0 + 4, q + 4);
+    }
+    __syncthreads();
+    // layers 1 and 2: 2 x 4 tiles of 32 x 32 over the four waves
+#pragma unroll
+    for (int t = w; t < 8; t += 4) {
+      const int ti = t >> 2, hh = (t & 3) * 32 + tile_col();
+      v16f acc = {};
+      tile_abt(L.xs + ti * 32 * LD1, LD1, L.w1s + (t & 3) * 32 * LD1, LD1, MLP_FEAT, acc);
+      const float bias = a.p[MLP_OFF_B1 + hh];
+#pragma unroll
+      for (int v = 0; v < 16; v += 4) {
+        const int r = ti * 32 + tile_row(v);
+        unsigned short q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          q[i] = to_bf16(fmaxf(acc[v + i] + bias, 0.0f));
+          L.hs[(r + i) * LDH + hh] = q[i];
+        }
+        store4(L.ht + hh * LDT + r, q);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = w; t < 8; t += 4) {
+      const int ti = t >> 2, hh = (t & 3) * 32 + tile_col();
+      v16f acc = {};
+      tile_abt(L.hs + ti * 32 * LDH, LDH, L.w2s + (t & 3) * 32 * LDH, LDH, MLP_HIDDEN, acc);
+      const float bias = a.p[MLP_OFF_B2 + hh];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) L.h2[(ti * 32 + tile_row(v)) * LDH + hh] = to_bf16(fmaxf(acc[v] + bias, 0.0f));
+    }
+    __syncthreads();
+    put_w2(r2t);
+    // head and loss: four lanes per row, 32 hidden units each
+    {
+      const int r = tid >> 2, q = tid & 3;
+      float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const v4u u = *(const v4u*)(L.h2 + r * LDH + q * 32 + i * 8);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float hv = from_bf16((unsigned short)(u[j >> 1] >> (16 * (j & 1))));
+          const int c = q * 32 + i * 8 + j;
+          s0 = fmaf(hv, L.w3[c], s0);
+          s1 = fmaf(hv, L.w3[MLP_HIDDEN + c], s1);
+        }
+      }
+      s0 += __shfl_xor(s0, 1);
+      s1 += __shfl_xor(s1, 1);
+      s0 += __shfl_xor(s0, 2);
+      s1 += __shfl_xor(s1, 2);
+      if (q == 0) {
+        float d1 = 0.0f, d2 = 0.0f, lr = 0.0f;
+        if (r < nrows) {
+          const float o1 = s0 + a.p[MLP_OFF_B3], o2 = s1 + a.p[MLP_OFF_B3 + 1];
+          const float sp = o1 > 20.0f ? o1 : log1pf(expf(o1));
+          const float sg = 1.0f / (1.0f + expf(-o1));
+          const float e1 = logf(sp) - a.T[(size_t)(r0 + r) * 2], e2 = o2 - a.T[(size_t)(r0 + r) * 2 + 1];
+          lr = e1 * e1 + e2 * e2;
+          d1 = 2.0f * e1 / (float)a.n * sg / sp;
+          d2 = 2.0f * e2 / (float)a.n;
+        }
+        L.dos[r][0] = d1;
+        L.dos[r][1] = d2;
+        L.loss[r] = lr;
+      }
+    }
+    __syncthreads();
+    if (tid < 3) {   // db3 and the loss, in row order
+      float s = 0.0f;
+      for (int r = 0; r < RB; ++r) s += tid < 2 ? L.dos[r][tid] : L.loss[r];
+      if (tid < 2) db3 += s;
+      else loss += s;
+    }
+    // dZ2 over H2 (in place, and transposed), db2 and dW3
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      unsigned short q[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = hf * 32 + g * 8 + i;
+        const float hv = from_bf16(L.h2[r * LDH + h]);
+        const float d1 = L.dos[r][0], d2 = L.dos[r][1];
+        dw30 = fmaf(d1, hv, dw30);
+        dw31 = fmaf(d2, hv, dw31);
+        q[i] = hv > 0.0f ? to_bf16(d1 * w30 + d2 * w31) : (unsigned short)0;
+        db2 += from_bf16(q[i]);
+        L.h2[r * LDH + h] = q[i];
+      }
+      store4(L.d2t + h * LDT + hf * 32 + g * 8, q);
+      store4(L.d2t + h * LDT + hf * 32 + g * 8 + 4, q + 4);
+    }
+    __syncthreads();
+    // dZ1^T into the place of H1 (whose last reader was layer 2)
+#pragma unroll
+    for (int t = w; t < 8; t += 4) {
+      const int ti = t >> 2, hh = (t & 3) * 32 + tile_col();
+      v16f acc = {};
+      tile_abt(L.h2 + ti * 32 * LDH, LDH, L.w2s + (t & 3) * 32 * LDH, LDH, MLP_HIDDEN, acc);
+#pragma unroll
+      for (int v = 0; v < 16; v += 4) {
+        const int r = ti * 32 + tile_row(v);
+        const uint2 on = *(const uint2*)(L.ht + hh * LDT + r);
+        unsigned short q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const unsigned short hv = (unsigned short)((i < 2 ? on.x : on.y) >> (16 * (i & 1)));
+          q[i] = from_bf16(hv) > 0.0f ? to_bf16(acc[v + i]) : (unsigned short)0;
+        }
+        store4(L.hs + hh * LDT + r, q);
+      }
+    }
+    // dW2: 4 x 4 tiles, wave w the tile row w
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      tile_abt(L.d2t + w * 32 * LDT, LDT, L.ht + t * 32 * LDT, LDT, RB, g2[t]);
+    __syncthreads();
+    // dW1: 4 x 1 tiles; db1
+    tile_abt(L.hs + w * 32 * LDT, LDT, L.xt, LDT, RB, g1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const v4u u = *(const v4u*)(L.hs + h * LDT + hf * 32 + i * 8);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) db1 += from_bf16((unsigned short)(u[j >> 1] >> (16 * (j & 1))));
+    }
+    __syncthreads();   // the next block refills xs, xt and w2s
+  }
+  float* p = a.part + (size_t)blockIdx.x * MLP_PART;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int i = w * 32 + tile_row(v);
+    p[MLP_OFF_W1 + i * MLP_FEAT + tile_col()] = g1[v];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) p[MLP_OFF_W2 + i * MLP_HIDDEN + t * 32 + tile_col()] = g2[t][v];
+  }
+  // the two halves of the rows
+  if (hf == 1) {
+    L.red[0][h] = db1;
+    L.red[1][h] = db2;
+    L.red[2][h] = dw30;
+    L.red[3][h] = dw31;
   }
   __syncthreads();
-  v16f acc = {};
-  tile_abt(at, CH + 8, bt, CH + 8, CH, acc);
-  float* p = g.part + (size_t)c * g.M * g.N;
+  if (hf == 0) {
+    p[MLP_OFF_B1 + h] = db1 + L.red[0][h];
+    p[MLP_OFF_B2 + h] = db2 + L.red[1][h];
+    p[MLP_OFF_W3 + h] = dw30 + L.red[2][h];
+    p[MLP_OFF_W3 + MLP_HIDDEN + h] = dw31 + L.red[3][h];
+  }
+  if (tid < 2) p[MLP_OFF_B3 + tid] = db3;
+  if (tid == 2) p[MLP_NPARAM] = loss;
+  (void)l;
+}
+
+struct update_args {
+  const float* part;
+  int G, n;
+  float* g;        // gradient in the state
+  float* grads;    // the caller's copy, or NULL
+  float* loss;
+  int adam;        // 1: also the Adam step below
+  float *p, *m, *v;
+  unsigned short *W1, *W2, *W2t;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// 64 parameters per workgroup (the last index is the loss), four threads each
+// a quarter of the partials, eight loads in flight, summed in order.
+__global__ __launch_bounds__(256) void k_mlp_update(update_args a) {
+  __shared__ float red[4][64];
+  const int l = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + l;
+  const int per = (a.G + 3) >> 2, g0 = q * per, g1 = min(a.G, g0 + per);
+  float s = 0.0f;
+  const float* src = a.part + i;     // i < MLP_PART always
+  int g = g0;
+  for (; g + 8 <= g1; g += 8) {
+    float v[8];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) p[(size_t)(ti * 32 + tile_row(v)) * g.N + tj * 32 + tile_col()] = acc[v];
-}
-
-// Bias gradient partials: db[j] over a chunk of 256 rows of D [n][N] (bf16).
-__global__ __launch_bounds__(128) void k_mlp_bgrad(const unsigned short* D, int N, int n, float* part) {
-  const int j = threadIdx.x, c = blockIdx.x;
-  float s = 0.0f;
-  for (int r = c * 256; r < min(n, (c + 1) * 256); ++r) s += from_bf16(D[(size_t)r * N + j]);
-  part[(size_t)c * N + j] = s;
-}
-
-// Sum partials over chunks in chunk order into g (FP32).
-__global__ void k_mlp_reduce(const float* part, int nchunk, int len, int stride, float* g) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= len) return;
-  float s = 0.0f;
-  for (int c = 0; c < nchunk; ++c) s += part[(size_t)c * stride + i];
-  g[i] = s;
-}
-
-// Adam on the FP32 master weights, then the bf16 copies (W1, W2, W2^T) and
-// the FP32 head.
-__global__ void k_mlp_adam(float* p, float* m, float* v, const float* g, int np, float lr, float b1, float b2,
-                           float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= np) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+    for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(g + u) * MLP_PART];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; g < g1; ++g) s += src[(size_t)g * MLP_PART];
+  red[q][l] = s;
+  __syncthreads();
+  if (q != 0 || i > MLP_NPARAM) return;
+  s = ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
+  if (i == MLP_NPARAM) {
+    *a.loss = s * (1.0f / (float)a.n);
+    return;
+  }
+  a.g[i] = s;
+  if (a.grads) a.grads[i] = s;
+  if (!a.adam) return;
+  const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * s;
+  const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * s * s;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float pi = a.p[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+  a.p[i] = pi;
+  if (i < MLP_OFF_B1) a.W1[i - MLP_OFF_W1] = to_bf16(pi);
+  if (i >= MLP_OFF_W2 && i < MLP_OFF_B2) {
+    const int e = i - MLP_OFF_W2;
+    a.W2[e] = to_bf16(pi);
+    a.W2t[(e % MLP_HIDDEN) * MLP_HIDDEN + e / MLP_HIDDEN] = to_bf16(pi);
+  }
 }
 
 __global__ void k_mlp_quantise(const float* p, unsigned short* W1, unsigned short* W2, unsigned short* W2t) {
@@ -369,8 +510,6 @@ __global__ void k_mlp_quantise(const float* p, unsigned short* W1, unsigned shor
     W2t[(i % MLP_HIDDEN) * MLP_HIDDEN + i / MLP_HIDDEN] = q;
   }
 }
-
-__global__ void k_mlp_scale(float* x, float f) { x[0] *= f; }
 
 __global__ void k_mlp_zero2(float* a, float* b, int np) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -396,17 +535,12 @@ namespace {
 struct state_view {
   float *p, *m, *v, *g;                 // MLP_NPARAM each
   unsigned short *W1, *W2, *W2t;        // bf16 copies
-  unsigned short *H1, *H2, *dZ2, *dZ1;  // [rows][128]
-  float* out;                           // [rows][2]
-  float* part;                          // partial sums
+  float* part;                          // partial sums of the step's workgroups
 };
 
-size_t part_floats(int rows) {
-  const size_t nb = (rows + RB - 1) / RB, nc = (rows + 255) / 256;
-  const size_t a = nb * (2 + 2 * MLP_HIDDEN + 1);
-  const size_t b = nc * MLP_HIDDEN * MLP_HIDDEN;
-  return a > b ? a : b;
-}
+int step_workgroups(int rows) { return std::min((rows + RB - 1) / RB, MLP_STEP_WG); }
+
+size_t part_floats(int rows) { return (size_t)step_workgroups(rows) * MLP_PART; }
 
 state_view carve(void* base, int rows) {
   char* c = (char*)base;
@@ -419,11 +553,6 @@ state_view carve(void* base, int rows) {
   s.W1 = (unsigned short*)take(MLP_HIDDEN * MLP_FEAT * 2);
   s.W2 = (unsigned short*)take(MLP_HIDDEN * MLP_HIDDEN * 2);
   s.W2t = (unsigned short*)take(MLP_HIDDEN * MLP_HIDDEN * 2);
-  s.H1 = (unsigned short*)take((size_t)rows * MLP_HIDDEN * 2);
-  s.H2 = (unsigned short*)take((size_t)rows * MLP_HIDDEN * 2);
-  s.dZ2 = (unsigned short*)take((size_t)rows * MLP_HIDDEN * 2);
-  s.dZ1 = (unsigned short*)take((size_t)rows * MLP_HIDDEN * 2);
-  s.out = (float*)take((size_t)rows * 2 * 4);
   s.part = (float*)take(part_floats(rows) * 4);
   return s;
 }
@@ -445,7 +574,7 @@ hipError_t launch_mlp_frames(const batch_ref& br, int grid, const void* blob,
 
 hipError_t mlp_forward_blob(const void* blob, const float* X, int n, float* out, hipStream_t st) {
   const mlp_blob* b = (const mlp_blob*)blob;
-  fwd_args a = {X, n, b->W1, b->W2, b->W3, b->b1, b->b2, b->b3, out, nullptr, nullptr};
+  fwd_args a = {X, n, b->W1, b->W2, b->W3, b->b1, b->b2, b->b3, out};
   hipLaunchKernelGGL(k_mlp_forward, dim3((n + RB - 1) / RB), dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -491,57 +620,53 @@ hipError_t mlp_load_state(void* state, int rows, const float* in, hipStream_t st
   return hipGetLastError();
 }
 
+namespace {
+
 // Forward, loss and backward over n <= rows rows: the gradient of the mean
-// loss into the state (and into grads when not NULL), the loss into *loss.
-hipError_t mlp_gradients(void* state, int rows, const float* X, const float* T, int n, float* loss, float* grads,
-                         hipStream_t st) {
+// loss into the state (and into grads when not NULL), the loss into *loss;
+// then, with u.adam set, the Adam step.
+hipError_t step(void* state, int rows, const float* X, const float* T, int n, float* loss, float* grads,
+                update_args u, hipStream_t st) {
   const state_view s = carve(state, rows);
-  const int nb = (n + RB - 1) / RB, nc = (n + 255) / 256;
-  fwd_args a = {X, n, s.W1, s.W2, s.p + MLP_OFF_W3, s.p + MLP_OFF_B1, s.p + MLP_OFF_B2, s.p + MLP_OFF_B3,
-                s.out, s.H1, s.H2};
-  hipLaunchKernelGGL(k_mlp_forward, dim3(nb), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_mlp_loss, dim3(nb), dim3(256), 0, st, s.out, T, n, s.p + MLP_OFF_W3, s.H2, s.dZ2, s.part);
-  // loss / n, dW3, db3 from the per-block partials (in block order)
-  const int hs = 2 + 2 * MLP_HIDDEN + 1;
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(1), dim3(256), 0, st, s.part, nb, 1, hs, loss);
-  hipLaunchKernelGGL(k_mlp_scale, dim3(1), dim3(1), 0, st, loss, 1.0f / (float)n);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(1), dim3(256), 0, st, s.part + 1, nb, MLP_OUT * MLP_HIDDEN, hs,
-                     s.g + MLP_OFF_W3);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(1), dim3(256), 0, st, s.part + 1 + MLP_OUT * MLP_HIDDEN, nb, MLP_OUT, hs,
-                     s.g + MLP_OFF_B3);
-  // dW2 = dZ2^T H1 and db2
-  wgrad_args g2 = {s.dZ2, nullptr, MLP_HIDDEN, s.H1, nullptr, MLP_HIDDEN, n, s.part};
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3(16, nc), dim3(64), 0, st, g2);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(MLP_HIDDEN * MLP_HIDDEN / 256), dim3(256), 0, st, s.part, nc,
-                     MLP_HIDDEN * MLP_HIDDEN, MLP_HIDDEN * MLP_HIDDEN, s.g + MLP_OFF_W2);
-  hipLaunchKernelGGL(k_mlp_bgrad, dim3(nc), dim3(MLP_HIDDEN), 0, st, s.dZ2, MLP_HIDDEN, n, s.part);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(1), dim3(MLP_HIDDEN), 0, st, s.part, nc, MLP_HIDDEN, MLP_HIDDEN,
-                     s.g + MLP_OFF_B2);
-  // dZ1 = (dZ2 W2) * [H1 > 0]; dW1 = dZ1^T X and db1
-  hipLaunchKernelGGL(k_mlp_back_h1, dim3(nb), dim3(256), 0, st, s.dZ2, s.W2t, s.H1, n, s.dZ1);
-  wgrad_args g1 = {s.dZ1, nullptr, MLP_HIDDEN, nullptr, X, MLP_FEAT, n, s.part};
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3(4, nc), dim3(64), 0, st, g1);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(MLP_HIDDEN * MLP_FEAT / 256), dim3(256), 0, st, s.part, nc,
-                     MLP_HIDDEN * MLP_FEAT, MLP_HIDDEN * MLP_FEAT, s.g + MLP_OFF_W1);
-  hipLaunchKernelGGL(k_mlp_bgrad, dim3(nc), dim3(MLP_HIDDEN), 0, st, s.dZ1, MLP_HIDDEN, n, s.part);
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(1), dim3(MLP_HIDDEN), 0, st, s.part, nc, MLP_HIDDEN, MLP_HIDDEN,
-                     s.g + MLP_OFF_B1);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && grads) e = hipMemcpyAsync(grads, s.g, MLP_NPARAM * 4, hipMemcpyDeviceToDevice, st);
-  return e;
+  const int G = step_workgroups(n);
+  const step_args a = {X, T, n, s.W1, s.W2, s.W2t, s.p, s.part};
+  hipLaunchKernelGGL(k_mlp_step, dim3(G), dim3(256), 0, st, a);
+  u.part = s.part;
+  u.G = G;
+  u.n = n;
+  u.g = s.g;
+  u.grads = grads;
+  u.loss = loss;
+  u.p = s.p;
+  u.m = s.m;
+  u.v = s.v;
+  u.W1 = s.W1;
+  u.W2 = s.W2;
+  u.W2t = s.W2t;
+  hipLaunchKernelGGL(k_mlp_update, dim3(MLP_PART / 64), dim3(256), 0, st, u);
+  return hipGetLastError();
 }
 
-// One Adam step (beta1 0.9, beta2 0.999, eps 1e-8) with the gradient in the
-// state, then the bf16 copies.  step counts from 1.
-hipError_t mlp_adam_step(void* state, int rows, float lr, int step, hipStream_t st) {
-  const state_view s = carve(state, rows);
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.0f / (1.0f - powf(b1, (float)step)), c2 = 1.0f / (1.0f - powf(b2, (float)step));
-  hipLaunchKernelGGL(k_mlp_adam, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, st, s.p, s.m, s.v, s.g, MLP_NPARAM,
-                     lr, b1, b2, 1e-8f, c1, c2);
-  hipLaunchKernelGGL(k_mlp_quantise, dim3((MLP_HIDDEN * MLP_HIDDEN + 255) / 256), dim3(256), 0, st, s.p, s.W1, s.W2,
-                     s.W2t);
-  return hipGetLastError();
+}  // namespace
+
+hipError_t mlp_gradients(void* state, int rows, const float* X, const float* T, int n, float* loss, float* grads,
+                         hipStream_t st) {
+  return step(state, rows, X, T, n, loss, grads, update_args{}, st);
+}
+
+// The gradient and one Adam step (beta1 0.9, beta2 0.999, eps 1e-8); k counts
+// from 1.
+hipError_t mlp_train_step(void* state, int rows, const float* X, const float* T, int n, float lr, int k, float* loss,
+                          hipStream_t st) {
+  update_args u = {};
+  u.adam = 1;
+  u.lr = lr;
+  u.b1 = 0.9f;
+  u.b2 = 0.999f;
+  u.eps = 1e-8f;
+  u.c1 = 1.0f / (1.0f - powf(u.b1, (float)k));
+  u.c2 = 1.0f / (1.0f - powf(u.b2, (float)k));
+  return step(state, rows, X, T, n, loss, nullptr, u, st);
 }
 
 hipError_t mlp_export(const void* state, int rows, void* blob, hipStream_t st) {
