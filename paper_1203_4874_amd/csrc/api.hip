@@ -147,6 +147,14 @@ constexpr tuning kDefaultTuning = {0, 0, 0, 0};
 constexpr int kRowItemsPerFrame = 384;
 constexpr int kRowWgPerCu = 4;   // resident inverse-row workgroups per CU (LDS: a row and its pass twiddle tables)
 
+// A call with fewer fused row-pass items than this runs the split row pass:
+// single rows spread over the chip and the column fold reads the frames again
+// (they sit in the caches), instead of items of several rows in turn on part
+// of the chip.  Whole calls, fused / split: 1000x180 FP32 125 / 96 us, 480x640
+// 135 / 123, 1080p RGB FP32 (411 items) 350 / 344; 719x1277 FP64 (255) 202 /
+// 196, 1080p RGB FP64 (429) 402 / 405.
+constexpr int split_row_items(int esize) { return esize == 4 ? 512 : 400; }
+
 // Does a strip of cw columns of length Py fit the column pass?
 bool col_fits(int Py, int cw, int twn, int esize) {
   return col_lds_bytes(Py, cw, twn, esize) <= kLdsLimit - 4096 && (int64_t)cw * Py <= col_max_strip_elems(esize);
@@ -438,6 +446,8 @@ struct chunk_view {
   int colGroups;        // the column filter's row groups of the frames (bit g set for group g)
   int gram_fmt;   // gram_format() of the call's precision
   int maxStride;  // largest Hmax / Wmax (matrix-core Gram staging)
+  bool split;     // the row pass takes single rows and the first launch folds (split_row_items)
+  front_grid front;   // the first launch
   bool finLean;   // no frame's scale solve refines or records diagnostics
   const void* mlp;  // the learned form's network (device mlp blob) or NULL
 };
@@ -455,15 +465,15 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
   const batch_ref b = {cv.descs, cv.starts, cv.nf, cv.ctr};
   auto br = [&](int) { return b; };
   const bool dd = cv.gram_fmt < 0;
-  // the first launch (with an inline head it also stores the call's head):
-  // a deblurring call's twiddle table of the kernels' row DFTs only, since
-  // its row pass folds the columns; a kernel-only call's column fold
-  CBP_TRY(launch_fold<T>(br(Q_FOLD), latent ? 0 : cv.grid[Q_FOLD], latent ? cv.grid[Q_TWID] : 0, ih, st));
+  // the first launch (with an inline head it also stores the call's head): a
+  // kernel-only call's column fold and row evaluation; a small deblurring
+  // call's single rows, column fold and twiddle tables; else the twiddle
+  // tables alone, the row pass that follows folding and evaluating
+  if (!latent) CBP_TRY(launch_front<T>(br(Q_FOLD), cv.front, ih, st));
+  else if (cv.split) CBP_TRY(launch_rows_front<T>(br(Q_ROWS), cv.front, cv.maxPx, cv.maxTwx, ih, st));
+  else CBP_TRY(launch_front<T>(br(Q_TWID), cv.front, ih, st));
   if (diag) CBP_TRY(launch_diag_init(br(Q_DIAG), cv.grid[Q_DIAG], st));
-  // the row pass (with the column fold and the row evaluation) or the row
-  // evaluation alone, then the column evaluation of the fold
-  if (latent) CBP_TRY(launch_row_fwd<T>(br(Q_ROW_FWD), cv.grid[Q_ROW_FWD], cv.maxPx, cv.maxTwx, 1, st));
-  else CBP_TRY(launch_eval_rows<T>(br(Q_EVAL_ROWS), cv.grid[Q_EVAL_ROWS], st));
+  if (latent && !cv.split) CBP_TRY(launch_row_fwd<T>(br(Q_ROW_FWD), cv.grid[Q_ROW_FWD], cv.maxPx, cv.maxTwx, 1, st));
   CBP_TRY(launch_eval_cols(br(Q_EVAL_COLS), cv.grid[Q_EVAL_COLS], st));
   // join: the Gram needs the row evaluation (and the column pass the row spectra)
   if (cv.gram_fmt < 0) CBP_TRY(launch_gram(br(Q_GRAM), cv.grid[Q_GRAM], st));
@@ -623,6 +633,15 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
       cv.colGroups |= 1 << col_group_size(p.Py);
     }
     const int esize = dtype == CBP_F32 ? 4 : 8;
+    cv.split = bb->latent && cv.items[Q_ROW_FWD] < split_row_items(dtype == CBP_F32 ? 4 : 8);
+    {
+      // four fold items per workgroup
+      auto grid4 = [&](int items) { return grid_for((items + 3) / 4, cap); };
+      cv.front = front_grid{};
+      if (!bb->latent) cv.front = front_grid{0, grid4(cv.items[Q_FOLD]), cv.grid[Q_EVAL_ROWS], 0};
+      else if (cv.split) cv.front = front_grid{grid_for(cv.items[Q_ROWS], kRowWgPerCu * kComputeUnits), grid4(cv.items[Q_FOLD]), 0, cv.grid[Q_TWID]};
+      else cv.front.twid = cv.grid[Q_TWID];
+    }
     // as many persistent row-pass workgroups as stay resident
     if (cap == 0) cv.grid[Q_ROW_FWD] = grid_for(cv.items[Q_ROW_FWD], row_fwd_per_cu(row_lds_bytes(cv.maxPx, cv.maxTwx, esize), esize) * kComputeUnits);
     // the widest strip and the tallest column share one allocation; keep it in LDS
@@ -962,7 +981,7 @@ cbp_status cbp_eval_unit_circle(const cbp_image* b, int32_t S, double* ex, doubl
   d.ex = (c64*)ex;
   d.ey = (c64*)ey;
   int items[Q_COUNT] = {};
-  items[Q_FOLD] = ((d.Wmax + 63) / 64) * S * d.RG;
+  items[Q_FOLD] = ((d.Wmax + FOLD_COLS - 1) / FOLD_COLS) * S * d.RG;
   items[Q_EVAL_COLS] = (d.Wmax + 15) / 16;
   items[Q_EVAL_ROWS] = (d.Hmax + 1) / 2;   // as queue_items, one (channel, frame) slot
   std::vector<char> hb(head, 0);
@@ -977,11 +996,10 @@ cbp_status cbp_eval_unit_circle(const cbp_image* b, int32_t S, double* ex, doubl
   (void)hipGetLastError();
   auto run = [&]() -> hipError_t {
     CBP_TRY(upload_bytes(*ds, ws, hb, st));
-    if (b->dtype == CBP_F32) CBP_TRY(launch_fold<float>(br, grid_for(items[Q_FOLD], 0), 0, nullptr, st));
-    else CBP_TRY(launch_fold<double>(br, grid_for(items[Q_FOLD], 0), 0, nullptr, st));
+    const front_grid g = {0, grid_for((items[Q_FOLD] + 3) / 4, 0), grid_for(items[Q_EVAL_ROWS], 0), 0};
+    if (b->dtype == CBP_F32) CBP_TRY(launch_front<float>(br, g, nullptr, st));
+    else CBP_TRY(launch_front<double>(br, g, nullptr, st));
     CBP_TRY(launch_eval_cols(br, grid_for(items[Q_EVAL_COLS], 0), st));
-    if (b->dtype == CBP_F32) CBP_TRY(launch_eval_rows<float>(br, grid_for(items[Q_EVAL_ROWS], 0), st));
-    else CBP_TRY(launch_eval_rows<double>(br, grid_for(items[Q_EVAL_ROWS], 0), st));
     return hipSuccess;
   };
   return run() == hipSuccess ? CBP_OK : CBP_E_DEVICE;
@@ -1019,13 +1037,8 @@ cbp_status cbp_sample_grams(const cbp_image* b1, const cbp_image* b2, int32_t m,
   (void)hipGetLastError();
   auto run = [&]() -> hipError_t {
     CBP_TRY(upload_head(*ds, bb, st));
-    if (b1->dtype == CBP_F32) {
-      CBP_TRY(launch_fold<float>(br, cv.grid[Q_FOLD], 0, nullptr, st));
-      CBP_TRY(launch_eval_rows<float>(br, cv.grid[Q_EVAL_ROWS], st));
-    } else {
-      CBP_TRY(launch_fold<double>(br, cv.grid[Q_FOLD], 0, nullptr, st));
-      CBP_TRY(launch_eval_rows<double>(br, cv.grid[Q_EVAL_ROWS], st));
-    }
+    if (b1->dtype == CBP_F32) CBP_TRY(launch_front<float>(br, cv.front, nullptr, st));
+    else CBP_TRY(launch_front<double>(br, cv.front, nullptr, st));
     CBP_TRY(launch_eval_cols(br, cv.grid[Q_EVAL_COLS], st));
     if (cv.gram_fmt < 0) CBP_TRY(launch_gram(br, cv.grid[Q_GRAM], st));
     else CBP_TRY(launch_gram_mfma(br, cv.grid[Q_GRAMM], cv.gram_fmt, cv.maxStride, st));
@@ -1137,13 +1150,8 @@ cbp_status cbp_estimate_kernel_sizes(const cbp_image* b1, const cbp_image* b2, c
     inline_head ih;
     const bool inl = make_inline_head(bb, &ih);
     if (!inl) CBP_TRY(upload_head(*ds, bb, st));
-    if (b1->dtype == CBP_F32) {
-      CBP_TRY(launch_fold<float>(br, cv.grid[Q_FOLD], 0, inl ? &ih : nullptr, st));
-      CBP_TRY(launch_eval_rows<float>(br, cv.grid[Q_EVAL_ROWS], st));
-    } else {
-      CBP_TRY(launch_fold<double>(br, cv.grid[Q_FOLD], 0, inl ? &ih : nullptr, st));
-      CBP_TRY(launch_eval_rows<double>(br, cv.grid[Q_EVAL_ROWS], st));
-    }
+    if (b1->dtype == CBP_F32) CBP_TRY(launch_front<float>(br, cv.front, inl ? &ih : nullptr, st));
+    else CBP_TRY(launch_front<double>(br, cv.front, inl ? &ih : nullptr, st));
     CBP_TRY(launch_eval_cols(br, cv.grid[Q_EVAL_COLS], st));
     CBP_TRY(launch_gram(br, cv.grid[Q_GRAM], st));
     CBP_TRY(launch_size_probe(br, c, S, nmax, NL, rat, st));

@@ -168,14 +168,62 @@ __device__ __attribute__((always_inline)) inline void ip_fft(cplx<T>* buf, int l
 constexpr int ROW_MAXE = CBP_MAX_FFT_F32 > CBP_MAX_FFT_F64 ? CBP_MAX_FFT_F32 : CBP_MAX_FFT_F64;
 
 // ---------------------------------------------------------------- pass 1
+// Rows y of both frames of channel ch, packed as B1 + i B2 in a (LDS, zero
+// beyond each frame): with with_ey their unit-circle evaluation, then the FFT
+// and the two half spectra.  twf: the plan's pass tables, twS: w_S^t.  Ends
+// with a barrier.
+template <typename T>
+__device__ __attribute__((always_inline)) inline void row_transform(const frame_desc& d, int ch, int y, int with_ey,
+                                                                    cplx<T>* a, const cplx<T>* twf,
+                                                                    double (*gy)[CBP_MAX_S], double (*fpart_l)[128],
+                                                                    const c64* twS) {
+  const fft_plan& px = d.fx;
+  const int N = px.N, hx = d.hx, S = d.S;
+  const bool in1 = y < d.H1, in2 = y < d.H2;
+  if (with_ey) {
+    // the row evaluation of both rows (k_front's lanes and order): waves
+    // 2 fr, 2 fr + 1 fold frame fr's row into partials, lane g S + r of the
+    // pair summing x = r + S (g + G i); the residues then add their G
+    // partials in order
+    const int G = 128 / S;
+    const int fr = threadIdx.x >> 7, l = threadIdx.x & 127;
+    const int gl = l / S, rr0 = l - gl * S;
+    const bool inr = fr ? in2 : in1;
+    {
+      double acc = 0.0;
+      if (inr && gl < G) acc = fold_strided((const T*)a + fr, 2, rr0 + S * gl, S * G, fr ? d.W2 : d.W1);
+      fpart_l[fr][l] = acc;
+    }
+    __syncthreads();
+    if (l < S) {
+      double sr = fpart_l[fr][l];
+      for (int gq = 1; gq < G; ++gq) sr += fpart_l[fr][gq * S + l];
+      gy[fr][l] = sr;
+    }
+    __syncthreads();
+    if (l < S && inr) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[fr], 1, twS, S, l);
+  }
+  ip_fft<-1, 256, ROW_MAXE, true>(a, N, px, twf, 1);
+  cplx<T>* o1 = (cplx<T>*)d.t1 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
+  cplx<T>* o2 = (cplx<T>*)d.t2 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
+  for (int k = threadIdx.x; k < hx; k += blockDim.x) {
+    const cplx<T> zk = a[k];
+    const cplx<T> zn = conj(a[k == 0 ? 0 : N - k]);
+    const cplx<T> s = zk + zn, df = zk - zn;
+    if (in1) o1[k] = {T(0.5) * s.re, T(0.5) * s.im};       // (Z_k + conj Z_{N-k}) / 2
+    if (in2) o2[k] = {T(0.5) * df.im, T(-0.5) * df.re};    // (Z_k - conj Z_{N-k}) / (2i)
+  }
+  __syncthreads();
+}
+
 // Items: (channel, row group g, residue r): the rows y = g rpg + r + S i,
 // i < rpg / S, y < Hmax, in increasing y.  Each row of both frames is packed
 // as B1 + i B2 and transformed; while the rows pass, the workgroup folds them
-// (the column fold of k_fold_cols: the same rows of the same residue and
+// (the column fold of fold_item: the same rows of the same residue and
 // group, summed in increasing y in FP64, hence the same bits) and writes
 // the group's partial sums, so the frames are read once.  With with_ey, the
 // unit-circle evaluation of both rows (fold modulo S and S-point DFT, as
-// k_eval_rows: the same lanes, the same order, hence the same bits) is taken
+// eval_rows_item: the same lanes, the same order, hence the same bits) is taken
 // from the row in LDS; waves 0-1 fold frame (w & 1).  The grid is
 // persistent: a workgroup loads its next row into registers while it
 // transforms the current one.
@@ -264,7 +312,7 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
     const frame_desc d = desc(fi);
     const rows_of_item q = item_rows(d, it - __builtin_amdgcn_readfirstlane(st[fi]));
     const fft_plan& px = d.fx;
-    const int N = px.N, hx = d.hx, S = d.S;
+    const int N = px.N, S = d.S;
     cplx<T>* a = (cplx<T>*)sm_rf;
     cplx<T>* twf = a + N;
     const int ch = q.ch;
@@ -295,43 +343,9 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
       // the next row is in flight while this one is transformed
       if (i + 1 < q.nv) fetch(d, ch, y + S);
       else fetch_from(it + step);
-      if (with_ey) {
-        // the row evaluation of both rows (k_eval_rows's lanes and order):
-        // waves 2 fr, 2 fr + 1 fold frame fr's row into partials, lane
-        // g S + r of the pair summing x = r + S (g + G i); the residues then
-        // add their G partials in order
-        const int G = 128 / S;
-        const int fr = threadIdx.x >> 7, l = threadIdx.x & 127;
-        const int gl = l / S, rr0 = l - gl * S;
-        const bool inr = fr ? in2 : in1;
-        {
-          double acc = 0.0;
-          if (inr && gl < G) acc = fold_strided((const T*)a + fr, 2, rr0 + S * gl, S * G, fr ? W2 : W1);
-          fpart_l[fr][l] = acc;
-        }
-        __syncthreads();
-        if (l < S) {
-          double sr = fpart_l[fr][l];
-          for (int gq = 1; gq < G; ++gq) sr += fpart_l[fr][gq * S + l];
-          gy[fr][l] = sr;
-        }
-        __syncthreads();
-        if (l < S && inr) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[fr], 1, twS, S, l);
-      }
-      ip_fft<-1, 256, ROW_MAXE, true>(a, N, px, twf, 1);
-      const cplx<T>* z = a;
-      cplx<T>* o1 = (cplx<T>*)d.t1 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
-      cplx<T>* o2 = (cplx<T>*)d.t2 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
-      for (int k = threadIdx.x; k < hx; k += blockDim.x) {
-        const cplx<T> zk = z[k];
-        const cplx<T> zn = conj(z[k == 0 ? 0 : N - k]);
-        const cplx<T> s = zk + zn, df = zk - zn;
-        if (in1) o1[k] = {T(0.5) * s.re, T(0.5) * s.im};       // (Z_k + conj Z_{N-k}) / 2
-        if (in2) o2[k] = {T(0.5) * df.im, T(-0.5) * df.re};    // (Z_k - conj Z_{N-k}) / (2i)
-      }
-      __syncthreads();
+      row_transform<T>(d, ch, y, with_ey, a, twf, gy, fpart_l, twS);
     }
-    // the group's column-fold partials (k_fold_cols's layout), for x < W
+    // the group's column-fold partials (fold_item's layout), for x < W
     double* fp1 = d.fpart + (((size_t)q.g * d.ncf + 2 * ch) * S + q.r) * (size_t)d.Wmax;
     double* fp2 = d.fpart + (((size_t)q.g * d.ncf + 2 * ch + 1) * S + q.r) * (size_t)d.Wmax;
 #pragma unroll
@@ -341,6 +355,57 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
       if (x < W2) fp2[x] = f2[t];
     }
   }
+}
+
+// The split row pass, a call's first launch (a small call, see split_row_items
+// in api.hip): g.rows workgroups take single rows (channel, y), g.fold fold the
+// columns from the frames themselves (k_front's fold, the same bits), g.twid
+// fill the twiddle tables.  A row is a workgroup of its own instead of a
+// turn of one residue's: 480x640 (168 items of three rows) 22.7 us and 4.7 for
+// the launch before it -> 13.6; 64x64 FP64 38.8 and 4.5 -> 8.4.
+template <typename T>
+__global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid g, inline_head ih) {
+  extern __shared__ __attribute__((aligned(16))) char sm_rf[];
+  __shared__ double gy[2][CBP_MAX_S];
+  __shared__ double fpart_l[2][128];
+  __shared__ c64 twS[CBP_MAX_S];
+  const batch_ref br = first_launch_head(br_ws, ih);
+  const int b = (int)blockIdx.x;
+  if (b >= g.rows) {
+    if (b < g.rows + g.fold)
+      for_wave_items<Q_FOLD>(br, b - g.rows, g.fold, [&](const frame_desc& d, int item, int lane)
+                                                         __attribute__((always_inline)) { fold_item<T>(d, item, lane); });
+    else
+      for_items_part<Q_TWID>(br, b - g.rows - g.fold, g.twid,
+                             [&](const frame_desc& d, int item) __attribute__((always_inline)) { twiddle_item(d, item); });
+    return;
+  }
+  int tabN = 0, tabS = 0;
+  unsigned long long tabCode = 0;
+  for_items_part<Q_ROWS>(br, b, g.rows, [&](const frame_desc& d, int item) __attribute__((always_inline)) {
+    const int N = d.fx.N, ch = item / d.Hmax, y = item - ch * d.Hmax;
+    cplx<T>* a = (cplx<T>*)sm_rf;
+    cplx<T>* twf = a + N;
+    const T* r1 = (const T*)d.b1 + ch * d.cs1 + (int64_t)min(y, d.H1 - 1) * d.p1;
+    const T* r2 = (const T*)d.b2 + ch * d.cs2 + (int64_t)min(y, d.H2 - 1) * d.p2;
+    T uv[8], wv[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int x = t * 256 + local_tid();
+      uv[t] = r1[min(x, d.W1 - 1)];
+      wv[t] = r2[min(x, d.W2 - 1)];
+    }
+    pass_twiddles(twf, d.fx, tabN, tabCode);
+    if (d.S != tabS) unit_twiddles(twS, d.S);
+    tabS = d.S;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int x = t * 256 + local_tid();
+      if (x < N) a[x] = {(y < d.H1 && x < d.W1) ? uv[t] : T(0), (y < d.H2 && x < d.W2) ? wv[t] : T(0)};
+    }
+    __syncthreads();
+    row_transform<T>(d, ch, y, 1, a, twf, gy, fpart_l, twS);
+  });
 }
 
 // ---------------------------------------------------------------- pass 2
@@ -853,8 +918,8 @@ int col_per_cu(int N, int cw, int twn, int g, int esize) {
 }
 
 void set_fft_attrs() {
-  const void* fns[4] = {(const void*)k_row_fwd<float>, (const void*)k_row_inv<float>, (const void*)k_row_fwd<double>,
-                        (const void*)k_row_inv<double>};
+  const void* fns[] = {(const void*)k_row_fwd<float>,  (const void*)k_row_inv<float>,  (const void*)k_rows_front<float>,
+                       (const void*)k_row_fwd<double>, (const void*)k_row_inv<double>, (const void*)k_rows_front<double>};
   for (const void* f : fns) hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   for (int nt : {256, 512, 1024})
     for (int g : {4, 2, 1}) {
@@ -902,6 +967,23 @@ hipError_t launch_row_inv(const batch_ref& br, int grid, int maxPx, int maxTw, h
 }
 
 
+template <typename T>
+hipError_t launch_rows_front(const batch_ref& br, const front_grid& g, int maxPx, int maxTw, const inline_head* ih,
+                             hipStream_t st) {
+  prof_begin(PH_ROW_FWD, st);
+  inline_head h;
+  if (ih) h = *ih;
+  else h.ndesc_bytes = h.nstart_bytes = 0;
+  hipLaunchKernelGGL(k_rows_front<T>, dim3(g.rows + g.fold + g.twid), dim3(256),
+                     row_lds_bytes(maxPx, maxTw, (int)sizeof(T)), st, br, g, h);
+  prof_end(PH_ROW_FWD, st);
+  return hipGetLastError();
+}
+
+template hipError_t launch_rows_front<float>(const batch_ref&, const front_grid&, int, int, const inline_head*,
+                                             hipStream_t);
+template hipError_t launch_rows_front<double>(const batch_ref&, const front_grid&, int, int, const inline_head*,
+                                              hipStream_t);
 template hipError_t launch_row_fwd<float>(const batch_ref&, int, int, int, int, hipStream_t);
 template hipError_t launch_row_fwd<double>(const batch_ref&, int, int, int, int, hipStream_t);
 template hipError_t launch_col<float>(const batch_ref&, int, int, int, int, int, hipStream_t);

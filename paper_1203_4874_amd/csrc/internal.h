@@ -23,7 +23,7 @@ namespace cbp {
 // Work queues, one per kernel.
 enum queue_id {
   Q_DIAG = 0, Q_FOLD, Q_EVAL_COLS, Q_EVAL_ROWS, Q_ROW_FWD, Q_GRAM, Q_GRAMM, Q_SAMPLE, Q_FINALIZE, Q_COL,
-  Q_ROW_INV, Q_TWID, Q_KRDFT, Q_COUNT
+  Q_ROW_INV, Q_TWID, Q_KRDFT, Q_ROWS, Q_COUNT
 };
 
 // Frames per batched launch (the item prefix sums of one launch sit in LDS).
@@ -100,15 +100,18 @@ constexpr int VAR_DIVIDE_B1 = 1, VAR_SCALE_K1 = 2, VAR_ONE_AXIS = 4;
 constexpr int VAR_FP64_GRAM = 8;
 __host__ __device__ inline int solve_refine_max(int variant) { return (variant & VAR_FP64_GRAM) ? 0 : 4; }
 
+constexpr int FOLD_COLS = 256;   // columns of a column-fold item
+
 // Work items of each queue for one frame (the grid of a one-frame launch).
 inline int queue_items(int q, const frame_plan& p) {
   const int ncf = 2 * p.nch;
   switch (q) {
     case Q_DIAG: return 1;
-    case Q_FOLD: return ((p.Wmax + 63) / 64) * p.S * p.RG * ncf;
+    case Q_FOLD: return ((p.Wmax + FOLD_COLS - 1) / FOLD_COLS) * p.S * p.RG * ncf;
     case Q_EVAL_COLS: return ((p.Wmax + 15) / 16) * ncf;
     case Q_EVAL_ROWS: return ((p.Hmax + 1) / 2) * ncf;
     case Q_ROW_FWD: return p.nch * p.RG * p.S;   // (channel, row group, residue); rows y < Hmax of each
+    case Q_ROWS: return p.nch * p.Hmax;           // single rows (the split row pass)
     case Q_GRAM: return (2 * p.N - 1) * p.S * 2;
     case Q_GRAMM: return p.S * 2;
     case Q_SAMPLE: return p.S * 2;
@@ -230,6 +233,41 @@ __device__ inline void for_items(const batch_ref& br, F&& body) {
   for_items_part<Q>(br, (int)blockIdx.x, (int)gridDim.x, body);
 }
 
+// Run body(frame, item, lane) for the items of queue Q, one wave each, on
+// workgroup b of the G of 256 threads serving Q: four consecutive items per
+// workgroup and turn.  The body holds no barrier.
+template <int Q, typename F>
+__device__ inline void for_wave_items(const batch_ref& br, int b, int G, F&& body) {
+  __shared__ int st[BATCH_CHUNK + 1];
+  const int nf = br.nframes;
+  const int* s = br.starts + (size_t)Q * (nf + 1);
+  for (int t = threadIdx.x; t <= nf; t += blockDim.x) st[t] = s[t];
+  __syncthreads();
+  const int T = __builtin_amdgcn_readfirstlane(st[nf]);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int first, end, step;
+  xcd_items((T + 3) >> 2, b, G, first, end, step);
+  for (int u = first; u < end; u += step) {
+    const int it = 4 * u + wave;
+    if (it >= T) break;
+    int lo = 0, hi = nf;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (st[mid] <= it) lo = mid;
+      else hi = mid;
+    }
+    const int fi = __builtin_amdgcn_readfirstlane(lo);
+    const int base = __builtin_amdgcn_readfirstlane(st[fi]);
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const __attribute__((address_space(4))) frame_desc cdesc;
+    const frame_desc d = ((const cdesc*)br.descs)[fi];
+#else
+    const frame_desc d = br.descs[fi];
+#endif
+    body(d, it - base, (int)threadIdx.x & 63);
+  }
+}
+
 // w_t = exp(-2 pi i t / S), t < S, into tw (the workgroup's threads).
 __device__ inline void unit_twiddles(c64* tw, int S) {
   for (int t = threadIdx.x; t < S; t += blockDim.x) {
@@ -286,6 +324,93 @@ __device__ __attribute__((always_inline)) inline c64 dft_at(const double* f, int
   }
   return e;
 }
+
+// The (channel, frame) slot cf of a frame: its pixels, pitch and size.
+template <typename T>
+__device__ inline void pick_frame(const frame_desc& d, int cf, const T*& b, int64_t& pitch, int& H, int& W) {
+  const int ch = cf >> 1;
+  if ((cf & 1) == 0) { b = (const T*)d.b1 + ch * d.cs1; pitch = d.p1; H = d.H1; W = d.W1; }
+  else { b = (const T*)d.b2 + ch * d.cs2; pitch = d.p2; H = d.H2; W = d.W2; }
+}
+
+// Four consecutive elements from an address with the element's alignment only.
+template <typename T>
+struct quad {
+  T v[4];
+};
+template <typename T>
+__device__ inline quad<T> load_quad(const T* p) {
+  quad<T> q;
+  __builtin_memcpy(&q, p, sizeof q);
+  return q;
+}
+
+// One item of the column fold, one wave: the rows y = r mod S of row group g
+// of one (channel, frame), 256 columns (four per lane), summed in increasing y
+// in FP64, four rows' loads in flight.
+// Items: (column block, residue, row group, cf).
+template <typename T>
+__device__ inline void fold_item(const frame_desc& d, int item, int lane) {
+  const int S = d.S;
+  const int nx = (d.Wmax + FOLD_COLS - 1) / FOLD_COLS;
+  const int bx = item % nx;
+  int rest = item / nx;
+  const int r = rest % S;
+  rest /= S;
+  const int g = rest % d.RG, cf = rest / d.RG;
+  const T* b;
+  int64_t pitch;
+  int H, W;
+  pick_frame(d, cf, b, pitch, H, W);
+  const int x = bx * FOLD_COLS + 4 * lane;
+  const int y1 = min(g * d.rpg + d.rpg, H);
+  double* out = d.fpart + (((size_t)g * d.ncf + cf) * S + r) * (size_t)d.Wmax + x;
+  if (x + 4 <= W) {
+    const T* col = b + x;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int y = g * d.rpg + r;
+    for (; y + 3 * S < y1; y += 4 * S) {
+      quad<T> q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = load_quad(col + (int64_t)(y + u * S) * pitch);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += (double)q[u].v[c];
+    }
+    for (; y < y1; y += S) {
+      const quad<T> q = load_quad(col + (int64_t)y * pitch);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] += (double)q.v[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) out[c] = acc[c];
+  } else {
+    for (int c = 0; c < 4 && x + c < W; ++c) {
+      double acc = 0.0;
+      for (int y = g * d.rpg + r; y < y1; y += S) acc += (double)b[(int64_t)y * pitch + x + c];
+      out[c] = acc;
+    }
+  }
+}
+
+// 256 entries of the table exp(-2 pi i t / Px) (the kernels' row DFTs).
+__device__ inline void twiddle_item(const frame_desc& d, int item) {
+  for (int u = threadIdx.x; u < 256; u += blockDim.x) {
+    const int t = item * 256 + u;
+    if (t < d.Px) {
+      double s, c;
+      sincospi(-2.0 * (double)t / (double)d.Px, &s, &c);
+      d.twxd[t] = {c, s};
+    }
+  }
+}
+
+// The descriptors and prefix sums of a call's first launch: br itself, or the
+// inline head of its arguments, which workgroup 0 stores at br's place for the
+// later launches.  Workgroup 0 also zeroes the call's item counters.
+struct inline_head;
+__device__ inline batch_ref first_launch_head(const batch_ref& br_ws, const inline_head& ih);
 
 // One item of the column evaluation (Sec. 4 eq. 3: the S-point DFT of the
 // column fold): the row-group partials of 16 columns of one (channel, frame)
@@ -376,16 +501,41 @@ struct inline_head {
   alignas(16) char bytes[kInlineHeadMax];
 };
 
-// eval.hip.  launch_fold runs the column fold on `grid` workgroups and, on
-// twid_grid more, the twiddle tables of every frame (items of Q_TWID; the
-// FFT passes need them, the fold does not, so they share one launch).  With
-// ih, the launch carries the call's head (br then points at its place in the
-// workspace).
+#if defined(__HIPCC__)
+__device__ inline batch_ref first_launch_head(const batch_ref& br_ws, const inline_head& ih) {
+  batch_ref br = br_ws;
+  if (blockIdx.x == 0 && br_ws.ctr != nullptr)
+    for (int i = threadIdx.x; i < CTR_COUNT; i += blockDim.x) br_ws.ctr[i] = 0;
+  if (ih.ndesc_bytes > 0) {
+    br.descs = (const frame_desc*)ih.bytes;
+    br.starts = (const int*)(ih.bytes + ih.ndesc_bytes);
+    if (blockIdx.x == 0) {
+      const uint4* src = (const uint4*)ih.bytes;
+      uint4* dd = (uint4*)br_ws.descs;
+      uint4* ds = (uint4*)br_ws.starts;
+      const int nd = ih.ndesc_bytes / 16, ns = ih.nstart_bytes / 16;
+      for (int i = threadIdx.x; i < nd; i += blockDim.x) dd[i] = src[i];
+      for (int i = threadIdx.x; i < ns; i += blockDim.x) ds[i] = src[nd + i];
+    }
+  }
+  return br;
+}
+#endif
+
+// Grids of a call's first launch: workgroups of the column fold (four items
+// each), of the row evaluation, of the kernels' row twiddles and of the split
+// row pass.
+struct front_grid {
+  int rows, fold, eval, twid;
+};
+
+// eval.hip.  A call's first launch when it runs no row FFT: the column fold and
+// the row evaluation of a kernel-only call, or (a deblurring call whose row
+// pass folds) the twiddle tables alone.  With ih, the launch carries the call's
+// head (br then points at its place in the workspace).
 template <typename T>
-hipError_t launch_fold(const batch_ref& br, int grid, int twid_grid, const inline_head* ih, hipStream_t st);
+hipError_t launch_front(const batch_ref& br, const front_grid& g, const inline_head* ih, hipStream_t st);
 hipError_t launch_eval_cols(const batch_ref& br, int grid, hipStream_t st);
-template <typename T>
-hipError_t launch_eval_rows(const batch_ref& br, int grid, hipStream_t st);
 
 // recover.hip
 hipError_t launch_diag_init(const batch_ref& br, int grid, hipStream_t st);
@@ -418,6 +568,12 @@ void set_gram_mfma_attrs();
 // (the k_eval_rows result, bit for bit) from the rows it already holds.
 template <typename T>
 hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, int with_ey, hipStream_t st);
+// The first launch of a deblurring call with the split row pass: every row of
+// both frames transformed and evaluated by a workgroup of its own, the column
+// fold and the twiddle tables beside them.
+template <typename T>
+hipError_t launch_rows_front(const batch_ref& br, const front_grid& g, int maxPx, int maxTw, const inline_head* ih,
+                             hipStream_t st);
 template <typename T>
 // gmask: the filter groups g (bit g) of the batch's frames; one launch per
 // group, each taking the items of its frames
