@@ -22,8 +22,10 @@
 namespace cbp {
 
 // ---------------------------------------------------------------- complex
+// (8-byte alignment: a float pair is then one 64-bit access, two neighbours
+// one read2 of LDS)
 template <typename T>
-struct cplx {
+struct alignas(8) cplx {
   T re, im;
 };
 

@@ -35,6 +35,15 @@ namespace {
 // buffer instead of a ping-pong pair).  Twiddles come from the plan's pass
 // tables in LDS (fft_core.h tw_pitch), FP64 sincospi rounded once to T (one
 // read per twiddle).
+//
+// What bounds them is vector instructions (55 to 70% of the issue slots) and
+// the two barriers of a pass, not memory: a third to a half of the
+// instructions were addresses, and registers held for nothing (see any_value
+// and full_twiddles) kept workgroups off the CUs.  Strides as running adds,
+// range checks by the buffer unit, half spectra read once, tables gathered
+// from one: 8 x 1080p RGB FP32 columns 409 -> 377 us, forward rows 319 -> 255,
+// inverse rows 138 -> 104 (the rows with the pass order of kDefaultTuning);
+// 719x1277 FP64 columns 47 -> 29.8, single rows 27.6 -> 22.8.
 
 // threadIdx.x behind an empty asm statement: values derived from it are
 // recomputed where they are used instead of being hoisted out of the item
@@ -45,129 +54,219 @@ __device__ __attribute__((always_inline)) inline int local_tid() {
   return t;
 }
 
+// A raw buffer over `bytes` bytes at p (both wave-uniform).  The hardware checks
+// each access against its length: a load past the end returns zero, a store past
+// it is dropped.  The rows and strips are read and written through it, so a
+// lane's entry costs one 32-bit offset: no clamped 64-bit address, and no zero
+// put in for the entries beyond the frame.
+__device__ __attribute__((always_inline)) inline __amdgpu_buffer_rsrc_t raw_buffer(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+// An offset past the end of every buffer here (all below 2^27 bytes), also with
+// a strip's row offsets added.
+constexpr int kPastEnd = (int)0x80000000u;
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+template <typename V>
+__device__ __attribute__((always_inline)) inline V buf_load(__amdgpu_buffer_rsrc_t b, int off) {
+  static_assert(sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "one load");
+  if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(b, off, 0, 0));
+  else if constexpr (sizeof(V) == 8) return __builtin_bit_cast(V, (u32x2)__builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
+  else return __builtin_bit_cast(V, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
+}
+
+template <typename V>
+__device__ __attribute__((always_inline)) inline void buf_store(__amdgpu_buffer_rsrc_t b, int off, const V& v) {
+  static_assert(sizeof(V) == 4 || sizeof(V) == 8 || sizeof(V) == 16, "one store");
+  if constexpr (sizeof(V) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), b, off, 0, 0);
+  else if constexpr (sizeof(V) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, 0);
+}
+
+// Gives v a value on every path (any; empty asm, no instruction) where it is set
+// and read only under one condition.  Without it the compiler takes the paths
+// that do not set v to keep what the last loop turn left in it: registers held
+// across the loop, and copies.
+template <typename V>
+__device__ __attribute__((always_inline)) inline void any_value(V& v) {
+  asm volatile("" : "=v"(v));
+}
+template <typename T>
+__device__ __attribute__((always_inline)) inline void any_value(cplx<T>& v) {
+  any_value(v.re);
+  any_value(v.im);
+}
+
 // Butterflies per thread of a radix-R pass over at most MAXE entries.
 template <int NT, int R, int MAXE>
 constexpr int ip_mb() { return (MAXE / R + NT - 1) / NT; }
 
-// w_N^t, t < N, into tw when the table holds another length (tabN: the
-// length it holds, wave-uniform); the caller synchronises before use.
+// w_N^t, t < N, into tw by the workgroup's nt threads: FP64 sincospi rounded
+// once to T, the second half from the first's conjugates.  Most of a
+// workgroup's start is this function (some 60 FP64 instructions a value), so
+// the other tables are gathered from it.  A call: inlined, sincospi's
+// constants would be kept in some forty registers across the item loops.
 template <typename T>
-__device__ __attribute__((always_inline)) inline void full_twiddles(cplx<T>* tw, int N, int& tabN) {
-  if (tabN == N) return;
-  for (int t = threadIdx.x; t < N; t += blockDim.x) {
+__device__ __attribute__((noinline)) void full_twiddles(__attribute__((address_space(3))) cplx<T>* tw, int N, int nt) {
+  for (int t = threadIdx.x; 2 * t <= N; t += nt) {
     double sn, cs;
     sincospi(-2.0 * (double)t / (double)N, &sn, &cs);
-    tw[t] = {T(cs), T(sn)};
+    tw[t].re = T(cs);
+    tw[t].im = T(sn);
+    if (t > 0) {
+      tw[N - t].re = T(cs);
+      tw[N - t].im = T(-sn);
+    }
   }
-  tabN = N;
 }
 
-// The pass twiddle tables of plan p into tws when they hold another plan's
-// (tabN, tabCode: the length and pass order they hold, wave-uniform); the
-// caller synchronises before use.  Entry k P + r - 1 of the pass with stride
-// Ns is w_(Ns R)^(r k): the angle r k / (Ns R) equals r k (N / (Ns R)) / N
-// exactly in FP64, so the values are those of the full table w_N^t.
+// unit_twiddles as a call, for the same reason.
+__device__ __attribute__((noinline)) void row_unit_twiddles(__attribute__((address_space(3))) c64* tw, int S) {
+  unit_twiddles((c64*)tw, S);
+}
+
+// The pass twiddle tables of plan p into tws from its full table tw.  Entry
+// k P + r - 1 of the pass with stride Ns is w_(Ns R)^(r k) = w_N^(r k N / (Ns R)).
 template <typename T>
-__device__ __attribute__((always_inline)) inline void pass_twiddles(cplx<T>* tws, const fft_plan& p, int& tabN,
-                                                                    unsigned long long& tabCode) {
-  if (tabN == p.N && tabCode == p.code) return;
-  int Ns = 1, off = 0;
-  for (int s = 0; s < p.npass; ++s) {
-    const int R = plan_radix(p, s);
-    if (Ns > 1) {
-      const int P = tw_pitch(R), n = Ns * P;
-      for (int e = threadIdx.x; e < n; e += blockDim.x) {
-        const int k = e / P, r = e - k * P + 1;
-        double sn = 0.0, cs = 1.0;
-        if (r < R) sincospi(-2.0 * (double)(r * k) / (double)(Ns * R), &sn, &cs);
-        tws[off + e] = {T(cs), T(sn)};
-      }
-      off += n;
+__device__ __attribute__((always_inline)) inline void pass_twiddles(cplx<T>* tws, const cplx<T>* tw, const fft_plan& p,
+                                                                    int nt) {
+  int Ns = plan_radix(p, 0), off = 0;
+  for (int s = 1; s < p.npass; ++s) {
+    const int R = plan_radix(p, s), P = tw_pitch(R), n = Ns * P, step = p.N / (Ns * R);
+    const float rp = __builtin_amdgcn_rcpf((float)P);
+    for (int e = threadIdx.x; e < n; e += nt) {
+      const int k = fdiv_floor(e, rp), r = e - mul24(k, P) + 1;
+      tws[off + e] = tw[r < R ? mul24(mul24(r, k), step) : 0];
     }
+    off += n;
     Ns *= R;
   }
+}
+
+// Both tables of a row pass's plan when tws holds another plan's (tabN,
+// tabCode: the length and pass order it holds, wave-uniform); a, the row's
+// buffer, holds the full table meanwhile.  Ends with a barrier when it wrote.
+template <typename T>
+__device__ __attribute__((always_inline)) inline void row_twiddles(cplx<T>* a, cplx<T>* tws, const fft_plan& p, int& tabN,
+                                                                   unsigned long long& tabCode) {
+  if (tabN == p.N && tabCode == p.code) return;
+  full_twiddles<T>((__attribute__((address_space(3))) cplx<T>*)a, p.N, 256);
+  __syncthreads();
+  pass_twiddles(tws, a, p, 256);
+  __syncthreads();
   tabN = p.N;
   tabCode = p.code;
 }
 
-// One radix-R pass (stride Ns) over ncol transforms of length N at
+// One radix-R pass (stride Ns) over 2^lnc transforms of length N at
 // buf + c ld, in place: butterfly j of transform c reads
 // buf[c ld + j + r N/R] and writes buf[c ld + (j - k) R + k + r Ns],
 // k = j mod Ns (the Stockham indexing of fft_core.h, read and write phases
-// separated by a barrier); tws: the pass's twiddle table.  ncol (a power of
-// two) N <= MAXE.  Butterfly b of the pass is (c, j) = (b mod ncol,
-// b / ncol): consecutive lanes take the same j of consecutive transforms,
-// whose entries the strip's column stride puts in distinct banks.
-template <int R, int DIR, int NT, int MAXE, typename T>
+// separated by a barrier); tws: the pass's twiddle table.  2^lnc N <= MAXE.
+// Butterfly b of the pass is (c, j) = (b mod 2^lnc, b >> lnc): consecutive
+// lanes take the same j of consecutive transforms, whose entries the strip's
+// column stride puts in distinct banks, and a thread's butterflies are all of
+// one transform.  Strides are wave-uniform, so an entry's address is one add.
+// TW: Ns > 1 (the first pass has no twiddles).
+template <int R, int DIR, int NT, int MAXE, bool TW, typename T>
 __device__ __attribute__((always_inline)) inline void ip_pass(cplx<T>* buf, int ld, int N, int Ns,
-                                                              const cplx<T>* tws, int ncol) {
+                                                              const cplx<T>* tws, int lnc) {
   constexpr int MB = ip_mb<NT, R, MAXE>();
   const int NR = N / R;
-  const int total = NR * ncol;
-  const int lnc = __builtin_ctz(ncol);
-  const float rns = 1.0f / (float)Ns;
+  // within one unit in the last place of 1 / Ns, as fdiv_floor allows at these sizes
+  const float rns = __builtin_amdgcn_rcpf((float)Ns);
   cplx<T> v[MB][R];
   int pos[MB];
-  const int tid = local_tid();
 #pragma unroll
   for (int q = 0; q < MB; ++q) {
-    const int b = tid + q * NT;
-    pos[q] = -1;
-    if (b < total) {
-      const int c = b & (ncol - 1), j = b >> lnc;
-      const int k = Ns > 1 ? j - mul24(fdiv_floor(j, rns), Ns) : 0;
-      const cplx<T>* src = buf + mul24(c, ld);
-      const int base = Ns > 1 ? stockham_read<R, DIR, true>(src, NR, tws, j, k, v[q])
-                              : stockham_read<R, DIR, false>(src, NR, tws, j, k, v[q]);
-      pos[q] = mul24(c, ld) + base;
+    any_value(pos[q]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) any_value(v[q][r]);
+  }
+  const int tid = local_tid();
+  cplx<T>* col = buf + mul24(tid & ((1 << lnc) - 1), ld);
+  const int j0 = tid >> lnc, js = NT >> lnc;
+#pragma unroll
+  for (int q = 0; q < MB; ++q) {
+    const int j = j0 + q * js;
+    if (j < NR) {
+      const int k = TW ? j - mul24(fdiv_floor(j, rns), Ns) : 0;
+      pos[q] = stockham_read<R, DIR, TW>(col, NR, tws, j, k, v[q]);
     }
   }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < MB; ++q)
-    if (pos[q] >= 0) {
+    if (j0 + q * js < NR) {
+      cplx<T>* o = col + pos[q];
 #pragma unroll
-      for (int r = 0; r < R; ++r) buf[pos[q] + mul24(r, Ns)] = v[q][r];
+      for (int r = 0; r < R; ++r, o += Ns) *o = v[q][r];
     }
   __syncthreads();
 }
 
-// All passes of plan p over ncol transforms (ncol p.N <= MAXE), in place;
-// tws: the plan's pass tables (pass_twiddles).  R9: the plan may hold
-// radix-9 passes (the row plans; the column plans do not, which keeps the
-// column pass's registers at the radix-8 pass).
+// The pass of radix R.  R9: the plan may hold radix-9 passes (the row plans;
+// the column plans do not, which keeps the column pass's registers at the
+// radix-8 pass).
+template <int DIR, int NT, int MAXE, bool R9, bool TW, typename T>
+__device__ __attribute__((always_inline)) inline void ip_radix(int R, cplx<T>* buf, int ld, int N, int Ns,
+                                                               const cplx<T>* tws, int lnc) {
+  if constexpr (R9) {
+    if (R == 9) {
+      ip_pass<9, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc);
+      return;
+    }
+  }
+  switch (R) {
+    case 2: ip_pass<2, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 3: ip_pass<3, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 4: ip_pass<4, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 5: ip_pass<5, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 7: ip_pass<7, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    default: ip_pass<8, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+  }
+}
+
+// All passes of plan p over 2^lnc transforms (2^lnc p.N <= MAXE), in place;
+// tws: the plan's pass tables (pass_twiddles).
 template <int DIR, int NT, int MAXE, bool R9 = false, typename T>
 __device__ __attribute__((always_inline)) inline void ip_fft(cplx<T>* buf, int ld, const fft_plan& p,
-                                                             const cplx<T>* tws, int ncol) {
-  int Ns = 1;
-  const cplx<T>* t = tws;   // this pass's table (the first pass, Ns = 1, has none)
-  for (int s = 0; s < p.npass; ++s) {
+                                                             const cplx<T>* tws, int lnc) {
+  if (p.npass == 0) return;   // N = 1
+  int Ns = plan_radix(p, 0);
+  ip_radix<DIR, NT, MAXE, R9, false>(Ns, buf, ld, p.N, 1, tws, lnc);
+  const cplx<T>* t = tws;   // this pass's table
+  for (int s = 1; s < p.npass; ++s) {
     const int R = plan_radix(p, s);
-    if constexpr (R9) {
-      if (R == 9) {
-        ip_pass<9, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol);
-        if (Ns > 1) t += Ns * tw_pitch(9);
-        Ns *= 9;
-        continue;
-      }
-    }
-    switch (R) {
-      case 2: ip_pass<2, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-      case 3: ip_pass<3, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-      case 4: ip_pass<4, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-      case 5: ip_pass<5, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-      case 7: ip_pass<7, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-      default: ip_pass<8, DIR, NT, MAXE>(buf, ld, p.N, Ns, t, ncol); break;
-    }
-    if (Ns > 1) t += Ns * tw_pitch(R);
+    ip_radix<DIR, NT, MAXE, R9, true>(R, buf, ld, p.N, Ns, t, lnc);
+    t += Ns * tw_pitch(R);
     Ns *= R;
   }
 }
 
 // Largest row length (entries) of the row passes.
 constexpr int ROW_MAXE = CBP_MAX_FFT_F32 > CBP_MAX_FFT_F64 ? CBP_MAX_FFT_F32 : CBP_MAX_FFT_F64;
+constexpr int ROW_HALF = (ROW_MAXE / 2 + 1 + 255) / 256;   // half-spectrum entries per thread of the row passes
 
 // ---------------------------------------------------------------- pass 1
+// Rows y of both frames of channel ch into registers, entries t 256 + tid:
+// zero beyond each frame's width and in rows past its height.
+template <typename T>
+__device__ __attribute__((always_inline)) inline void fetch_rows(const frame_desc& d, int ch, int y, T (&u)[8], T (&w)[8]) {
+  const auto r1 = raw_buffer((const T*)d.b1 + ch * d.cs1 + (int64_t)min(y, d.H1 - 1) * d.p1,
+                             y < d.H1 ? d.W1 * (int)sizeof(T) : 0);
+  const auto r2 = raw_buffer((const T*)d.b2 + ch * d.cs2 + (int64_t)min(y, d.H2 - 1) * d.p2,
+                             y < d.H2 ? d.W2 * (int)sizeof(T) : 0);
+  const int off = local_tid() * (int)sizeof(T);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    u[t] = buf_load<T>(r1, off + t * 256 * (int)sizeof(T));
+    w[t] = buf_load<T>(r2, off + t * 256 * (int)sizeof(T));
+  }
+}
+
 // Rows y of both frames of channel ch, packed as B1 + i B2 in a (LDS, zero
 // beyond each frame): with with_ey their unit-circle evaluation, then the FFT
 // and the two half spectra.  twf: the plan's pass tables, twS: w_S^t.  Ends
@@ -203,15 +302,17 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
     __syncthreads();
     if (l < S && inr) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[fr], 1, twS, S, l);
   }
-  ip_fft<-1, 256, ROW_MAXE, true>(a, N, px, twf, 1);
-  cplx<T>* o1 = (cplx<T>*)d.t1 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
-  cplx<T>* o2 = (cplx<T>*)d.t2 + (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
-  for (int k = threadIdx.x; k < hx; k += blockDim.x) {
+  ip_fft<-1, 256, ROW_MAXE, true>(a, N, px, twf, 0);
+  const int64_t to = (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
+  const int row = hx * (int)sizeof(cplx<T>);
+  const auto o1 = raw_buffer((cplx<T>*)d.t1 + to, in1 ? row : 0), o2 = raw_buffer((cplx<T>*)d.t2 + to, in2 ? row : 0);
+  for (int k = threadIdx.x; k < hx; k += 256) {
     const cplx<T> zk = a[k];
     const cplx<T> zn = conj(a[k == 0 ? 0 : N - k]);
     const cplx<T> s = zk + zn, df = zk - zn;
-    if (in1) o1[k] = {T(0.5) * s.re, T(0.5) * s.im};       // (Z_k + conj Z_{N-k}) / 2
-    if (in2) o2[k] = {T(0.5) * df.im, T(-0.5) * df.re};    // (Z_k - conj Z_{N-k}) / (2i)
+    const int off = k * (int)sizeof(cplx<T>);
+    buf_store(o1, off, cplx<T>{T(0.5) * s.re, T(0.5) * s.im});       // (Z_k + conj Z_{N-k}) / 2
+    buf_store(o2, off, cplx<T>{T(0.5) * df.im, T(-0.5) * df.re});    // (Z_k - conj Z_{N-k}) / (2i)
   }
   __syncthreads();
 }
@@ -230,7 +331,7 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
 static_assert(CBP_MAX_FFT_F32 <= 8 * 256 && CBP_MAX_FFT_F64 <= 8 * 256, "one row is eight loads per thread");
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_ref br, int with_ey) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
   __shared__ double gy[2][CBP_MAX_S];
   __shared__ double fpart_l[2][128];
@@ -276,21 +377,9 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
     q.nv = q.y0 >= d.Hmax ? 0 : min(gi, (d.Hmax - 1 - q.y0) / S + 1);
     return q;
   };
-  // the two rows y of channel ch into registers: eight loads per frame and
-  // thread, from clamped (always valid) addresses; entries outside the frame
-  // are zeroed when they are used
+  // the two rows y of channel ch into registers (fetch_rows)
   T uv[8], wv[8];
-  auto fetch = [&](const frame_desc& d, int ch, int y) __attribute__((always_inline)) {
-    // row pointers clamped to each frame's last row (rows past it read as zero)
-    const T* r1 = (const T*)d.b1 + ch * d.cs1 + (int64_t)min(y, d.H1 - 1) * d.p1;
-    const T* r2 = (const T*)d.b2 + ch * d.cs2 + (int64_t)min(y, d.H2 - 1) * d.p2;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int x = t * 256 + local_tid();
-      uv[t] = r1[min(x, d.W1 - 1)];
-      wv[t] = r2[min(x, d.W2 - 1)];
-    }
-  };
+  auto fetch = [&](const frame_desc& d, int ch, int y) __attribute__((always_inline)) { fetch_rows<T>(d, ch, y, uv, wv); };
   // the first row of the first item at or after it that has rows (it >= end: none)
   auto fetch_from = [&](int it) __attribute__((always_inline)) {
     for (; it < end; it += step) {
@@ -316,28 +405,25 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
     cplx<T>* a = (cplx<T>*)sm_rf;
     cplx<T>* twf = a + N;
     const int ch = q.ch;
-    const int W1 = d.W1, W2 = d.W2;
     // the column fold of this item's rows, both frames (FP64, increasing y)
     double f1[8], f2[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) f1[t] = f2[t] = 0.0;
     for (int i = 0; i < q.nv; ++i) {
       const int y = q.y0 + S * i;
-      const bool in1 = y < d.H1, in2 = y < d.H2;
-      pass_twiddles(twf, px, tabN, tabCode);
+      row_twiddles(a, twf, px, tabN, tabCode);
       if (with_ey && S != tabS) {
         // w_t for the row evaluation (made again only when S changes; the
         // barrier after the row's store orders it before its use)
-        unit_twiddles(twS, S);
+        row_unit_twiddles((__attribute__((address_space(3))) c64*)twS, S);
         tabS = S;
       }
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const int x = t * 256 + local_tid();
-        const T u1 = (in1 && x < W1) ? uv[t] : T(0), u2 = (in2 && x < W2) ? wv[t] : T(0);
-        f1[t] += (double)u1;
-        f2[t] += (double)u2;
-        if (x < N) a[x] = {u1, u2};
+        f1[t] += (double)uv[t];
+        f2[t] += (double)wv[t];
+        if (x < N) a[x] = {uv[t], wv[t]};
       }
       __syncthreads();
       // the next row is in flight while this one is transformed
@@ -346,13 +432,13 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
       row_transform<T>(d, ch, y, with_ey, a, twf, gy, fpart_l, twS);
     }
     // the group's column-fold partials (fold_item's layout), for x < W
-    double* fp1 = d.fpart + (((size_t)q.g * d.ncf + 2 * ch) * S + q.r) * (size_t)d.Wmax;
-    double* fp2 = d.fpart + (((size_t)q.g * d.ncf + 2 * ch + 1) * S + q.r) * (size_t)d.Wmax;
+    const auto fp1 = raw_buffer(d.fpart + (((size_t)q.g * d.ncf + 2 * ch) * S + q.r) * (size_t)d.Wmax, d.W1 * 8);
+    const auto fp2 = raw_buffer(d.fpart + (((size_t)q.g * d.ncf + 2 * ch + 1) * S + q.r) * (size_t)d.Wmax, d.W2 * 8);
+    const int off = local_tid() * 8;
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const int x = t * 256 + local_tid();
-      if (x < W1) fp1[x] = f1[t];
-      if (x < W2) fp2[x] = f2[t];
+      buf_store(fp1, off + t * 2048, f1[t]);
+      buf_store(fp2, off + t * 2048, f2[t]);
     }
   }
 }
@@ -362,7 +448,7 @@ __global__ __launch_bounds__(256) void k_row_fwd(batch_ref br, int with_ey) {
 // columns from the frames themselves (k_front's fold, the same bits), g.twid
 // fill the twiddle tables.  A row is a workgroup of its own instead of a
 // turn of one residue's: 480x640 (168 items of three rows) 22.7 us and 4.7 for
-// the launch before it -> 13.6; 64x64 FP64 38.8 and 4.5 -> 8.4.
+// the launch before it -> 13.6 (12.5 since); 64x64 FP64 38.8 and 4.5 -> 8.4.
 template <typename T>
 __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid g, inline_head ih) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
@@ -386,22 +472,15 @@ __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid 
     const int N = d.fx.N, ch = item / d.Hmax, y = item - ch * d.Hmax;
     cplx<T>* a = (cplx<T>*)sm_rf;
     cplx<T>* twf = a + N;
-    const T* r1 = (const T*)d.b1 + ch * d.cs1 + (int64_t)min(y, d.H1 - 1) * d.p1;
-    const T* r2 = (const T*)d.b2 + ch * d.cs2 + (int64_t)min(y, d.H2 - 1) * d.p2;
     T uv[8], wv[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int x = t * 256 + local_tid();
-      uv[t] = r1[min(x, d.W1 - 1)];
-      wv[t] = r2[min(x, d.W2 - 1)];
-    }
-    pass_twiddles(twf, d.fx, tabN, tabCode);
-    if (d.S != tabS) unit_twiddles(twS, d.S);
+    fetch_rows<T>(d, ch, y, uv, wv);
+    row_twiddles(a, twf, d.fx, tabN, tabCode);
+    if (d.S != tabS) row_unit_twiddles((__attribute__((address_space(3))) c64*)twS, d.S);
     tabS = d.S;
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int x = t * 256 + local_tid();
-      if (x < N) a[x] = {(y < d.H1 && x < d.W1) ? uv[t] : T(0), (y < d.H2 && x < d.W2) ? wv[t] : T(0)};
+      if (x < N) a[x] = {uv[t], wv[t]};
     }
     __syncthreads();
     row_transform<T>(d, ch, y, 1, a, twf, gy, fpart_l, twS);
@@ -490,10 +569,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     return br.descs[fi];
 #endif
   };
-  // strip entries e = y cw + c (cw consecutive threads read one row
-  // segment) of frame fr of item it into registers, from clamped (always
-  // valid) addresses; rows past the frame and columns past hx are zeroed when
-  // they are stored to LDS
+  // frame fr's strip of item it into registers: column c = tid mod cw (cw
+  // consecutive threads read one row segment), rows tid / cw + i NT / cw;
+  // zero in rows past the frame and columns past hx
   cplx<T> pre[PF];
   auto fetch = [&](int it, int fr) __attribute__((always_inline)) {
     const int fi = frame_of(it);
@@ -502,15 +580,14 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     const int cw = d.cw, hx = d.hx, tp = d.hxp, lcw = __builtin_ctz(cw);
     const int nstrip = (hx + cw - 1) / cw;
     const int kx0 = (item % nstrip) * cw, ch = item / nstrip;
-    const int Hf = fr ? d.H2 : d.H1;
-    const cplx<T>* src = (const cplx<T>*)(fr ? d.t2 : d.t1) + ch * (int64_t)d.Hmax * tp;
+    const auto src = raw_buffer((const cplx<T>*)(fr ? d.t2 : d.t1) + ch * (int64_t)d.Hmax * tp + kx0,
+                                ((fr ? d.H2 : d.H1) * tp - kx0) * (int)sizeof(cplx<T>));
     const int tid = local_tid();
+    const int c = tid & (cw - 1);
+    const int off = kx0 + c < hx ? (mul24(tid >> lcw, tp) + c) * (int)sizeof(cplx<T>) : kPastEnd;
+    const int step = (NT >> lcw) * tp * (int)sizeof(cplx<T>);
 #pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int e = tid + i * NT;
-      const int y = e >> lcw, c = e & (cw - 1);
-      pre[i] = src[(int64_t)min(y, Hf - 1) * tp + min(kx0 + c, hx - 1)];
-    }
+    for (int i = 0; i < PF; ++i) pre[i] = buf_load<cplx<T>>(src, off + i * step);
   };
   auto first_frame = [&](int it) __attribute__((always_inline)) {
     return (desc(frame_of(it)).variant & VAR_DIVIDE_B1) ? 0 : 1;   // frame 2 first when both are divided
@@ -540,8 +617,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
   __syncthreads();
   const int it0 = __builtin_amdgcn_readfirstlane(s_next[0]);
   if (it0 < end) fetch(it0, first_frame(it0));
-  int tabN = 0;                   // length of the full twiddle table in LDS
-  int tabNp = 0;                  // plan of the pass tables in LDS (length,
+  int tabN = 0;                     // plan of the tables in LDS (length,
   unsigned long long tabCode = 0;   // pass order)
   for (int it = it0, nit, par = 1; it < end; it = nit, par ^= 1) {
     // the item after this one, read by every thread after the next barrier
@@ -556,7 +632,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     const fft_plan& py = d.fy;
     const int N = py.N, cw = d.cw, hx = d.hx, tp = d.hxp, m = d.m;
     const int ld = col_ld<T>(N, cw);
-    const int k1 = d.k1, k2 = d.k2, H1 = d.H1, H2 = d.H2;
+    const int k1 = d.k1, k2 = d.k2;
     const T lam = (T)d.lambda;
     const bool two = !(d.variant & VAR_DIVIDE_B1);   // two-channel division, or B1 / K1 alone
     cplx<T>* buf = (cplx<T>*)sm_cf;                   // [cw][ld]
@@ -568,25 +644,26 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     const int nstrip = (hx + cw - 1) / cw;
     const int kx0 = (item % nstrip) * cw, ch = item / nstrip;
     const int lcw = __builtin_ctz(cw);                // cw is a power of two
-    const int tot = N << lcw;
     // the registers' strip into buf[c ld + y]
-    auto spill = [&](int Hf) __attribute__((always_inline)) {
+    auto spill = [&]() __attribute__((always_inline)) {
       const int tid = local_tid();
+      const int y = tid >> lcw, ys = NT >> lcw;
+      cplx<T>* at = buf + mul24(tid & (cw - 1), ld) + y;
 #pragma unroll
-      for (int i = 0; i < PF; ++i) {
-        const int e = tid + i * NT;
-        const int y = e >> lcw, c = e & (cw - 1);
-        if (e < tot) buf[mul24(c, ld) + y] = (y < Hf && kx0 + c < hx) ? pre[i] : cplx<T>{T(0), T(0)};
-      }
+      for (int i = 0; i < PF; ++i)
+        if (y + i * ys < N) at[i * ys] = pre[i];
     };
-    if (G > 1 && tabN != N)
-      for (int y = threadIdx.x; y < N / G; y += NT) {
-        double sn, cs;
-        sincospi(-2.0 * (double)(G * y) / (double)N, &sn, &cs);   // = w_N^t, t = G y, as full_twiddles
-        twg[y] = {T(cs), T(sn)};
-      }
-    full_twiddles(tw, N, tabN);
-    pass_twiddles(twp, py, tabNp, tabCode);
+    // the tables, when those in LDS are another plan's (the last item's reads
+    // of them are behind its closing barrier)
+    if (tabN != N || tabCode != py.code) {
+      full_twiddles<T>((__attribute__((address_space(3))) cplx<T>*)tw, N, NT);
+      __syncthreads();
+      if (G > 1)
+        for (int y = threadIdx.x; y < N / G; y += NT) twg[y] = tw[G * y];
+      pass_twiddles(twp, tw, py, NT);
+      tabN = N;
+      tabCode = py.code;
+    }
     // the kernels' row DFTs at this strip's columns (k_kernel_dft), zero past hx
     {
       const cplx<T>* krg = (const cplx<T>*)d.kr;
@@ -609,23 +686,22 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
       }
     };
     cplx<T> st2[SM];
+#pragma unroll
+    for (int j = 0; j < SM; ++j) any_value(st2[j]);
     if (two) {
-      spill(H2);
+      spill();
       __syncthreads();
       fetch(it, 0);   // frame 1's strip in flight while frame 2's is transformed
-      ip_fft<-1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, cw);
+      ip_fft<-1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, lcw);
       for_held([&](auto GC, int a, int c, int y, int q) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < GC(); ++j) st2[a + j] = buf[mul24(c, ld) + y + j * q];
       });
       __syncthreads();   // buf is refilled with frame 1
     }
-    spill(H1);
+    spill();
     __syncthreads();
-    // the next item's first strip in flight while this one is finished
-    nit = __builtin_amdgcn_readfirstlane(s_next[par]);
-    if (nit < end) fetch(nit, first_frame(nit));
-    ip_fft<-1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, cw);
+    ip_fft<-1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, lcw);
     // filter: the combined spectrum in place of frame 1's
     const int kmax = k1 > k2 ? k1 : k2;
     auto filt = [&](cplx<T>* at, const cplx<T>& kh1, const cplx<T>& kh2, const cplx<T>& b2)
@@ -654,20 +730,21 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
       cplx<T> P1[g], P2[g];
 #pragma unroll
       for (int p = 0; p < g; ++p) {
-        const int top = g * (nt - 1) + p;
-        cplx<T> e1 = top < CBP_MAX_K ? kr1[top] : cplx<T>{T(0), T(0)};
-        cplx<T> e2 = top < CBP_MAX_K ? kr2[top] : cplx<T>{T(0), T(0)};
-        for (int t = nt - 2; t >= 0; --t) {
-          e1 = e1 * u + kr1[g * t + p];
-          e2 = e2 * u + kr2[g * t + p];
+        P1[p] = kr1[g * (nt - 1) + p];
+        P2[p] = kr2[g * (nt - 1) + p];
+      }
+      for (int t = nt - 2; t >= 0; --t) {
+#pragma unroll
+        for (int p = 0; p < g; ++p) {
+          P1[p] = P1[p] * u + kr1[g * t + p];
+          P2[p] = P2[p] * u + kr2[g * t + p];
         }
-        if (p > 0) {
-          const cplx<T> zp = tw[p * y];
-          e1 = zp * e1;
-          e2 = zp * e2;
-        }
-        P1[p] = e1;
-        P2[p] = e2;
+      }
+#pragma unroll
+      for (int p = 1; p < g; ++p) {
+        const cplx<T> zp = tw[p * y];
+        P1[p] = zp * P1[p];
+        P2[p] = zp * P2[p];
       }
       cplx<T>* col = buf + mul24(c, ld) + y;
       if constexpr (g == 1) {
@@ -687,13 +764,22 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
       }
     });
     __syncthreads();
-    ip_fft<+1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, cw);
+    // the next item's first strip in flight during the inverse transform (not
+    // earlier: its registers and the stashed spectrum's are never both held)
+    nit = __builtin_amdgcn_readfirstlane(s_next[par]);
+    if (nit < end) fetch(nit, first_frame(nit));
+    ip_fft<+1, NT, col_max_elems<T, NT>()>(buf, ld, py, twp, lcw);
     // the first m rows, row segments of cw columns
-    cplx<T>* uo = (cplx<T>*)d.u + (int64_t)ch * m * tp;
-    for (int e = threadIdx.x; e < (m << lcw); e += NT) {
-      const int y = e >> lcw, c = e & (cw - 1);
-      const int col = kx0 + c;
-      if (col < hx) uo[(int64_t)y * tp + col] = buf[mul24(c, ld) + y];
+    {
+      const auto uo = raw_buffer((cplx<T>*)d.u + ch * (int64_t)m * tp + kx0, (m * tp - kx0) * (int)sizeof(cplx<T>));
+      const int tid = local_tid();
+      const int c = tid & (cw - 1), y = tid >> lcw, ys = NT >> lcw;
+      const int off = kx0 + c < hx ? (mul24(y, tp) + c) * (int)sizeof(cplx<T>) : kPastEnd;
+      const int step = ys * tp * (int)sizeof(cplx<T>);
+      const cplx<T>* at = buf + mul24(c, ld) + y;
+#pragma unroll
+      for (int i = 0; i < PF; ++i)
+        if (y + i * ys < m) buf_store(uo, off + i * step, at[i * ys]);
     }
     __syncthreads();   // the next item refills buf, kr and tw
   }
@@ -777,25 +863,24 @@ __global__ __launch_bounds__(256) void k_row_inv(batch_ref br) {
     return br.descs[fi];
 #endif
   };
-  // the spectra of item it's two rows into registers: entry k < hx read
-  // directly, k >= hx as the conjugate of entry N - k (< hx); indices past N
-  // clamp to 0 and are discarded
-  cplx<T> Av[8], Bv[8];
+  // the half spectra of item it's two rows into registers, entries
+  // t 256 + tid < hx (the second row is zero past the last)
+  cplx<T> Av[ROW_HALF], Bv[ROW_HALF];
   auto fetch = [&](int it) __attribute__((always_inline)) {
     const int fi = frame_of(it);
     const frame_desc d = desc(fi);
     const int item = it - __builtin_amdgcn_readfirstlane(st[fi]);
-    const int N = d.fx.N, hx = d.hx, m = d.m;
+    const int m = d.m, row = d.hx * (int)sizeof(cplx<T>);
     const int npair = (m + 1) / 2;
     const int ya = 2 * (item % npair), ch = item / npair;
     const cplx<T>* ua = (const cplx<T>*)d.u + (int64_t)ch * m * d.hxp + (int64_t)ya * d.hxp;
-    const cplx<T>* ubv = ya + 1 < m ? ua + d.hxp : ua;
+    const bool hb = ya + 1 < m;
+    const auto ra = raw_buffer(ua, row), rb = raw_buffer(hb ? ua + d.hxp : ua, hb ? row : 0);
+    const int off = local_tid() * (int)sizeof(cplx<T>);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int k = t * 256 + (int)threadIdx.x;
-      const int kk = k < hx ? k : max(N - k, 0);
-      Av[t] = ua[kk];
-      Bv[t] = ubv[kk];
+    for (int t = 0; t < ROW_HALF; ++t) {
+      Av[t] = buf_load<cplx<T>>(ra, off + t * 256 * (int)sizeof(cplx<T>));
+      Bv[t] = buf_load<cplx<T>>(rb, off + t * 256 * (int)sizeof(cplx<T>));
     }
   };
   if (first < end) fetch(first);
@@ -810,30 +895,32 @@ __global__ __launch_bounds__(256) void k_row_inv(batch_ref br) {
     const T scale = (T)(1.0 / ((double)d.Py * (double)d.Px));
     cplx<T>* a = (cplx<T>*)sm_ri;
     cplx<T>* twf = a + N;
-    pass_twiddles(twf, px, tabN, tabCode);
+    row_twiddles(a, twf, px, tabN, tabCode);
     const int npair = (m + 1) / 2;
     const int ya = 2 * (item % npair), yb = ya + 1, ch = item / npair;
     const bool hb = yb < m;
+    // A + i B at k and, from the conjugates, at N - k
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int k = t * 256 + (int)threadIdx.x;
-      if (k < N) {
-        cplx<T> A = Av[t], B = hb ? Bv[t] : cplx<T>{T(0), T(0)};
-        if (k >= hx) { A = conj(A); B = conj(B); }
+    for (int t = 0; t < ROW_HALF; ++t) {
+      const int k = t * 256 + local_tid();
+      if (k < hx) {
+        cplx<T> A = Av[t], B = Bv[t];
         if ((k == 0) || (2 * k == N)) { A.im = T(0); B.im = T(0); }
-        a[k] = {A.re - B.im, A.im + B.re};   // A + i B
+        a[k] = {A.re - B.im, A.im + B.re};
+        if (k > 0) a[N - k] = {A.re + B.im, B.re - A.im};
       }
     }
     __syncthreads();
     // the next item's spectra are in flight while this one is transformed
     if (it + step < end) fetch(it + step);
-    ip_fft<+1, 256, ROW_MAXE, true>(a, N, px, twf, 1);
+    ip_fft<+1, 256, ROW_MAXE, true>(a, N, px, twf, 0);
     const cplx<T>* z = a;
     T* oa = (T*)d.out + ch * d.ocs + (int64_t)ya * d.opitch;
-    T* ob = oa + d.opitch;
-    for (int x = threadIdx.x; x < n; x += blockDim.x) {
-      oa[x] = z[x].re * scale;
-      if (hb) ob[x] = z[x].im * scale;
+    const auto ba = raw_buffer(oa, n * (int)sizeof(T)), bb = raw_buffer(hb ? oa + d.opitch : oa, hb ? n * (int)sizeof(T) : 0);
+    for (int x = threadIdx.x; x < n; x += 256) {
+      const int off = x * (int)sizeof(T);
+      buf_store(ba, off, z[x].re * scale);
+      buf_store(bb, off, z[x].im * scale);
     }
     __syncthreads();
   }

@@ -175,7 +175,7 @@ template <int R, int DIR, bool TW, typename T>
 CBP_HD int stockham_read(const cplx<T>* src, int NR, const cplx<T>* tws, int j, int k, cplx<T>* v) {
   const cplx<T>* s = src + j;
 #pragma unroll
-  for (int r = 0; r < R; ++r) v[r] = s[mul24(r, NR)];
+  for (int r = 0; r < R; ++r, s += NR) v[r] = *s;
   if (TW) {
     const cplx<T>* tk = tws + mul24(k, tw_pitch(R));
 #pragma unroll

@@ -1,0 +1,69 @@
+"""The latent at the edges of the FFT passes' ranges (the longest rows and
+columns, odd and short grids, strips and rows that end inside a workgroup),
+against a float64 division with the call's own kernels; frames with a pitch are
+read up to their width and latents written up to theirs."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def smooth7(n):
+    while True:
+        r = n
+        for p in (2, 3, 5, 7):
+            while r % p == 0:
+                r //= p
+        if r == 1:
+            return n
+        n += 1
+
+
+def blurred(m, n, k1, k2, seed):
+    r = np.random.default_rng(seed)
+    L = r.random((m, n))
+    out = []
+    for k in (k1, k2):
+        K = r.random((k, k)) + 0.1
+        K /= K.sum()
+        s = (m + k - 1, n + k - 1)
+        out.append(np.fft.irfft2(np.fft.rfft2(L, s) * np.fft.rfft2(K, s), s))
+    return out
+
+
+def division(b1, b2, K1, K2, m, n, lam):
+    s = (smooth7(max(b1.shape[0], b2.shape[0])), smooth7(max(b1.shape[1], b2.shape[1])))
+    B1, B2, F1, F2 = (np.fft.rfft2(np.asarray(x, float), s) for x in (b1, b2, K1, K2))
+    q = (F1.conj() * B1 + F2.conj() * B2) / (abs(F1) ** 2 + abs(F2) ** 2 + lam)
+    return np.fft.irfft2(q, s)[:m, :n]
+
+
+@pytest.mark.parametrize("single", [True, False])
+@pytest.mark.parametrize("m,n,k1,k2", [
+    (11, 2040, 9, 4),     # rows of 2048: one half-spectrum entry beyond four a thread
+    (2037, 9, 12, 5),     # columns of 2048
+    (725, 30, 11, 3),     # an odd column length, 735
+    (31, 723, 5, 7),      # an odd row length, 729
+    (3, 300, 2, 3), (300, 3, 3, 2), (6, 6, 2, 2), (257, 513, 15, 13),
+])
+def test_latent_at_edges(single, m, n, k1, k2):
+    torch = pytest.importorskip("torch")
+    import paper_1203_4874_amd as P
+    dtype = torch.float32 if single else torch.float64
+    lam = 0.1
+    frames = []
+    for b in blurred(m, n, k1, k2, 3):
+        big = torch.full((b.shape[0], b.shape[1] + 3), float("nan"), dtype=dtype, device="cuda")
+        big[:, :-3] = torch.as_tensor(b, dtype=dtype)
+        frames.append(big[:, :-3])
+    L, K1, K2 = P.deblur(*frames, m, n, lam=lam)
+    b1, b2 = (f.cpu().numpy() for f in frames)
+    ref = division(b1, b2, K1.cpu().numpy(), K2.cpu().numpy(), m, n, lam)
+    # a transform adds a few roundings a pass; the division amplifies those of
+    # the kernels' spectra (k-term sums, k <= 15, of terms that add up to c) by
+    # at most 1 / lam in the numerator and twice that in the denominator
+    c = max(1.0, float(K1.abs().sum()), float(K2.abs().sum()))
+    tol = (3 * 20 + 3 * 15 * c / lam) * 2.0 ** (-24 if single else -53)
+    rms = lambda x: np.sqrt((np.asarray(x, float) ** 2).mean())
+    assert rms(L.cpu().numpy() - ref) <= tol * rms(b1)
