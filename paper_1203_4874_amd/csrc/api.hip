@@ -135,7 +135,7 @@ int max_fft(int esize) { return esize == 4 ? CBP_MAX_FFT_F32 : CBP_MAX_FFT_F64; 
 // Launch-shape knobs of one batch class, chosen by the autotuner.
 struct tuning {
   int fold_rows;   // target rows per column-fold group (rounded up to a multiple of S; >= 32); 0: from the frame
-  int cw;          // columns per column-pass strip (0: widest that fits and keeps >= 256 strips, one per CU)
+  int cw;          // columns per column-pass strip (0: set_strip_widths)
   int wg_per_cu;   // persistent-grid cap of the streaming queues, workgroups per CU (0: one per item)
   int fft_order;   // radix pass order of the row and column FFTs
 };
@@ -168,18 +168,36 @@ bool col_fits(int Py, int cw, int twn, int esize) {
 }
 
 // Columns per column-pass strip: `want` (a power of two up to 16) if given,
-// else the widest strip of a workgroup of at most 512 threads (two or more per CU) that still
-// leaves at least 256 strips over the frame's channels; either way narrowed
-// until the strip fits.
-int choose_cw(int Py, int hx, int nch, int twn, int esize, int want) {
+// else the widest strip of a workgroup of at most 512 threads (two or more per
+// CU); either way narrowed until the strip fits.
+int widest_cw(int Py, int twn, int esize, int want) {
   int cw = want > 0 ? want : 8;
   if (cw > 16) cw = 16;
   while (cw & (cw - 1)) cw &= cw - 1;
-  while (cw > 1 && (!col_fits(Py, cw, twn, esize) ||
-                    (want <= 0 && (col_threads(Py, cw, esize) > 512 ||
-                                   (int64_t)((hx + cw - 1) / cw) * nch < 256))))
-    cw >>= 1;
+  while (cw > 1 && (!col_fits(Py, cw, twn, esize) || (want <= 0 && col_threads(Py, cw, esize) > 512))) cw >>= 1;
   return cw;
+}
+
+// The automatic strip widths of a call's frames: as wide as leaves kMinStrips
+// strips over all of them (a column's transform is the same in any strip, so
+// the width may depend on the batch).  A wide strip reads and writes whole
+// sectors of T and U rows where one column takes 8 bytes of each; fewer strips
+// than resident workgroups leave CUs idle.  Columns of a call, width from each
+// frame alone / from the call: 16 x 256x256 FP32 (1 column / 4) 76 / 24 us,
+// 16 x 720p (2 / 4) 181 / 167.  At 256 strips instead of 512 these are 26 and
+// 168, and 719x1277 FP64 (2 columns / 1) 29.2 against 26.6.
+constexpr int64_t kMinStrips = 512;
+void set_strip_widths(std::vector<frame_plan>& plans) {
+  // one width for all: the launch's workgroups are sized for its widest strip
+  // and its tallest column
+  int cw = 16;
+  for (const frame_plan& p : plans) cw = std::min(cw, p.cw);
+  for (; cw > 1; cw >>= 1) {
+    int64_t strips = 0;
+    for (const frame_plan& p : plans) strips += (int64_t)((p.hx + cw - 1) / cw) * p.nch;
+    if (strips >= kMinStrips) break;
+  }
+  for (frame_plan& p : plans) p.cw = cw;
 }
 
 bool valid_image(const cbp_image* im) {
@@ -267,7 +285,7 @@ cbp_status make_plan(const cbp_image* b1, const cbp_image* b2, int m, int n, con
   fp->hxp = pitch_of(fp->hx, esize);
   fp->twy = col_table_entries(fp->fy);
   fp->twx = pass_table_entries(fp->fx);
-  fp->cw = choose_cw(fp->Py, fp->hx, fp->nch, fp->twy, esize, tn.cw);
+  fp->cw = widest_cw(fp->Py, fp->twy, esize, tn.cw);
   const int gfmt = gram_format(o->precision);
   if (gfmt >= 0 && (fp->N > 32 || gram_mfma_lds_bytes(std::max(fp->Hmax, fp->Wmax), gfmt) > kLdsLimit - 2048))
     return CBP_E_UNSUPPORTED;
@@ -579,6 +597,7 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
   bb->latent = latent;
   bb->diag = o->diag != nullptr;
   if (nf == 0) return CBP_OK;
+  if (latent && tn.cw <= 0) set_strip_widths(bb->plans);
   const size_t head = head_bytes(nf);
   size_t need = head;
   for (const frame_plan& fp : bb->plans) need += fp.total;

@@ -67,3 +67,19 @@ def test_latent_at_edges(single, m, n, k1, k2):
     tol = (3 * 20 + 3 * 15 * c / lam) * 2.0 ** (-24 if single else -53)
     rms = lambda x: np.sqrt((np.asarray(x, float) ** 2).mean())
     assert rms(L.cpu().numpy() - ref) <= tol * rms(b1)
+
+
+@pytest.mark.parametrize("single", [True, False])
+def test_strip_width_of_a_mixed_batch(single):
+    """Columns from 10 to 2048 entries and few to many strips in one launch: each
+    frame gets the bits of its own call, whose strips have another width."""
+    torch = pytest.importorskip("torch")
+    import paper_1203_4874_amd as P
+    dtype = torch.float32 if single else torch.float64
+    frames = []
+    for s, (m, n) in enumerate([(2037, 20), (6, 700), (300, 301), (64, 64)] + 4 * [(257, 130)]):
+        frames.append([torch.as_tensor(b, dtype=dtype, device="cuda") for b in blurred(m, n, 5, 4, s)] + [m, n])
+    for part in (frames, frames[2:]):
+        Ls, K1s, K2s, _ = P.deblur_batch(part, lam=1e-2)
+        for f, L, K1, K2 in zip(part, Ls, K1s, K2s):
+            assert all(torch.equal(x, y) for x, y in zip((L, K1, K2), P.deblur(*f, lam=1e-2)))
