@@ -139,14 +139,15 @@ struct tuning {
   int wg_per_cu;   // persistent-grid cap of the streaming queues, workgroups per CU (0: one per item)
   int fft_order;   // radix pass order of the row and column FFTs
 };
-// Odd radices first: the first pass writes its outputs R entries apart, which
-// puts an odd R in distinct LDS banks and R = 8 in an eighth of them; and the
-// last pass, with the longest twiddle table, is then one of radix 8 or 4, whose
-// table is the shortest.  At 1080p (row length 1944) a forward row workgroup
-// drops to 36 KB of LDS, four to the CU instead of three; 8 x 1080p RGB FP32,
-// radix 8 first / odd first: forward rows 324 / 255 us, inverse rows 115 / 104,
-// columns 383 / 377; 16 x 720p 122 / 117, 47 / 43 and 180 / 181.
-constexpr tuning kDefaultTuning = {0, 0, 0, 2};
+// The cheapest plans (3) have odd radices first: the first pass writes its
+// outputs R entries apart, which puts an odd R in distinct LDS banks and R = 8
+// in an eighth of them; and the last pass, with the longest twiddle table, is
+// then an even one, whose table is shorter.  At 1080p (row length 1944) a
+// forward row workgroup drops to 36 KB of LDS, four to the CU instead of three;
+// 8 x 1080p RGB FP32, radix 8 first / odd first (2): forward rows 324 / 255 us,
+// inverse rows 115 / 104, columns 383 / 377.  The composite radices of 3 save
+// a pass of most lengths.
+constexpr tuning kDefaultTuning = {0, 0, 0, 3};
 // Row-pass items (one per (channel, fold group, residue)) a frame aims at
 // when fold_rows is 0: one frame alone still spreads over the chip, a large
 // frame keeps the fold's partial sums (one row per item) small.  The group
@@ -167,14 +168,13 @@ bool col_fits(int Py, int cw, int twn, int esize) {
   return col_lds_bytes(Py, cw, twn, esize) <= kLdsLimit - 4096 && (int64_t)cw * Py <= col_max_strip_elems(esize);
 }
 
-// Columns per column-pass strip: `want` (a power of two up to 16) if given,
-// else the widest strip of a workgroup of at most 512 threads (two or more per
-// CU); either way narrowed until the strip fits.
+// Columns per column-pass strip: `want` (a power of two) if given, at most 8 (a
+// wave per column of a workgroup of 512 threads, two or more per CU), narrowed
+// until the strip fits.
 int widest_cw(int Py, int twn, int esize, int want) {
-  int cw = want > 0 ? want : 8;
-  if (cw > 16) cw = 16;
+  int cw = want > 0 && want < 8 ? want : 8;
   while (cw & (cw - 1)) cw &= cw - 1;
-  while (cw > 1 && (!col_fits(Py, cw, twn, esize) || (want <= 0 && col_threads(Py, cw, esize) > 512))) cw >>= 1;
+  while (cw > 1 && !col_fits(Py, cw, twn, esize)) cw >>= 1;
   return cw;
 }
 
@@ -190,7 +190,7 @@ constexpr int64_t kMinStrips = 512;
 void set_strip_widths(std::vector<frame_plan>& plans) {
   // one width for all: the launch's workgroups are sized for its widest strip
   // and its tallest column
-  int cw = 16;
+  int cw = 8;
   for (const frame_plan& p : plans) cw = std::min(cw, p.cw);
   for (; cw > 1; cw >>= 1) {
     int64_t strips = 0;
@@ -279,7 +279,7 @@ cbp_status make_plan(const cbp_image* b1, const cbp_image* b2, int m, int n, con
     return CBP_OK;
   }
   if (fp->Py > max_fft(esize) || fp->Px > max_fft(esize)) return CBP_E_SHAPE;
-  if (!make_fft_plan(fp->Py, &fp->fy, tn.fft_order) || !make_fft_plan(fp->Px, &fp->fx, tn.fft_order, true))
+  if (!make_fft_plan(fp->Py, &fp->fy, tn.fft_order, true) || !make_fft_plan(fp->Px, &fp->fx, tn.fft_order, true))
     return CBP_E_SHAPE;
   fp->hx = fp->Px / 2 + 1;
   fp->hxp = pitch_of(fp->hx, esize);
@@ -844,7 +844,7 @@ tuning autotune(dev_state& ds, const std::vector<frame_req>& reqs, const cbp_opt
   for (int order = 0; order < FFT_ORDERS; ++order)
     if (order != kDefaultTuning.fft_order) { tuning t = best; t.fft_order = order; consider(t); }
   for (int rows : {32, 64, 128, 256}) { tuning t = best; t.fold_rows = rows; consider(t); }
-  for (int cw : {1, 2, 4, 8, 16}) { tuning t = best; t.cw = cw; consider(t); }
+  for (int cw : {1, 2, 4, 8}) { tuning t = best; t.cw = cw; consider(t); }
   for (int wpc : {2, 4, 8, 16}) { tuning t = best; t.wg_per_cu = wpc; consider(t); }
   *best_ms = bms;
   return best;

@@ -207,40 +207,38 @@ __device__ __attribute__((always_inline)) inline void ip_pass(cplx<T>* buf, int 
   __syncthreads();
 }
 
-// The pass of radix R.  R9: the plan may hold radix-9 passes (the row plans;
-// the column plans do not, which keeps the column pass's registers at the
-// radix-8 pass).
-template <int DIR, int NT, int MAXE, bool R9, bool TW, typename T>
+// The pass of radix R.
+template <int DIR, int NT, int MAXE, bool TW, typename T>
 __device__ __attribute__((always_inline)) inline void ip_radix(int R, cplx<T>* buf, int ld, int N, int Ns,
                                                                const cplx<T>* tws, int lnc) {
-  if constexpr (R9) {
-    if (R == 9) {
-      ip_pass<9, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc);
-      return;
-    }
-  }
   switch (R) {
     case 2: ip_pass<2, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
     case 3: ip_pass<3, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
     case 4: ip_pass<4, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
     case 5: ip_pass<5, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 6: ip_pass<6, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
     case 7: ip_pass<7, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 9: ip_pass<9, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 10: ip_pass<10, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 12: ip_pass<12, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 14: ip_pass<14, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
+    case 15: ip_pass<15, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
     default: ip_pass<8, DIR, NT, MAXE, TW>(buf, ld, N, Ns, tws, lnc); break;
   }
 }
 
 // All passes of plan p over 2^lnc transforms (2^lnc p.N <= MAXE), in place;
 // tws: the plan's pass tables (pass_twiddles).
-template <int DIR, int NT, int MAXE, bool R9 = false, typename T>
+template <int DIR, int NT, int MAXE, typename T>
 __device__ __attribute__((always_inline)) inline void ip_fft(cplx<T>* buf, int ld, const fft_plan& p,
                                                              const cplx<T>* tws, int lnc) {
   if (p.npass == 0) return;   // N = 1
   int Ns = plan_radix(p, 0);
-  ip_radix<DIR, NT, MAXE, R9, false>(Ns, buf, ld, p.N, 1, tws, lnc);
+  ip_radix<DIR, NT, MAXE, false>(Ns, buf, ld, p.N, 1, tws, lnc);
   const cplx<T>* t = tws;   // this pass's table
   for (int s = 1; s < p.npass; ++s) {
     const int R = plan_radix(p, s);
-    ip_radix<DIR, NT, MAXE, R9, true>(R, buf, ld, p.N, Ns, t, lnc);
+    ip_radix<DIR, NT, MAXE, true>(R, buf, ld, p.N, Ns, t, lnc);
     t += Ns * tw_pitch(R);
     Ns *= R;
   }
@@ -302,7 +300,7 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
     __syncthreads();
     if (l < S && inr) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[fr], 1, twS, S, l);
   }
-  ip_fft<-1, 256, ROW_MAXE, true>(a, N, px, twf, 0);
+  ip_fft<-1, 256, ROW_MAXE>(a, N, px, twf, 0);
   const int64_t to = (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
   const int row = hx * (int)sizeof(cplx<T>);
   const auto o1 = raw_buffer((cplx<T>*)d.t1 + to, in1 ? row : 0), o2 = raw_buffer((cplx<T>*)d.t2 + to, in2 ? row : 0);
@@ -488,11 +486,11 @@ __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid 
 }
 
 // ---------------------------------------------------------------- pass 2
-// The column pass keeps one strip of cw columns (cw up to 16: up to 128-byte
+// The column pass keeps one strip of cw columns (cw up to 8: up to 64-byte
 // row segments of T) in LDS, column-major with an odd leading dimension, and
 // transforms it in place.  One buffer per strip instead of two frames'
 // ping-pong pairs is what makes wide strips fit; frame 2's spectrum waits in
-// registers while frame 1 is transformed.  The workgroup has NT = 512 or 1024
+// registers while frame 1 is transformed.  The workgroup has NT = 256 or 512
 // threads.
 
 // Column stride of a strip in LDS: the smallest ld >= N whose residue modulo
@@ -516,11 +514,17 @@ constexpr int col_max_elems() { return NT * 72 / (int)sizeof(cplx<T>); }
 
 // The strip's entries as each thread holds them for the stash and the
 // filter: column c = tid / (NT / cw) (wave-uniform: NT / cw >= 64) and rows in
-// groups of g = 4, 2 or 1 (g divides N): rows y + j N/g, j < g,
+// groups of g = 4, 5, 7, 3 or 1 (g divides N): rows y + j N/g, j < g,
 // y = tid mod (NT / cw) + i NT / cw < N/g, whose twiddles w_N^(y + j N/g)
 // differ by the g-th roots of unity.  Group i holds slots g i .. g i + g - 1.
 template <typename T, int NT, int G>
 constexpr int col_groups() { return (col_max_elems<T, NT>() / G + NT - 1) / NT; }
+
+// Entries of one kernel's row DFTs at one column in LDS: CBP_MAX_K and zeros for
+// the last coefficients of a group's polynomials (a multiple of g <= 7 past k).
+constexpr int KR_LD = CBP_MAX_K + 4;
+static_assert((CBP_MAX_K + 6) / 7 * 7 <= KR_LD && (CBP_MAX_K + 4) / 5 * 5 <= KR_LD && (CBP_MAX_K + 2) / 3 * 3 <= KR_LD &&
+                  (CBP_MAX_K + 3) / 4 * 4 <= KR_LD, "group padding");
 
 // Items: (strip of cw columns, channel).  A workgroup that owns several
 // items loads the next strip (and frame 1's strip of the current item) into
@@ -537,7 +541,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
   __shared__ int st[BATCH_CHUNK + 1];
   constexpr int SM = G * col_groups<T, NT, G>();
   constexpr int PF = (col_max_elems<T, NT>() + NT - 1) / NT;   // strip entries per thread
-  constexpr int LNT = NT == 1024 ? 10 : NT == 512 ? 9 : 8;
+  constexpr int LNT = NT == 512 ? 9 : 8;
   __shared__ int s_next[2];   // the workgroup's next items (thread 0 takes them), alternate slots
   const int nf = br.nframes;
   const int* sq = br.starts + (size_t)Q_COL * (nf + 1);
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
   // leave another idle)
   const int ntot = __builtin_amdgcn_readfirstlane(st[nf]);
   const bool dyn = ntot > (int)gridDim.x;
-  const dyn_items q = make_dyn_items(br.ctr + CTR_COL + 8 * (G == 4 ? 0 : G == 2 ? 1 : 2), ntot, (int)blockIdx.x,
+  const dyn_items q = make_dyn_items(br.ctr + CTR_COL + 8 * col_group_index(G), ntot, (int)blockIdx.x,
                                      (int)gridDim.x);
   const int end = q.hi;
   auto frame_of = [&](int it) __attribute__((always_inline)) {
@@ -636,8 +640,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     const T lam = (T)d.lambda;
     const bool two = !(d.variant & VAR_DIVIDE_B1);   // two-channel division, or B1 / K1 alone
     cplx<T>* buf = (cplx<T>*)sm_cf;                   // [cw][ld]
-    cplx<T>* kr = buf + (size_t)cw * ld;              // [cw][2][CBP_MAX_K] row DFTs of the kernels at kx
-    cplx<T>* tw = kr + (size_t)cw * 2 * CBP_MAX_K;    // [N] w_N^t (the filter's kernel spectra)
+    cplx<T>* kr = buf + (size_t)cw * ld;              // [cw][2][KR_LD] row DFTs of the kernels at kx
+    cplx<T>* tw = kr + (size_t)cw * 2 * KR_LD;        // [N] w_N^t (the filter's kernel spectra)
     // the filter's row groups (see col_groups) and its w_N^(G y), y < N / G
     cplx<T>* twg = tw + N;
     cplx<T>* twp = G > 1 ? twg + N / G : twg;         // the plan's pass tables
@@ -667,9 +671,10 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     // the kernels' row DFTs at this strip's columns (k_kernel_dft), zero past hx
     {
       const cplx<T>* krg = (const cplx<T>*)d.kr;
-      for (int e = threadIdx.x; e < cw * 2 * CBP_MAX_K; e += NT) {
-        const int c = e / (2 * CBP_MAX_K);
-        kr[e] = kx0 + c < hx ? krg[(size_t)kx0 * 2 * CBP_MAX_K + e] : cplx<T>{T(0), T(0)};
+      for (int e = threadIdx.x; e < cw * 2 * KR_LD; e += NT) {
+        const int row = e / KR_LD, yy = e - row * KR_LD;   // row = 2 column + kernel
+        kr[e] = kx0 + (row >> 1) < hx && yy < CBP_MAX_K ? krg[((size_t)kx0 * 2 + row) * CBP_MAX_K + yy]
+                                                        : cplx<T>{T(0), T(0)};
       }
     }
     // the entries this thread holds (see col_groups): f(group size, slot of
@@ -718,13 +723,13 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
     for_held([&](auto GC, int a, int c, int y, int q) __attribute__((always_inline)) {
       // kernel spectra at (ky, kx) = sum_yy kr[yy] z^yy, z = w_N^ky.  For the
       // group's rows ky = y + j N/g (z = w_N^y times the g-th roots of unity
-      // (-i)^(4j/g)): K = sum_p z^p E_p(z^g), E_p(u) = sum_t kr[g t + p] u^t
+      // w_g^j): K = sum_p z^p E_p(z^g), E_p(u) = sum_t kr[g t + p] u^t
       // by Horner's rule in u = w_N^(g y), then the g-point DFT of the
       // z^p E_p.  kr is zero beyond each kernel's size; the column is
       // wave-uniform.
       constexpr int g = GC();
-      const cplx<T>* kr1 = kr + (size_t)c * 2 * CBP_MAX_K;
-      const cplx<T>* kr2 = kr1 + CBP_MAX_K;
+      const cplx<T>* kr1 = kr + c * 2 * KR_LD;
+      const cplx<T>* kr2 = kr1 + KR_LD;
       const int nt = (kmax + g - 1) / g;          // coefficients per E_p
       const cplx<T> u = g == 1 ? tw[y] : twg[y];
       cplx<T> P1[g], P2[g];
@@ -747,21 +752,12 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
         P2[p] = zp * P2[p];
       }
       cplx<T>* col = buf + mul24(c, ld) + y;
-      if constexpr (g == 1) {
-        filt(col, P1[0], P2[0], st2[a]);
-      } else if constexpr (g == 2) {
-        filt(col, P1[0] + P1[1], P2[0] + P2[1], st2[a]);
-        filt(col + q, P1[0] - P1[1], P2[0] - P2[1], st2[a + 1]);
-      } else {
-        // rows y, y + N/4, y + N/2, y + 3N/4: roots 1, -i, -1, i
-        const cplx<T> s02_1 = P1[0] + P1[2], d02_1 = P1[0] - P1[2], s13_1 = P1[1] + P1[3], d13_1 = P1[1] - P1[3];
-        const cplx<T> s02_2 = P2[0] + P2[2], d02_2 = P2[0] - P2[2], s13_2 = P2[1] + P2[3], d13_2 = P2[1] - P2[3];
-        const cplx<T> md13_1 = mul_i(d13_1, -1), md13_2 = mul_i(d13_2, -1);   // -i (P1 - P3)
-        filt(col, s02_1 + s13_1, s02_2 + s13_2, st2[a]);
-        filt(col + q, d02_1 + md13_1, d02_2 + md13_2, st2[a + 1]);
-        filt(col + 2 * q, s02_1 - s13_1, s02_2 - s13_2, st2[a + 2]);
-        filt(col + 3 * q, d02_1 - md13_1, d02_2 - md13_2, st2[a + 3]);
+      if constexpr (g > 1) {
+        dft_small<g, -1>(P1);
+        dft_small<g, -1>(P2);
       }
+#pragma unroll
+      for (int j = 0; j < g; ++j, col += q) filt(col, P1[j], P2[j], st2[a + j]);
     });
     __syncthreads();
     // the next item's first strip in flight during the inverse transform (not
@@ -913,7 +909,7 @@ __global__ __launch_bounds__(256) void k_row_inv(batch_ref br) {
     __syncthreads();
     // the next item's spectra are in flight while this one is transformed
     if (it + step < end) fetch(it + step);
-    ip_fft<+1, 256, ROW_MAXE, true>(a, N, px, twf, 0);
+    ip_fft<+1, 256, ROW_MAXE>(a, N, px, twf, 0);
     const cplx<T>* z = a;
     T* oa = (T*)d.out + ch * d.ocs + (int64_t)ya * d.opitch;
     const auto ba = raw_buffer(oa, n * (int)sizeof(T)), bb = raw_buffer(hb ? oa + d.opitch : oa, hb ? n * (int)sizeof(T) : 0);
@@ -934,21 +930,17 @@ size_t row_lds_bytes(int N, int twn, int esize) { return ((size_t)N + (size_t)tw
 // full twiddle table and twn more entries (col_table_entries: the filter's
 // w_N^(g y) and the plan's pass twiddle tables)
 size_t col_lds_bytes(int N, int cw, int twn, int esize) {
-  return ((size_t)cw * (N + 15) + (size_t)cw * 2 * CBP_MAX_K + (size_t)N + (size_t)twn) * 2 * esize;
+  return ((size_t)cw * (N + 15) + (size_t)cw * 2 * KR_LD + (size_t)N + (size_t)twn) * 2 * esize;
 }
 
-// Threads of the column-pass workgroup for a strip of cw * N entries: the
-// fewest of 256 / 512 / 1024 whose registers hold the strip with at least
-// one wave per column (cw <= NT / 64).
+// Threads of the column-pass workgroup for a strip of cw * N entries: 256 when
+// its registers hold the strip with at least one wave per column, else 512.
 int col_threads(int N, int cw, int esize) {
-  const int64_t e = (int64_t)cw * N;
   const int l256 = esize == 4 ? col_max_elems<float, 256>() : col_max_elems<double, 256>();
-  const int l512 = esize == 4 ? col_max_elems<float, 512>() : col_max_elems<double, 512>();
-  if (cw <= 4 && e <= l256) return 256;
-  return (cw <= 8 && e <= l512) ? 512 : 1024;
+  return cw <= 4 && (int64_t)cw * N <= l256 ? 256 : 512;
 }
 
-int col_max_strip_elems(int esize) { return esize == 4 ? col_max_elems<float, 1024>() : col_max_elems<double, 1024>(); }
+int col_max_strip_elems(int esize) { return esize == 4 ? col_max_elems<float, 512>() : col_max_elems<double, 512>(); }
 
 // Resident row-pass workgroups per CU (its registers and lds bytes of LDS),
 // for the persistent grid: a workgroup beyond that would start only when
@@ -973,25 +965,23 @@ int row_fwd_per_cu(size_t lds, int esize) {
 // (element size, variant, LDS in 4 KiB steps).
 // The column-pass instance of element type T, workgroup size nt and filter
 // group g.
+template <typename T, int NT>
+const void* col_kernel_of(int g) {
+  return g == 4 ? (const void*)k_col_filter<T, NT, 4> : g == 5 ? (const void*)k_col_filter<T, NT, 5>
+         : g == 7 ? (const void*)k_col_filter<T, NT, 7> : g == 3 ? (const void*)k_col_filter<T, NT, 3>
+                                                                 : (const void*)k_col_filter<T, NT, 1>;
+}
+
 template <typename T>
 const void* col_kernel(int nt, int g) {
-  if (nt == 256)
-    return g == 4 ? (const void*)k_col_filter<T, 256, 4> : g == 2 ? (const void*)k_col_filter<T, 256, 2>
-                                                                   : (const void*)k_col_filter<T, 256, 1>;
-  if (nt == 512)
-    return g == 4 ? (const void*)k_col_filter<T, 512, 4> : g == 2 ? (const void*)k_col_filter<T, 512, 2>
-                                                                   : (const void*)k_col_filter<T, 512, 1>;
-  return g == 4 ? (const void*)k_col_filter<T, 1024, 4> : g == 2 ? (const void*)k_col_filter<T, 1024, 2>
-                                                                  : (const void*)k_col_filter<T, 1024, 1>;
+  return nt == 256 ? col_kernel_of<T, 256>(g) : col_kernel_of<T, 512>(g);
 }
 
 int col_per_cu(int N, int cw, int twn, int g, int esize) {
-  static std::atomic<int> cache[2][3][3][41];
+  static std::atomic<int> cache[2][2][5][41];
   const int nt = col_threads(N, cw, esize);
-  const int v = nt == 256 ? 0 : nt == 512 ? 1 : 2;
-  const int gi = g == 4 ? 0 : g == 2 ? 1 : 2;
   const int b = std::min((int)((col_lds_bytes(N, cw, twn, esize) + 4095) / 4096), 40);
-  std::atomic<int>& c = cache[esize == 8][v][gi][b];
+  std::atomic<int>& c = cache[esize == 8][nt == 512][col_group_index(g)][b];
   int n = c.load(std::memory_order_relaxed);
   if (n > 0) return n;
   const void* f = esize == 8 ? col_kernel<double>(nt, g) : col_kernel<float>(nt, g);
@@ -1008,8 +998,8 @@ void set_fft_attrs() {
   const void* fns[] = {(const void*)k_row_fwd<float>,  (const void*)k_row_inv<float>,  (const void*)k_rows_front<float>,
                        (const void*)k_row_fwd<double>, (const void*)k_row_inv<double>, (const void*)k_rows_front<double>};
   for (const void* f : fns) hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  for (int nt : {256, 512, 1024})
-    for (int g : {4, 2, 1}) {
+  for (int nt : {256, 512})
+    for (int g : COL_GROUPS) {
       hipFuncSetAttribute(col_kernel<float>(nt, g), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       hipFuncSetAttribute(col_kernel<double>(nt, g), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     }
@@ -1031,7 +1021,7 @@ hipError_t launch_col(const batch_ref& br, int grid, int maxPy, int maxcw, int m
   const int nt = col_threads(maxPy, maxcw, (int)sizeof(T));
   void* args[] = {(void*)&br};
   hipError_t e = hipSuccess;
-  for (int g : {4, 2, 1})
+  for (int g : COL_GROUPS)
     if ((gmask >> g & 1) && e == hipSuccess) e = hipLaunchKernel(col_kernel<T>(nt, g), dim3(grid), dim3(nt), args, lds, st);
   prof_end(PH_COL_FILTER, st);
   return e != hipSuccess ? e : hipGetLastError();

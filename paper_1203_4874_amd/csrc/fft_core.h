@@ -1,4 +1,4 @@
-// Mixed-radix (2, 3, 4, 5, 7, 8) Stockham autosort FFT passes.
+// Mixed-radix (2 to 10, 12, 14, 15) Stockham autosort FFT passes.
 //
 // A length-N transform (N a product of the radices) runs as one pass per
 // radix factor R.  Pass s with stride Ns (the product of the radices already
@@ -17,6 +17,8 @@
 // Everything here is host+device so the same butterfly code can be checked
 // on the CPU.
 #pragma once
+
+#include <initializer_list>
 
 #include "common.h"
 
@@ -136,6 +138,41 @@ CBP_HD void dft9(cplx<T>* v) {
   }
 }
 
+// x with a x = 1 mod b (b > 1, coprime to a).
+CBP_HD constexpr int inverse_mod(int a, int b) {
+  for (int x = 1; x < b; ++x)
+    if (a * x % b == 1) return x;
+  return 1;
+}
+
+// R = A B, coprime (Good, "The interaction algorithm and practical Fourier
+// analysis", 1958): with n = B a + A b mod R and m = c mod A, d mod B,
+// w_R^(nm) = w_A^(ac) w_B^(bd): A-point DFTs over a, then B-point DFTs over b,
+// no twiddles between.
+template <int R, int DIR, typename T>
+CBP_HD void dft_small(cplx<T>* v);
+
+template <int A, int B, int DIR, typename T>
+CBP_HD void dft_coprime(cplx<T>* v) {
+  constexpr int R = A * B, U = B * inverse_mod(B, A), V = A * inverse_mod(A, B);   // m = U c + V d mod R
+  cplx<T> y[R];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    cplx<T> t[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) t[a] = v[(B * a + A * b) % R];
+    dft_small<A, DIR>(t);
+#pragma unroll
+    for (int c = 0; c < A; ++c) y[c * B + b] = t[c];
+  }
+#pragma unroll
+  for (int c = 0; c < A; ++c) {
+    dft_small<B, DIR>(y + c * B);
+#pragma unroll
+    for (int d = 0; d < B; ++d) v[(U * c + V * d) % R] = y[c * B + d];
+  }
+}
+
 template <int R, int DIR, typename T>
 CBP_HD void dft_small(cplx<T>* v) {
   if constexpr (R == 2) dft2<DIR>(v);
@@ -145,6 +182,11 @@ CBP_HD void dft_small(cplx<T>* v) {
   else if constexpr (R == 7) dft7<DIR>(v);
   else if constexpr (R == 8) dft8<DIR>(v);
   else if constexpr (R == 9) dft9<DIR>(v);
+  else if constexpr (R == 6) dft_coprime<2, 3, DIR>(v);
+  else if constexpr (R == 10) dft_coprime<2, 5, DIR>(v);
+  else if constexpr (R == 12) dft_coprime<4, 3, DIR>(v);
+  else if constexpr (R == 14) dft_coprime<2, 7, DIR>(v);
+  else if constexpr (R == 15) dft_coprime<3, 5, DIR>(v);
 }
 
 // ---------------------------------------------------------------- one butterfly
@@ -209,14 +251,93 @@ CBP_HD int plan_radix(const fft_plan& p, int s) { return (int)((p.code >> (4 * s
 // Factor N into the supported radices.  `order` picks the pass order:
 //   0: radix 8 first, then 4, 2, (9,) 3, 5, 7 (fewest passes);
 //   1: radix 4 first, then 8, 2, (9,) 3, 5, 7;
-//   2: odd radices first: 7, 5, (9,) 3, then 8, 4, 2.
-// with9 takes factors 9 as one radix-9 pass before the remaining 3.
+//   2: odd radices first: 7, 5, (9,) 3, then 8, 4, 2;
+//   3: the passes of least cost among all radices (fft_costs), odd radices
+//      first, larger ones before smaller ones (N up to FFT_COST_MAX).
+// with9 (orders 0 to 2) takes factors 9 as one radix-9 pass before the
+// remaining 3.
 // Returns false when N has another prime factor, too many passes, or an
 // unknown order.
-constexpr int FFT_ORDERS = 3;
+constexpr int FFT_ORDERS = 4;
+constexpr int FFT_COST_MAX = 2048;
+
+// The plans of order 3 for every N, the radices in pass order.  A butterfly
+// costs its DFT, 3.5 instructions per twiddle, 4 per entry for addresses and
+// LDS, and 12 (counted in the passes' code).  A pass costs its threads'
+// butterflies, N / (R threads), half of it rounded up (the longest thread's;
+// other workgroups fill part of the gaps), and its barriers.  So a large
+// radix saves a pass where its butterflies still fill the threads: rows of 1296
+// entries as 9, 12, 12 instead of 9, 9, 8, 2 (16 x 720p 117 -> 110 us), but
+// rows of 1944 as 9, 9, 3, 8 and not 9, 9, 6, 4 (8 x 1080p RGB 255, 265).
+struct fft_costs {
+  static constexpr int kRadices = 12;
+  static constexpr int radix(int i) {
+    constexpr int r[kRadices] = {15, 9, 7, 5, 3, 14, 12, 10, 8, 6, 4, 2};
+    return r[i];
+  }
+  static constexpr float dft(int i) {   // instructions per entry of the R-point DFT
+    constexpr float f[kRadices] = {12.5f, 10.0f, 9.4f, 7.2f, 5.3f, 11.4f, 9.3f, 9.2f, 8.0f, 7.3f, 4.0f, 2.0f};
+    return f[i];
+  }
+  signed char counts[FFT_COST_MAX + 1][kRadices];   // passes of each radix, -1: no plan
+  fft_costs() {
+    for (int N = 1; N <= FFT_COST_MAX; ++N) plan(N);
+  }
+  void plan(int N) {
+    // threads a transform: those the column pass's strips give it (rows have 256)
+    const int threads = N <= 576 ? 64 : N <= 1152 ? 128 : 256;
+    int rest = N;
+    for (int f : {2, 3, 5, 7})
+      while (rest % f == 0) rest /= f;
+    for (int i = 0; i < kRadices; ++i) counts[N][i] = rest > 1 ? -1 : 0;
+    if (rest > 1) return;
+    int div[64], nd = 0;   // the divisors, ascending
+    for (int d = 1; d <= N && nd < 64; ++d)
+      if (N % d == 0) div[nd++] = d;
+    float cost[64];
+    int last[64], from[64];
+    for (int a = 0; a < nd; ++a) {
+      cost[a] = 0.0f;
+      last[a] = -1;
+      for (int i = 0; i < kRadices && a > 0; ++i) {
+        const int R = radix(i);
+        if (div[a] % R != 0) continue;
+        int b = 0;
+        while (div[b] != div[a] / R) ++b;
+        const float fly = R * (dft(i) + 4.0f) + 3.5f * (R - 1) + 12.0f;
+        const int all = N / R;
+        const float rounds = 0.5f * ((float)((all + threads - 1) / threads) + (float)all / (float)threads);
+        const float c = cost[b] + fly * rounds + 200.0f;
+        if (last[a] < 0 || c < cost[a]) {
+          cost[a] = c;
+          last[a] = i;
+          from[a] = b;
+        }
+      }
+    }
+    for (int a = nd - 1; a > 0; a = from[a]) ++counts[N][last[a]];
+  }
+};
+
+inline bool make_cheapest_plan(int N, fft_plan* p) {
+  static const fft_costs all;   // 0.8 ms, once
+  if (N < 1 || N > FFT_COST_MAX) return false;
+  const signed char* count = all.counts[N];
+  if (count[0] < 0) return false;
+  p->N = N;
+  p->npass = 0;
+  p->code = 0;
+  for (int i = 0; i < fft_costs::kRadices; ++i)
+    for (int c = 0; c < count[i]; ++c) {
+      p->code |= (unsigned long long)fft_costs::radix(i) << (4 * p->npass);
+      p->radix[p->npass++] = fft_costs::radix(i);
+    }
+  return true;
+}
 
 inline bool make_fft_plan(int N, fft_plan* p, int order = 0, bool with9 = false) {
-  static const int orders[FFT_ORDERS][7] = {
+  if (order == 3) return make_cheapest_plan(N, p);
+  static const int orders[3][7] = {
       {8, 4, 2, 9, 3, 5, 7}, {4, 8, 2, 9, 3, 5, 7}, {7, 5, 9, 3, 8, 4, 2}};
   if (N < 1 || order < 0 || order >= FFT_ORDERS) return false;
   p->N = N;

@@ -134,14 +134,23 @@ struct batch_ref {
 
 // Item counters of a chunk's dynamically scheduled launches, eight each (one
 // per XCD): the row pass, the inverse rows, and the column pass per filter
-// group (4, 2, 1).
+// group.
 constexpr int CTR_ROW_FWD = 0, CTR_ROW_INV = 8, CTR_COL = 16, CTR_COUNT = 64;
-static_assert(CTR_COL + 3 * 8 <= CTR_COUNT, "counter block");
 
-// Rows per group of the column filter's kernel-spectrum evaluation (rows
-// y + j N/g, j < g, share one Horner chain in w_N^(g y)): 4, 2 or 1 as N
-// allows.
-__host__ __device__ inline int col_group_size(int N) { return (N & 3) == 0 ? 4 : (N & 1) == 0 ? 2 : 1; }
+// Rows per group of the column filter's kernel-spectrum evaluation: rows
+// y + j N/g, j < g, share one Horner chain in w_N^(g y), so an entry costs
+// 8 k / g multiply-adds (k terms, two kernels) and its share of a g-point DFT.
+// 4, else 5, 7 or 3 as N allows; 1 is left for N = 1 and 2 (N = 2^a 3^b 5^c 7^d).
+// Columns of 16 x 720p (729 and 735 rows, k 15 and 7), g = 1 and six passes of
+// radix 3, or 7, 7, 5, 3 / g = 3 and 5, passes 9, 9, 9 and 15, 7, 7: 165 / 143 us.
+constexpr int COL_GROUPS[] = {4, 5, 7, 3, 1};
+__host__ __device__ inline int col_group_size(int N) {
+  return (N & 3) == 0 ? 4 : N % 5 == 0 ? 5 : N % 7 == 0 ? 7 : N % 3 == 0 ? 3 : 1;
+}
+__host__ __device__ constexpr int col_group_index(int g) {
+  return g == 4 ? 0 : g == 5 ? 1 : g == 7 ? 2 : g == 3 ? 3 : 4;
+}
+static_assert(CTR_COL + 5 * 8 <= CTR_COUNT, "counter block");
 
 // Column-pass twiddle entries beyond the full table: the filter's
 // w_N^(g y), y < N / g (g = col_group_size(N) > 1), and the pass tables of
