@@ -266,41 +266,40 @@ __device__ __attribute__((always_inline)) inline void fetch_rows(const frame_des
 }
 
 // Rows y of both frames of channel ch, packed as B1 + i B2 in a (LDS, zero
-// beyond each frame): with with_ey their unit-circle evaluation, then the FFT
-// and the two half spectra.  twf: the plan's pass tables, twS: w_S^t.  Ends
-// with a barrier.
+// beyond each frame; a barrier since its store): the FFT and the two half
+// spectra, and with gy the fold of both rows modulo S into gy[frame][S] by the
+// last wave (the caller's DFT of it, row_eval, needs no more).  twf: the plan's
+// pass tables.  Ends with a barrier.
+//
+// The fold has k_front's lanes and order: waves 2 fr, 2 fr + 1 fold frame fr's
+// row into partials, lane g S + r of the pair summing x = r + S (g + G i); a
+// residue then adds its G partials in order.  The partials are behind the
+// passes' barriers when they are added, so the fold adds none of its own.
 template <typename T>
-__device__ __attribute__((always_inline)) inline void row_transform(const frame_desc& d, int ch, int y, int with_ey,
-                                                                    cplx<T>* a, const cplx<T>* twf,
-                                                                    double (*gy)[CBP_MAX_S], double (*fpart_l)[128],
-                                                                    const c64* twS) {
+__device__ __attribute__((always_inline)) inline void row_transform(const frame_desc& d, int ch, int y, cplx<T>* a,
+                                                                    const cplx<T>* twf, double (*gy)[CBP_MAX_S],
+                                                                    double (*fpart_l)[128]) {
+  static_assert(2 * CBP_MAX_S <= 64, "both rows' residues fill one wave");
   const fft_plan& px = d.fx;
   const int N = px.N, hx = d.hx, S = d.S;
   const bool in1 = y < d.H1, in2 = y < d.H2;
-  if (with_ey) {
-    // the row evaluation of both rows (k_front's lanes and order): waves
-    // 2 fr, 2 fr + 1 fold frame fr's row into partials, lane g S + r of the
-    // pair summing x = r + S (g + G i); the residues then add their G
-    // partials in order
-    const int G = 128 / S;
+  const int G = 128 / S;
+  if (gy) {
     const int fr = threadIdx.x >> 7, l = threadIdx.x & 127;
-    const int gl = l / S, rr0 = l - gl * S;
-    const bool inr = fr ? in2 : in1;
-    {
-      double acc = 0.0;
-      if (inr && gl < G) acc = fold_strided((const T*)a + fr, 2, rr0 + S * gl, S * G, fr ? d.W2 : d.W1);
-      fpart_l[fr][l] = acc;
-    }
-    __syncthreads();
-    if (l < S) {
-      double sr = fpart_l[fr][l];
-      for (int gq = 1; gq < G; ++gq) sr += fpart_l[fr][gq * S + l];
-      gy[fr][l] = sr;
-    }
-    __syncthreads();
-    if (l < S && inr) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[fr], 1, twS, S, l);
+    double acc = 0.0;
+    if ((fr ? in2 : in1) && l < G * S) acc = fold_strided((const T*)a + fr, 2, l, S * G, fr ? d.W2 : d.W1);
+    fpart_l[fr][l] = acc;
+    if (px.npass == 0) __syncthreads();   // N = 1
   }
   ip_fft<-1, 256, ROW_MAXE>(a, N, px, twf, 0);
+  if (gy) {
+    const int lane = (int)threadIdx.x - 192, fr = lane >= S, l = fr ? lane - S : lane;
+    if (lane >= 0 && lane < 2 * S) {
+      double sr = fpart_l[fr][l];
+      for (int q = 1; q < G; ++q) sr += fpart_l[fr][q * S + l];
+      gy[fr][l] = sr;
+    }
+  }
   const int64_t to = (int64_t)ch * d.Hmax * d.hxp + (int64_t)y * d.hxp;
   const int row = hx * (int)sizeof(cplx<T>);
   const auto o1 = raw_buffer((cplx<T>*)d.t1 + to, in1 ? row : 0), o2 = raw_buffer((cplx<T>*)d.t2 + to, in2 ? row : 0);
@@ -315,6 +314,18 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
   __syncthreads();
 }
 
+// The S-point DFTs of the folds gy[i] of rows y0 + i S, i < n, both frames
+// (threads tid of nt): the row evaluation of k_front, output for output.
+__device__ __attribute__((always_inline)) inline void row_eval(const frame_desc& d, int ch, int y0, int n, int tid, int nt,
+                                                               const double (*gy)[2][CBP_MAX_S], const c64* twS) {
+  const int S = d.S;
+  for (int o = tid; o < n * 2 * S; o += nt) {
+    const int i = o / (2 * S), rest = o - i * 2 * S, fr = rest >= S, l = fr ? rest - S : rest;
+    const int y = y0 + i * S;
+    if (y < (fr ? d.H2 : d.H1)) d.ey[((size_t)(2 * ch + fr) * S + l) * d.Hmax + y] = dft_at(gy[i][fr], 1, twS, S, l);
+  }
+}
+
 // Items: (channel, row group g, residue r): the rows y = g rpg + r + S i,
 // i < rpg / S, y < Hmax, in increasing y.  Each row of both frames is packed
 // as B1 + i B2 and transformed; while the rows pass, the workgroup folds them
@@ -323,15 +334,19 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
 // the group's partial sums, so the frames are read once.  With with_ey, the
 // unit-circle evaluation of both rows (fold modulo S and S-point DFT, as
 // eval_rows_item: the same lanes, the same order, hence the same bits) is taken
-// from the row in LDS; waves 0-1 fold frame (w & 1).  The grid is
+// from the row in LDS; the DFTs of up to EY_ROWS rows run together, over all
+// threads, instead of on 2 S of them while the row waits, with two barriers of
+// their own (8 x 1080p RGB 255 -> 248 us, 16 x 720p 110 -> 105).  The grid is
 // persistent: a workgroup loads its next row into registers while it
 // transforms the current one.
 static_assert(CBP_MAX_FFT_F32 <= 8 * 256 && CBP_MAX_FFT_F64 <= 8 * 256, "one row is eight loads per thread");
 
+constexpr int EY_ROWS = 8;
+
 template <typename T>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_ref br, int with_ey) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
-  __shared__ double gy[2][CBP_MAX_S];
+  __shared__ double gy[EY_ROWS][2][CBP_MAX_S];
   __shared__ double fpart_l[2][128];
   __shared__ c64 twS[CBP_MAX_S];
   __shared__ int st[BATCH_CHUNK + 1];
@@ -411,8 +426,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
       const int y = q.y0 + S * i;
       row_twiddles(a, twf, px, tabN, tabCode);
       if (with_ey && S != tabS) {
-        // w_t for the row evaluation (made again only when S changes; the
-        // barrier after the row's store orders it before its use)
+        // w_t for the row evaluation (made again only when S changes: behind
+        // the last item's evaluation, and the barrier after the row's store
+        // orders it before its use)
+        __syncthreads();
         row_unit_twiddles((__attribute__((address_space(3))) c64*)twS, S);
         tabS = S;
       }
@@ -427,7 +444,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
       // the next row is in flight while this one is transformed
       if (i + 1 < q.nv) fetch(d, ch, y + S);
       else fetch_from(it + step);
-      row_transform<T>(d, ch, y, with_ey, a, twf, gy, fpart_l, twS);
+      const int e = i % EY_ROWS;
+      row_transform<T>(d, ch, y, a, twf, with_ey ? gy[e] : nullptr, fpart_l);
+      if (with_ey && (e == EY_ROWS - 1 || i + 1 == q.nv)) row_eval(d, ch, y - e * S, e + 1, threadIdx.x, 256, gy, twS);
     }
     // the group's column-fold partials (fold_item's layout), for x < W
     const auto fp1 = raw_buffer(d.fpart + (((size_t)q.g * d.ncf + 2 * ch) * S + q.r) * (size_t)d.Wmax, d.W1 * 8);
@@ -450,7 +469,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
 template <typename T>
 __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid g, inline_head ih) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
-  __shared__ double gy[2][CBP_MAX_S];
+  __shared__ double gy[1][2][CBP_MAX_S];
   __shared__ double fpart_l[2][128];
   __shared__ c64 twS[CBP_MAX_S];
   const batch_ref br = first_launch_head(br_ws, ih);
@@ -473,15 +492,19 @@ __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid 
     T uv[8], wv[8];
     fetch_rows<T>(d, ch, y, uv, wv);
     row_twiddles(a, twf, d.fx, tabN, tabCode);
-    if (d.S != tabS) row_unit_twiddles((__attribute__((address_space(3))) c64*)twS, d.S);
-    tabS = d.S;
+    if (d.S != tabS) {
+      __syncthreads();   // the last item's evaluation reads twS
+      row_unit_twiddles((__attribute__((address_space(3))) c64*)twS, d.S);
+      tabS = d.S;
+    }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int x = t * 256 + local_tid();
       if (x < N) a[x] = {uv[t], wv[t]};
     }
     __syncthreads();
-    row_transform<T>(d, ch, y, 1, a, twf, gy, fpart_l, twS);
+    row_transform<T>(d, ch, y, a, twf, gy[0], fpart_l);
+    row_eval(d, ch, y, 1, threadIdx.x, 256, gy, twS);
   });
 }
 

@@ -83,3 +83,17 @@ def test_strip_width_of_a_mixed_batch(single):
         Ls, K1s, K2s, _ = P.deblur_batch(part, lam=1e-2)
         for f, L, K1, K2 in zip(part, Ls, K1s, K2s):
             assert all(torch.equal(x, y) for x, y in zip((L, K1, K2), P.deblur(*f, lam=1e-2)))
+
+
+@pytest.mark.parametrize("rows", [1290, 1930])
+def test_evaluation_of_long_items(rows):
+    """Fused items of more than eight rows evaluate them in parts: the bits of
+    the split pass, which takes one row at a time."""
+    torch = pytest.importorskip("torch")
+    import paper_1203_4874_amd as P
+    r = np.random.default_rng(rows)
+    frames = [[torch.as_tensor(r.random((3, rows + k - 1, 20 + k - 1)), dtype=torch.float32, device="cuda")
+               for k in (5, 4)] + [rows, 20] for _ in range(4)]
+    Ls, K1s, K2s, _ = P.deblur_batch(frames, lam=1e-2)
+    for f, L, K1, K2 in zip(frames, Ls, K1s, K2s):
+        assert all(torch.equal(x, y) for x, y in zip((L, K1, K2), P.deblur(*f, lam=1e-2)))
