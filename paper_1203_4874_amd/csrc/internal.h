@@ -427,6 +427,11 @@ __device__ inline batch_ref first_launch_head(const batch_ref& br_ws, const inli
 // w_j^r F[r][x].  256 threads: 16 columns x 16 residues / frequencies in
 // flight, each thread two residues when S > 16.  F (CBP_MAX_S x 16 doubles) and tw (CBP_MAX_S) are LDS scratch.
 // Items: (column block, cf).
+// Bound by latency (a block's loads wait for memory, its start for the head):
+// eight groups' partials are in flight, the last ones too, and the twiddles are
+// made meanwhile.  Last groups in pairs, twiddles first / so: 8 x 1080p RGB 51 /
+// 47 us, 480x640 5.5 / 5.0, 64x64 4.5 / 3.5.  (32 columns and four residues a
+// thread: 46, 6.5 and 4.6.)
 static_assert(CBP_MAX_S <= 32, "the column evaluation holds residues ty and ty + 16 per thread");
 __device__ inline void eval_cols_item(const frame_desc& d, int item, double (*F)[16], c64* tw) {
   const int nx = (d.Wmax + 15) / 16;
@@ -435,7 +440,6 @@ __device__ inline void eval_cols_item(const frame_desc& d, int item, double (*F)
   const int W = (cf & 1) ? d.W2 : d.W1;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int x = bx * 16 + tx;
-  unit_twiddles(tw, S);
   // residues ty and ty + 16 (S <= 32) at once: eight groups' loads of each in
   // flight; even groups into s0, odd into s1, in group order
   {
@@ -444,14 +448,17 @@ __device__ inline void eval_cols_item(const frame_desc& d, int item, double (*F)
     const double* p0 = d.fpart + ((size_t)cf * S + ty) * Wmax + x;
     const double* p1 = p0 + (size_t)16 * Wmax;
     double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
-    int g = 0;
-    for (; g + 8 <= RG; g += 8) {
+    for (int g = 0; g < RG; g += 8) {
       double v[8], w[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        v[u] = h0 ? p0[(size_t)(g + u) * gs] : 0.0;
-        w[u] = h1 ? p1[(size_t)(g + u) * gs] : 0.0;
+        v[u] = w[u] = 0.0;   // (a zero added past RG changes no bit: a sum is never -0)
+        if (g + u < RG) {
+          if (h0) v[u] = p0[(size_t)(g + u) * gs];
+          if (h1) w[u] = p1[(size_t)(g + u) * gs];
+        }
       }
+      if (g == 0) unit_twiddles(tw, S);   // while the first loads are in flight
 #pragma unroll
       for (int u = 0; u < 8; u += 2) {
         s0 += v[u];
@@ -459,20 +466,6 @@ __device__ inline void eval_cols_item(const frame_desc& d, int item, double (*F)
         t0 += w[u];
         t1 += w[u + 1];
       }
-    }
-    for (; g + 2 <= RG; g += 2) {
-      if (h0) {
-        s0 += p0[(size_t)g * gs];
-        s1 += p0[(size_t)(g + 1) * gs];
-      }
-      if (h1) {
-        t0 += p1[(size_t)g * gs];
-        t1 += p1[(size_t)(g + 1) * gs];
-      }
-    }
-    if (g < RG) {
-      if (h0) s0 += p0[(size_t)g * gs];
-      if (h1) t0 += p1[(size_t)g * gs];
     }
     if (ty < S) F[ty][tx] = s0 + s1;
     if (ty + 16 < S) F[ty + 16][tx] = t0 + t1;
