@@ -46,3 +46,16 @@ def test_orders_share_a_launch():
     for f, A, B in zip(frames, K1s, K2s):
         _, K1, K2 = P.deblur(*f, lam=1e-6)
         assert torch.equal(A, K1) and torch.equal(B, K2)
+
+
+# smallest eigenvalues from rounding level (no noise) to a good part of the largest (noise alone)
+@pytest.mark.parametrize("noise", [0.0, 1e-6, 1e-3, 1e-1, None])
+def test_size_of_smallest_eigenvalue(noise):
+    torch = pytest.importorskip("torch")
+    import paper_1203_4874_amd as P
+    B1, B2, _, _, m, n = frame(torch, 7, 5)
+    r = np.random.default_rng(5)
+    B1, B2 = (r.standard_normal(B.shape) if noise is None else B + noise * r.standard_normal(B.shape) for B in (B1, B2))
+    K1, K2 = P.recover_kernels(torch.as_tensor(B1, device="cuda"), torch.as_tensor(B2, device="cuda"), m, n)
+    R1, R2 = orc.recover_kernels(B1, B2, m, n)
+    assert max(rel(K1.cpu().numpy(), R1), rel(K2.cpu().numpy(), R2)) <= 1e-6     # the FP64 form's bound
