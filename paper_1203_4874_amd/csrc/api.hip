@@ -129,6 +129,7 @@ size_t head_bytes(int nframes) {
          align_up((size_t)nchunks(nframes) * CTR_COUNT * sizeof(int));
 }
 
+static_assert(CBP_MAX_FFT_F32 <= FFT_COST_MAX && CBP_MAX_FFT_F64 <= FFT_COST_MAX, "a plan for every length");
 int max_fft(int esize) { return esize == 4 ? CBP_MAX_FFT_F32 : CBP_MAX_FFT_F64; }
 
 // ---------------------------------------------------------------- tuning

@@ -566,8 +566,8 @@ size_t gram_mfma_lds_bytes(int maxStride, int fmt);
 void set_gram_mfma_attrs();
 
 // fft.hip.  The row pass also writes the column fold's partials (the
-// k_fold_cols result, bit for bit) and, with with_ey, the row evaluation EY
-// (the k_eval_rows result, bit for bit) from the rows it already holds.
+// result of fold_item, bit for bit) and, with with_ey, the row evaluation EY
+// (the result of k_front, bit for bit) from the rows it already holds.
 template <typename T>
 hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, int with_ey, hipStream_t st);
 // The first launch of a deblurring call with the split row pass: every row of
