@@ -154,7 +154,7 @@ constexpr tuning kDefaultTuning = {0, 0, 0, 3};
 // frame keeps the fold's partial sums (one row per item) small.  The group
 // depends on the frame alone, so a frame gets the same bits in any batch.
 constexpr int kRowItemsPerFrame = 384;
-constexpr int kRowWgPerCu = 4;   // resident inverse-row workgroups per CU (LDS: a row and its pass twiddle tables)
+constexpr int kRowWgPerCu = 4;   // workgroups per CU of the split row pass
 
 // A call with fewer fused row-pass items than this runs the split row pass:
 // single rows spread over the chip and the column fold reads the frames again
@@ -579,7 +579,7 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
   const bool latent = reqs[0].latent != nullptr;
   for (int f = 0; f < nreq; ++f) {
     const frame_req& r = reqs[f];
-    frame_plan fp;
+    frame_plan fp = {};
     cbp_status s = make_plan(r.b1, r.b2, r.m, r.n, o, tn, &fp, sizes_only);
     if (s == CBP_OK && r.b1->dtype != dtype) s = CBP_E_INVALID;
     if (s == CBP_OK && (r.latent != nullptr) != latent) s = CBP_E_INVALID;
@@ -670,7 +670,9 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
       else cv.front.twid = cv.grid[Q_TWID];
     }
     // as many persistent row-pass workgroups as stay resident
-    if (cap == 0) cv.grid[Q_ROW_FWD] = grid_for(cv.items[Q_ROW_FWD], row_fwd_per_cu(row_lds_bytes(cv.maxPx, cv.maxTwx, esize), esize) * kComputeUnits);
+    if (cap == 0 && latent)
+      for (int q : {Q_ROW_FWD, Q_ROW_INV})
+        cv.grid[q] = grid_for(cv.items[q], row_per_cu(q == Q_ROW_INV, row_lds_bytes(cv.maxPx, cv.maxTwx, esize), esize) * kComputeUnits);
     // the widest strip and the tallest column share one allocation; keep it in LDS
     while (cv.maxcw > 1 && !col_fits(cv.maxPy, cv.maxcw, cv.maxTwy, esize)) {
       cv.maxcw >>= 1;

@@ -965,16 +965,20 @@ int col_threads(int N, int cw, int esize) {
 
 int col_max_strip_elems(int esize) { return esize == 4 ? col_max_elems<float, 512>() : col_max_elems<double, 512>(); }
 
-// Resident row-pass workgroups per CU (its registers and lds bytes of LDS),
-// for the persistent grid: a workgroup beyond that would start only when
-// another ends and leave a tail.  Kept per (element size, LDS in 4 KiB steps).
-int row_fwd_per_cu(size_t lds, int esize) {
-  static std::atomic<int> cache[2][41];
+// Resident forward or inverse row-pass workgroups per CU (its registers and lds
+// bytes of LDS), for the persistent grid: a workgroup beyond that would start
+// only when another ends and leave a tail, fewer leave the CU's waits unfilled
+// (inverse rows, four a CU / as many as fit: 16 x 720p 40.2 / 36.8 us, six a CU;
+// 16 x 256x256 12.3 / 11.6).
+// Kept per (direction, element size, LDS in 4 KiB steps).
+int row_per_cu(bool inverse, size_t lds, int esize) {
+  static std::atomic<int> cache[2][2][41];
   const int b = std::min((int)((lds + 4095) / 4096), 40);
-  std::atomic<int>& c = cache[esize == 8][b];
+  std::atomic<int>& c = cache[inverse][esize == 8][b];
   int n = c.load(std::memory_order_relaxed);
   if (n > 0) return n;
-  const void* f = esize == 8 ? (const void*)k_row_fwd<double> : (const void*)k_row_fwd<float>;
+  const void* f = inverse ? (esize == 8 ? (const void*)k_row_inv<double> : (const void*)k_row_inv<float>)
+                          : (esize == 8 ? (const void*)k_row_fwd<double> : (const void*)k_row_fwd<float>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 256, (size_t)b * 4096) != hipSuccess || n < 1) {
     (void)hipGetLastError();
     return 1;

@@ -585,7 +585,7 @@ hipError_t launch_kernel_dft(const batch_ref& br, int grid, hipStream_t st);
 template <typename T>
 hipError_t launch_row_inv(const batch_ref& br, int grid, int maxPx, int maxTw, hipStream_t st);
 size_t row_lds_bytes(int N, int twn, int esize);   // twn: pass twiddle-table entries
-int row_fwd_per_cu(size_t lds, int esize);
+int row_per_cu(bool inverse, size_t lds, int esize);
 size_t col_lds_bytes(int N, int cw, int twn, int esize);
 int col_max_strip_elems(int esize);   // largest cw * Py the column pass holds
 int col_threads(int N, int cw, int esize);
