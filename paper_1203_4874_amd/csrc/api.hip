@@ -159,9 +159,9 @@ constexpr int kRowWgPerCu = 4;   // workgroups per CU of the split row pass
 // A call with fewer fused row-pass items than this runs the split row pass:
 // single rows spread over the chip and the column fold reads the frames again
 // (they sit in the caches), instead of items of several rows in turn on part
-// of the chip.  Whole calls, fused / split: 1000x180 FP32 125 / 96 us, 480x640
-// 135 / 123, 1080p RGB FP32 (411 items) 350 / 344; 719x1277 FP64 (255) 202 /
-// 196, 1080p RGB FP64 (429) 402 / 405.
+// of the chip.  Whole calls, fused / split: 1000x180 FP32 112 / 86 us, 480x640
+// RGB 134 / 125, 1080p RGB FP32 (411 items) 313 / 305, two of them 404 / 416;
+// 1080p RGB FP64 (429) 371 / 381.
 constexpr int split_row_items(int esize) { return esize == 4 ? 512 : 400; }
 
 // Does a strip of cw columns of length Py fit the column pass?

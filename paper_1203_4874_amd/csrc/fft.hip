@@ -43,7 +43,9 @@ namespace {
 // range checks by the buffer unit, half spectra read once, tables gathered
 // from one: 8 x 1080p RGB FP32 columns 409 -> 377 us, forward rows 319 -> 255,
 // inverse rows 138 -> 104 (the rows with the pass order of kDefaultTuning);
-// 719x1277 FP64 columns 47 -> 29.8, single rows 27.6 -> 22.8.
+// 719x1277 FP64 columns 47 -> 29.8, single rows 27.6 -> 22.8.  With the plans
+// of fft_costs and the strip widths and evaluations of later, 354, 248, 104;
+// 24.8 and 21.3.
 
 // threadIdx.x behind an empty asm statement: values derived from it are
 // recomputed where they are used instead of being hoisted out of the item
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
 // columns from the frames themselves (k_front's fold, the same bits), g.twid
 // fill the twiddle tables.  A row is a workgroup of its own instead of a
 // turn of one residue's: 480x640 (168 items of three rows) 22.7 us and 4.7 for
-// the launch before it -> 13.6 (12.5 since); 64x64 FP64 38.8 and 4.5 -> 8.4.
+// the launch before it -> 13.6 (12.2 since); 64x64 FP64 38.8 and 4.5 -> 8.4 (8.6).
 template <typename T>
 __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid g, inline_head ih) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
