@@ -201,6 +201,18 @@ void set_strip_widths(std::vector<frame_plan>& plans) {
   for (frame_plan& p : plans) p.cw = cw;
 }
 
+// LDS in which the column pass forms the kernels' row DFTs itself: the largest
+// kernel pair and its columns' twiddles.  Taken when every strip of the call has
+// a workgroup of its own at once: the launch of k_kernel_dft (4.7 us however
+// little it does) is then more than the sums repeated in each channel.  Whole
+// calls, own launch / here: 64x64 FP64 73.5 / 71.4 us, 480x640 FP32 113.5 / 111.0,
+// 719x1277 FP64 158.2 / 155.7, 16 x 256x256 learned 285.7 / 282.4.
+int own_kr_bytes(const frame_plan* p, int n, int cw) {
+  int most = 0;
+  for (int i = 0; i < n; ++i) most = std::max(most, (p[i].k1 * p[i].k1 + p[i].k2 * p[i].k2 + 1) & ~1);
+  return most * (int)sizeof(double) + cw * CBP_MAX_K * (int)sizeof(c64);
+}
+
 bool valid_image(const cbp_image* im) {
   if (!im || !im->data) return false;
   if (im->dtype != CBP_F32 && im->dtype != CBP_F64) return false;
@@ -469,6 +481,7 @@ struct chunk_view {
   int grid[Q_COUNT];
   int maxN, maxS, maxPx, maxPy, maxcw;
   int maxTwx, maxTwy;   // largest row / column pass twiddle tables (entries)
+  int ownKr;            // bytes of LDS in which the column pass forms the kernels' row DFTs (0: k_kernel_dft does)
   int colGroups;        // the column filter's row groups of the frames (bit g set for group g)
   int gram_fmt;   // gram_format() of the call's precision
   int maxStride;  // largest Hmax / Wmax (matrix-core Gram staging)
@@ -515,8 +528,8 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
     CBP_TRY(launch_finalize(br(Q_FINALIZE), cv.grid[Q_FINALIZE], cv.maxS, 0, cv.finLean, dd, st));
   }
   if (latent) {
-    CBP_TRY(launch_kernel_dft<T>(br(Q_KRDFT), cv.grid[Q_KRDFT], st));
-    CBP_TRY(launch_col<T>(br(Q_COL), cv.grid[Q_COL], cv.maxPy, cv.maxcw, cv.maxTwy, cv.colGroups, st));
+    if (!cv.ownKr) CBP_TRY(launch_kernel_dft<T>(br(Q_KRDFT), cv.grid[Q_KRDFT], st));
+    CBP_TRY(launch_col<T>(br(Q_COL), cv.grid[Q_COL], cv.maxPy, cv.maxcw, cv.maxTwy, cv.colGroups, cv.ownKr, st));
     CBP_TRY(launch_row_inv<T>(br(Q_ROW_INV), cv.grid[Q_ROW_INV], cv.maxPx, cv.maxTwx, st));
   }
   return hipSuccess;
@@ -691,6 +704,14 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
     // strip while finishing the current one (as many as stay resident)
     cv.grid[Q_COL] = grid_for(cv.items[Q_COL],
                               cap > 0 ? cap : col_per_cu(cv.maxPy, cv.maxcw, cv.maxTwy, col_group_size(cv.maxPy), esize) * kComputeUnits);
+    cv.ownKr = 0;
+    if (latent && cv.items[Q_COL] <= cv.grid[Q_COL]) {
+      const int own = own_kr_bytes(bb->plans.data() + f0, cnt, cv.maxcw);
+      const int twn = cv.maxTwy + (own + 16) / (2 * esize) + 1;
+      if (col_lds_bytes(cv.maxPy, cv.maxcw, twn, esize) <= kLdsLimit - 4096 &&
+          cv.items[Q_COL] <= col_per_cu(cv.maxPy, cv.maxcw, twn, col_group_size(cv.maxPy), esize) * kComputeUnits)
+        cv.ownKr = own;
+    }
     bb->chunks.push_back(cv);
   }
   return CBP_OK;

@@ -551,6 +551,44 @@ constexpr int KR_LD = CBP_MAX_K + 4;
 static_assert((CBP_MAX_K + 6) / 7 * 7 <= KR_LD && (CBP_MAX_K + 4) / 5 * 5 <= KR_LD && (CBP_MAX_K + 2) / 3 * 3 <= KR_LD &&
                   (CBP_MAX_K + 3) / 4 * 4 <= KR_LD, "group padding");
 
+// The kernels' row DFTs at columns kx0 .. kx0 + cw into kr [cw][2][KR_LD], zero
+// past hx and past each kernel's rows: k_kernel_dft's sums.  at: LDS for the
+// kernels and the columns' twiddles.  (A call: inlined, it costs the column pass
+// of every launch some five registers.)
+template <typename T, int NT>
+__device__ __attribute__((noinline)) void own_row_dfts(__attribute__((address_space(3))) char* at,
+                                                       __attribute__((address_space(3))) cplx<T>* kr, const double* K1,
+                                                       const double* K2, const c64* twd, int k1, int k2, int Px, int hx,
+                                                       int kx0, int cw) {
+  typedef __attribute__((address_space(3))) double lds_d;
+  const int n1 = k1 * k1, nk = n1 + k2 * k2;
+  lds_d* Kl = (lds_d*)at;                    // K1, K2
+  lds_d* wl = Kl + ((nk + 1) & ~1);          // [cw][CBP_MAX_K] w_Px^(kx x), re and im
+  for (int e = threadIdx.x; e < nk; e += NT) Kl[e] = e < n1 ? K1[e] : K2[e - n1];
+  for (int e = threadIdx.x; e < cw * CBP_MAX_K; e += NT) {
+    const int c = e / CBP_MAX_K, x = e - c * CBP_MAX_K;
+    const c64 w = twd[min(kx0 + c, hx - 1) * x % Px];
+    wl[2 * e] = w.re;
+    wl[2 * e + 1] = w.im;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < cw * 2 * KR_LD; e += NT) {
+    const int row = e / KR_LD, yy = e - row * KR_LD, c = row >> 1;   // row = 2 column + kernel
+    const int k = row & 1 ? k2 : k1;
+    double sr = 0.0, si = 0.0;
+    if (yy < k && kx0 + c < hx) {
+      lds_d* kv = Kl + (row & 1 ? n1 : 0) + yy * k;
+      lds_d* w = wl + 2 * c * CBP_MAX_K;
+      for (int x = 0; x < k; ++x) {
+        sr += kv[x] * w[2 * x];
+        si += kv[x] * w[2 * x + 1];
+      }
+    }
+    kr[e].re = T(sr);
+    kr[e].im = T(si);
+  }
+}
+
 // Items: (strip of cw columns, channel).  A workgroup that owns several
 // items loads the next strip (and frame 1's strip of the current item) into
 // registers while it transforms.
@@ -561,7 +599,7 @@ static_assert((CBP_MAX_K + 6) / 7 * 7 <= KR_LD && (CBP_MAX_K + 4) / 5 * 5 <= KR_
 // compile-time group keeps the stashed spectrum's slots compile-time
 // indices, in registers.
 template <typename T, int NT, int G>
-__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch_ref br) {
+__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch_ref br, int own) {
   extern __shared__ __attribute__((aligned(16))) char sm_cf[];
   __shared__ int st[BATCH_CHUNK + 1];
   constexpr int SM = G * col_groups<T, NT, G>();
@@ -693,8 +731,13 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
       tabN = N;
       tabCode = py.code;
     }
-    // the kernels' row DFTs at this strip's columns (k_kernel_dft), zero past hx
-    {
+    // the kernels' row DFTs at this strip's columns, zero past hx: from
+    // k_kernel_dft, or (own: the place in LDS of the kernels and the columns'
+    // twiddles) formed here, the same sums
+    if (own) {
+      own_row_dfts<T, NT>((__attribute__((address_space(3))) char*)(sm_cf + own), (__attribute__((address_space(3))) cplx<T>*)kr,
+                          d.K1, d.K2, d.twxd, k1, k2, d.Px, hx, kx0, cw);
+    } else {
       const cplx<T>* krg = (const cplx<T>*)d.kr;
       for (int e = threadIdx.x; e < cw * 2 * KR_LD; e += NT) {
         const int row = e / KR_LD, yy = e - row * KR_LD;   // row = 2 column + kernel
@@ -811,7 +854,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 2) void k_col_filter(batch
 // half-spectrum column kx < hx (zero for yy >= k_fr), in FP64 from the FP64
 // twiddle table, rounded once to T: the column pass evaluates each kernel's
 // spectrum at (ky, kx) from these along y.  Once per frame, shared by its
-// channels.  Items: 256 consecutive entries of [0, hx * 2 * CBP_MAX_K).
+// channels; a call whose strips all run at once forms them in its column pass
+// instead (see own_kr_bytes in api.hip).  Items: 256 consecutive entries of [0, hx * 2 * CBP_MAX_K).
 static_assert(2 * CBP_MAX_K == 64, "one column's entries fill one wave");
 
 template <typename T>
@@ -1044,11 +1088,13 @@ hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, i
 }
 
 template <typename T>
-hipError_t launch_col(const batch_ref& br, int grid, int maxPy, int maxcw, int maxTw, int gmask, hipStream_t st) {
+hipError_t launch_col(const batch_ref& br, int grid, int maxPy, int maxcw, int maxTw, int gmask, int ownBytes,
+                      hipStream_t st) {
   prof_begin(PH_COL_FILTER, st);
-  const size_t lds = col_lds_bytes(maxPy, maxcw, maxTw, (int)sizeof(T));
+  const size_t strip = (col_lds_bytes(maxPy, maxcw, maxTw, (int)sizeof(T)) + 15) & ~(size_t)15, lds = strip + ownBytes;
   const int nt = col_threads(maxPy, maxcw, (int)sizeof(T));
-  void* args[] = {(void*)&br};
+  int own = ownBytes ? (int)strip : 0;
+  void* args[] = {(void*)&br, (void*)&own};
   hipError_t e = hipSuccess;
   for (int g : COL_GROUPS)
     if ((gmask >> g & 1) && e == hipSuccess) e = hipLaunchKernel(col_kernel<T>(nt, g), dim3(grid), dim3(nt), args, lds, st);
@@ -1092,8 +1138,8 @@ template hipError_t launch_rows_front<double>(const batch_ref&, const front_grid
                                               hipStream_t);
 template hipError_t launch_row_fwd<float>(const batch_ref&, int, int, int, int, hipStream_t);
 template hipError_t launch_row_fwd<double>(const batch_ref&, int, int, int, int, hipStream_t);
-template hipError_t launch_col<float>(const batch_ref&, int, int, int, int, int, hipStream_t);
-template hipError_t launch_col<double>(const batch_ref&, int, int, int, int, int, hipStream_t);
+template hipError_t launch_col<float>(const batch_ref&, int, int, int, int, int, int, hipStream_t);
+template hipError_t launch_col<double>(const batch_ref&, int, int, int, int, int, int, hipStream_t);
 template hipError_t launch_kernel_dft<float>(const batch_ref&, int, hipStream_t);
 template hipError_t launch_kernel_dft<double>(const batch_ref&, int, hipStream_t);
 template hipError_t launch_row_inv<float>(const batch_ref&, int, int, int, hipStream_t);

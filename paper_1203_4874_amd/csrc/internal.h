@@ -579,7 +579,8 @@ hipError_t launch_rows_front(const batch_ref& br, const front_grid& g, int maxPx
 template <typename T>
 // gmask: the filter groups g (bit g) of the batch's frames; one launch per
 // group, each taking the items of its frames
-hipError_t launch_col(const batch_ref& br, int grid, int maxPy, int maxcw, int maxTw, int gmask, hipStream_t st);
+hipError_t launch_col(const batch_ref& br, int grid, int maxPy, int maxcw, int maxTw, int gmask, int ownBytes,
+                      hipStream_t st);
 template <typename T>
 hipError_t launch_kernel_dft(const batch_ref& br, int grid, hipStream_t st);
 template <typename T>

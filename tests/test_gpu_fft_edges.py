@@ -97,3 +97,18 @@ def test_evaluation_of_long_items(rows):
     Ls, K1s, K2s, _ = P.deblur_batch(frames, lam=1e-2)
     for f, L, K1, K2 in zip(frames, Ls, K1s, K2s):
         assert all(torch.equal(x, y) for x, y in zip((L, K1, K2), P.deblur(*f, lam=1e-2)))
+
+
+@pytest.mark.parametrize("single", [True, False])
+@pytest.mark.parametrize("k1,k2", [(1, 2), (16, 15)])
+def test_kernel_row_transforms_in_either_launch(single, k1, k2):
+    """A call whose strips all run at once forms the kernels' row transforms in
+    its column pass, one with more strips in a launch before it: the same bits."""
+    torch = pytest.importorskip("torch")
+    import paper_1203_4874_amd as P
+    dtype = torch.float32 if single else torch.float64
+    frames = [[torch.as_tensor(b, dtype=dtype, device="cuda") for b in blurred(130, 390, k1, k2, s)] + [130, 390]
+              for s in range(4)]
+    Ls, K1s, K2s, _ = P.deblur_batch(12 * frames, lam=1e-2)
+    for f in (0, 1, 2, 3, 45):
+        assert all(torch.equal(x, y) for x, y in zip((Ls[f], K1s[f], K2s[f]), P.deblur(*frames[f % 4], lam=1e-2)))
