@@ -80,6 +80,14 @@ __device__ inline double sum_rows(double v) {
   return readlane_d(v, 63);
 }
 
+// The same in double-double.
+__device__ inline dd sum_rows(dd v) {
+  v = dd_add(v, dpp_dd<0x128>(v));
+  v = dd_add(v, dpp_dd<0x142>(v));
+  v = dd_add(v, dpp_dd<0x143>(v));
+  return {readlane_d(v.hi, 63), readlane_d(v.lo, 63)};
+}
+
 // Reciprocal and reciprocal square root: hardware estimate (2^-23 or
 // better) and one third-order step (error below 2^-68 before rounding).
 __device__ inline double rcp_h(double x) {
@@ -138,14 +146,38 @@ __device__ inline double wave_parts(const double* p) {
   return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
 }
 
+// The same in double-double: high parts in hi, low parts in lo.
+template <int C>
+__device__ inline dd wave_parts(const double* hi, const double* lo) {
+  dd v[8];
+#pragma unroll
+  for (int w = 0; w < 8; ++w) v[w] = w < C ? dd{hi[w], lo[w]} : dd{0.0, 0.0};
+#pragma unroll
+  for (int n = 4; n > 0; n >>= 1)
+#pragma unroll
+    for (int w = 0; w < n; ++w) v[w] = dd_add(v[2 * w], v[2 * w + 1]);
+  return v[0];
+}
+
 // Sum over the block of a value equal in the eight lanes of each row.  slot:
-// the row of s.part used (free again two barriers later).  Contains a barrier.
+// the row of s.part used (free again two barriers later), slot and slot2 for a
+// double-double.  Contains a barrier.
 template <int C>
 __device__ inline double block_rows_sum(const blk_ws& s, int slot, double v) {
   double* p = s.part + slot * BLK_MAX_WAVES;
   p[threadIdx.x >> 6] = sum_rows(v);
   __syncthreads();
   return wave_parts<C>(p);
+}
+template <int C>
+__device__ inline dd block_rows_sum(const blk_ws& s, int slot, int slot2, dd v) {
+  double* h = s.part + slot * BLK_MAX_WAVES;
+  double* l = s.part + slot2 * BLK_MAX_WAVES;
+  v = sum_rows(v);
+  h[threadIdx.x >> 6] = v.hi;
+  l[threadIdx.x >> 6] = v.lo;
+  __syncthreads();
+  return wave_parts<C>(h, l);
 }
 
 // ---------------------------------------------------------------- 2. Sturm counts
@@ -613,16 +645,18 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
     join(ar, dpp_z<0x141>(ar.p), dpp_z<0x141>(ar.s));
     join(ai, dpp_z<0x141>(ai.p), dpp_z<0x141>(ai.s));
     const dd yre = ar.result(), yim = ai.result();
-    // mu = x^H y: its rounding moves the residual along x only, which
-    // rescales x and does not turn it
-    const double m = block_rows_sum<C>(s, 0, fma(x.re, yre.hi, x.im * yim.hi));
-    mu = {m, 0.0};
+    // mu = x^H y and the residual r = y - mu x in double-double, r then rounded
+    dot2 t;
+    t.init();
+    t.add_prod(x.re, yre.hi); t.add(x.re * yre.lo);
+    t.add_prod(x.im, yim.hi); t.add(x.im * yim.lo);
+    mu = block_rows_sum<C>(s, 0, 5, t.result());
     if (done || it == max_refine) break;
-    // r = y - mu x
     auto resid = [&](dd y, double xv) __attribute__((always_inline)) {
-      double h, lo2;
-      two_prod(m, xv, h, lo2);
-      return __builtin_amdgcn_ldexp((y.hi - h) + (y.lo - lo2), -ex);
+      dot2 q;
+      q.init();
+      q.add_dd(y); q.add_prod(-mu.hi, xv); q.add(-mu.lo * xv);
+      return __builtin_amdgcn_ldexp(dd_val(q.result()), -ex);
     };
     const c64 rr = csel(r < n, c64{resid(yre, x.re), resid(yim, x.im)}, c64{0.0, 0.0});
     // correction c = W (T - sigma I)^{-1} W^H r
