@@ -47,6 +47,11 @@ namespace cbp {
 
 constexpr int BLK_MAX_WAVES = 8;
 
+// Powers of two that the norm of block_eig's matrix lies between (2^-464 is
+// 2e-140, 2^511 is 7e153); beyond them it returns a NaN vector, which the
+// callers turn into zero kernels and diagnostic flags.
+constexpr int BLK_MIN_EXP = -464, BLK_MAX_EXP = 511;
+
 // ---------------------------------------------------------------- explicit-FMA complex helpers
 __device__ inline c64 cfma(c64 a, c64 b, c64 s) {      // s + a b
   return {fma(a.re, b.re, fma(-a.im, b.im, s.re)), fma(a.re, b.im, fma(a.im, b.re, s.im))};
@@ -394,7 +399,7 @@ __device__ inline __attribute__((always_inline)) void block_tridiag(const blk_ws
 }
 
 // lambda_min / lambda_max of the Hermitian positive semidefinite matrix with
-// entries a (see block_tridiag), as small_extreme_ratio: the midpoints of
+// entries a (see block_tridiag; scaled as block_eig's), as small_extreme_ratio: the midpoints of
 // their brackets, the first wave bisecting one and the second the other.
 // Valid in every thread; 0 for a zero matrix.
 template <int C>
@@ -421,11 +426,13 @@ __device__ inline __attribute__((always_inline)) double block_extreme_ratio(cons
 // G in double-double.  Leaves the unit eigenvector in s.x (zero beyond n), the
 // number of refinement steps in *steps and T in s.ab with *ghi its scaled
 // Gershgorin bound; want_diag as in small_eig (the second eigenvalue in *lam1
-// and mu = x^H G x returned, else NaN).
+// and mu = x^H G x returned, else NaN).  ge: a power of two near G's largest
+// entry (frexp's exponent); the reduction takes G 2^-ge, so that its squares
+// and reciprocals stay in range down to the roundings of a G that is singular.
 template <int C, class Acc>
 __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, const Acc& acc, int n, bool want_diag,
                                                               double* lam1, int* steps, double* ghi,
-                                                              int max_refine) {
+                                                              int max_refine, int ge) {
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
   const int r = tid >> 3, q = tid & 7;
   *lam1 = __builtin_nan("");
@@ -441,7 +448,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
       a[i] = {0.0, 0.0};
       if (r < n && c < n) {
         const cdd v = acc.get(r, c);
-        a[i] = {v.re.hi, v.im.hi};
+        a[i] = {__builtin_amdgcn_ldexp(v.re.hi, -ge), __builtin_amdgcn_ldexp(v.im.hi, -ge)};
       }
       w[i] = {r == c ? 1.0 : 0.0, 0.0};
     }
@@ -451,6 +458,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
   int ex;
   double glo, tn;
   scale_tridiag(s, n, al_, bl_, &ex, &glo, ghi, &tn);
+  const int gx = ge + ex;      // of T against G's own eigenvalues
   if (n == 1) {
     if (tid < 64) s.x[tid] = {tid == 0 ? 1.0 : 0.0, 0.0};
     __syncthreads();
@@ -496,7 +504,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
   if (want_diag) {
     double lo1, hi1;
     bisect_minors(s, n, 2, glo, *ghi, tn, &lo1, &hi1);
-    *lam1 = __builtin_amdgcn_ldexp(0.5 * (lo1 + hi1), ex);
+    *lam1 = __builtin_amdgcn_ldexp(0.5 * (lo1 + hi1), gx);
   }
   // 3. sigma, the LDL^T factors of T - sigma I (every lane in step, entries
   // eight at a time; lane k keeps pivot k)
@@ -597,7 +605,8 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
     }
     const double* y = yb[SMALL_INVIT & 1];
     const double yl = y[l];
-    const double iy = 1.0 / sqrt(wsum(l < n ? yl * yl : 0.0));
+    const double iy = gx >= BLK_MIN_EXP && gx <= BLK_MAX_EXP ? 1.0 / sqrt(wsum(l < n ? yl * yl : 0.0))
+                                                             : __builtin_nan("");
     c64 t = {0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < C; ++i) {
@@ -656,7 +665,7 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
       dot2 q;
       q.init();
       q.add_dd(y); q.add_prod(-mu.hi, xv); q.add(-mu.lo * xv);
-      return __builtin_amdgcn_ldexp(dd_val(q.result()), -ex);
+      return __builtin_amdgcn_ldexp(dd_val(q.result()), -gx);
     };
     const c64 rr = csel(r < n, c64{resid(yre, x.re), resid(yim, x.im)}, c64{0.0, 0.0});
     // correction c = W (T - sigma I)^{-1} W^H r

@@ -259,7 +259,9 @@ __global__ __launch_bounds__(64 * C) void k_sample_dd(batch_ref br) {
     const gram_acc G{rho, k1, k2};
     double lam1, ghi;
     int steps;
-    const dd mu = block_eig<C>(w, G, N, diag != nullptr, &lam1, &steps, &ghi, SMALL_REFINE_MAX);
+    // G's largest entry is on its diagonal: rho11(0) or rho22(0)
+    const int ge = __builtin_amdgcn_frexp_exp(fmax(rho[0].re.hi, rho[k2].re.hi));
+    const dd mu = block_eig<C>(w, G, N, diag != nullptr, &lam1, &steps, &ghi, SMALL_REFINE_MAX, ge);
     const size_t base = ((size_t)pass * S + j) * N;
     if (tid < N) {
       const c64 xi = w.x[tid];
@@ -439,7 +441,8 @@ __device__ inline __attribute__((always_inline)) const c64* scale_solve(const Ac
   double hmax = 0.0;
   if (DD) {
     if (diag && tid < 64) hmax = wmax(tid < n ? dd_val(acc.get(tid, tid).re) : 0.0);
-    mu = block_eig<C>(bw, acc, n, diag != nullptr, &lam1, &steps, &ghi, max_refine);
+    // (unit vectors' cofactors: entries near one)
+    mu = block_eig<C>(bw, acc, n, diag != nullptr, &lam1, &steps, &ghi, max_refine, 0);
   } else {
     const float rn = 1.0f / (float)n;
     for (int e = tid; e < n * n; e += blockDim.x) {

@@ -55,13 +55,15 @@ __device__ inline cdd trial_gram(const cdd* rho, int K1, int K2, int n1, int r, 
 template <int C>
 __device__ inline double probe_ratio(const blk_ws& w, const cdd* rho, int K1, int K2, int n1, int n) {
   const int r = (int)threadIdx.x >> 3, q = threadIdx.x & 7;
+  // scaled by the power of two of G's largest entry, one of its diagonal's
+  const int ge = __builtin_amdgcn_frexp_exp(fmax(rho[0].re.hi, rho[K2].re.hi));
   c64 a[C];
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     const int c = q + 8 * i;
     const bool in = r < n && c < n;
     const cdd g = trial_gram(rho, K1, K2, n1, in ? r : 0, in ? c : 0);
-    a[i] = csel(in, c64{g.re.hi, g.im.hi}, c64{0.0, 0.0});
+    a[i] = csel(in, c64{__builtin_amdgcn_ldexp(g.re.hi, -ge), __builtin_amdgcn_ldexp(g.im.hi, -ge)}, c64{0.0, 0.0});
   }
   return block_extreme_ratio<C>(w, n, a);
 }
