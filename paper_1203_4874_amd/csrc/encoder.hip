@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256) void k_blur_pair(blur_args<T> g1, blur_args<T>
 // a workgroup converts 4096 of them, a thread in groups of 16 bytes of pixels
 // with neighbouring lanes on neighbouring groups, without an index division.  1080p RGB FP32: quantise 18.5 us and dequantise 19.7
 // (one element per thread and step, two 64-bit divisions each) -> 7.8 and 7.8 (4 TB/s).
-// Other images go row by row, four elements of a row per thread.
+// Other images go by rows (convert_rows).
 template <typename T>
 __device__ inline unsigned int quantize_one(T x, unsigned int mask) {
   const T v = rint(x * T(255));
@@ -449,36 +449,54 @@ __global__ __launch_bounds__(256) void k_dequantize_dense(const unsigned char* s
   }
 }
 
-// Rows of a pitched image: blockIdx.y + gridDim.y i counts rows over the
-// channels, blockIdx.x covers 1024 elements of a row.
-template <typename T>
-__global__ __launch_bounds__(256) void k_quantize(const T* src, int64_t sp, int64_t scs, unsigned char* dst, int64_t dp,
-                                                  int64_t dcs, int H, int W, int nch, unsigned int mask) {
-  for (int64_t row = blockIdx.y; row < (int64_t)H * nch; row += gridDim.y) {
-    const int c = (int)(row / H), y = (int)(row - (int64_t)c * H);
-    const T* s = src + (int64_t)c * scs + (int64_t)y * sp;
-    unsigned char* d = dst + (int64_t)c * dcs + (int64_t)y * dp;
+// Pitched images: channels blockIdx.z + gridDim.z i.  A row has 2^lx lanes (at
+// most 256) and a thread takes 2^lc columns of it, 256 apart (more than 1024
+// columns: blockIdx.x), in 4 / 2^lc rows, so narrow rows share a workgroup: one
+// row a workgroup would leave most of its lanes idle.  FP32 quantise of a
+// million rows of 8 in a pitched image: 22 us element by element with two 64-bit
+// divisions each, 508 a row at a time, 13 so; 100000 rows of 300: 71, 61, 49.
+struct row_split {
+  int lx, lc;
+};
+
+template <typename S, typename D, typename F>
+__device__ inline void convert_rows(const S* src, int64_t sp, int64_t scs, D* dst, int64_t dp, int64_t dcs, int H, int W,
+                                    int nch, row_split rs, F one) {
+  const int tid = threadIdx.x;
+  const int rows = 256 >> rs.lx, per = rows * (4 >> rs.lc);   // rows of the lanes, of the workgroup
+  const int x0 = (int)blockIdx.x * 1024 + (tid & ((1 << rs.lx) - 1));
+  for (int c = blockIdx.z; c < nch; c += gridDim.z) {
+    const S* s = src + (int64_t)c * scs;
+    D* d = dst + (int64_t)c * dcs;
+    for (int64_t y0 = (int64_t)blockIdx.y * per + (tid >> rs.lx); y0 < H; y0 += (int64_t)gridDim.y * per) {
+      S v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int x = (int)blockIdx.x * 1024 + i * 256 + (int)threadIdx.x;
-      if (x < W) d[x] = (unsigned char)quantize_one<T>(s[x], mask);
+      for (int i = 0; i < 4; ++i) {
+        const int64_t y = y0 + (i >> rs.lc) * rows;
+        const int x = x0 + (i & ((1 << rs.lc) - 1)) * 256;
+        if (x < W && y < H) v[i] = s[y * sp + x];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t y = y0 + (i >> rs.lc) * rows;
+        const int x = x0 + (i & ((1 << rs.lc) - 1)) * 256;
+        if (x < W && y < H) d[y * dp + x] = one(v[i]);
+      }
     }
   }
 }
 
 template <typename T>
+__global__ __launch_bounds__(256) void k_quantize(const T* src, int64_t sp, int64_t scs, unsigned char* dst, int64_t dp,
+                                                  int64_t dcs, int H, int W, int nch, row_split rs, unsigned int mask) {
+  convert_rows(src, sp, scs, dst, dp, dcs, H, W, nch, rs,
+               [&](T x) { return (unsigned char)quantize_one<T>(x, mask); });
+}
+
+template <typename T>
 __global__ __launch_bounds__(256) void k_dequantize(const unsigned char* src, int64_t sp, int64_t scs, T* dst,
-                                                    int64_t dp, int64_t dcs, int H, int W, int nch) {
-  for (int64_t row = blockIdx.y; row < (int64_t)H * nch; row += gridDim.y) {
-    const int c = (int)(row / H), y = (int)(row - (int64_t)c * H);
-    const unsigned char* s = src + (int64_t)c * scs + (int64_t)y * sp;
-    T* d = dst + (int64_t)c * dcs + (int64_t)y * dp;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int x = (int)blockIdx.x * 1024 + i * 256 + (int)threadIdx.x;
-      if (x < W) d[x] = (T)s[x] / T(255);
-    }
-  }
+                                                    int64_t dp, int64_t dcs, int H, int W, int nch, row_split rs) {
+  convert_rows(src, sp, scs, dst, dp, dcs, H, W, nch, rs, [](unsigned char q) { return (T)q / T(255); });
 }
 
 }  // namespace
@@ -538,8 +556,15 @@ bool dense(int64_t pitch, int64_t cs, int H, int W, int nch) {
   return pitch == W && (nch == 1 || cs == (int64_t)H * W);
 }
 bool aligned16(const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; }
+row_split split_rows(int W) {
+  row_split r = {0, W > 512 ? 2 : W > 256 ? 1 : 0};
+  while (r.lx < 8 && 1 << r.lx < W) ++r.lx;
+  return r;
+}
 dim3 row_grid(int H, int W, int nch) {
-  return dim3((W + 1023) / 1024, (unsigned)std::min<int64_t>((int64_t)H * nch, 65535));
+  const row_split r = split_rows(W);
+  const int64_t per = 1024 >> r.lx >> r.lc;
+  return dim3((W - 1) / 1024 + 1, (unsigned)std::min<int64_t>((H + per - 1) / per, 65535), std::min(nch, 65535));
 }
 
 }  // namespace
@@ -554,7 +579,7 @@ hipError_t launch_quantize(const T* src, int64_t sp, int64_t scs, unsigned char*
                        mask);
   else
     hipLaunchKernelGGL(k_quantize<T>, row_grid(H, W, nch), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch,
-                       mask);
+                       split_rows(W), mask);
   return hipGetLastError();
 }
 
@@ -566,7 +591,8 @@ hipError_t launch_dequantize(const unsigned char* src, int64_t sp, int64_t scs, 
     hipLaunchKernelGGL(k_dequantize_dense<T>, dim3((unsigned)((total + 4095) / 4096)), dim3(256), 0, st, src, dst,
                        total);
   else
-    hipLaunchKernelGGL(k_dequantize<T>, row_grid(H, W, nch), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch);
+    hipLaunchKernelGGL(k_dequantize<T>, row_grid(H, W, nch), dim3(256), 0, st, src, sp, scs, dst, dp, dcs, H, W, nch,
+                       split_rows(W));
   return hipGetLastError();
 }
 
