@@ -31,7 +31,6 @@ constexpr size_t kAlign = 256;
 constexpr size_t kScratchBytes = size_t(48) << 20;
 __device__ __align__(256) char scratch[kScratchBytes];
 constexpr size_t kLdsLimit = 160 * 1024;
-constexpr int kComputeUnits = 256;
 constexpr int32_t kKnownFlags =
     CBP_FLAG_GRAPH | CBP_FLAG_AUTOTUNE | CBP_FLAG_DIVIDE_B1 | CBP_FLAG_SCALE_K1 | CBP_FLAG_ONE_AXIS;
 

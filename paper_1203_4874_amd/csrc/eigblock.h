@@ -37,8 +37,16 @@
 // store to a dump slot.  Every sum is formed in an order that depends on n
 // alone (padding adds exact zeros), with explicit FMAs, so the result does
 // not depend on C.  A reflector takes ~1500 cycles at C = 2 .. 4 (6 cycles per
-// instruction: about 220 .. 280 of them and the two LDS round trips); at C = 5
-// and 8 two waves share a SIMD and it takes 2600 and 3100.
+// instruction: about 220 .. 280 of them and the two LDS round trips); from C = 5
+// on two waves share a SIMD and it takes up to twice as long.
+//
+// Many solves in a launch are bound by instructions instead, so what one wave
+// can do the others leave alone: the bisection, the factors and X are the first
+// wave's, and a wave whose rows are reduced takes part in Q only.  On every wave
+// / so, FP64 calls of one frame with kernels of 18 and 17 184 / 170 us, 21 and 20
+// 240 / 202 (six waves instead of eight), 32 and 32 325 / 303; of 400 frames of
+// 48x40 4.91 / 4.50 ms, 7.89 / 6.41, 15.5 / 14.7 (18 and 17 then 4.15 by
+// many_solves in recover.hip; the one-wave solver took 4.18, 6.83, 39.3).
 #pragma once
 
 #include "eigsmall.h"
@@ -288,7 +296,7 @@ __device__ inline void bisect_minors(const blk_ws& s, int n, int target, double 
 // of row r bisect the (r+1)-th smallest to 1/9 of its bracket per
 // round.  Returns it in every lane of the group (r < n), to 15 / 9^9 decades;
 // s.ab is the scaled T of scale_tridiag (only ratios of the values are used).
-__device__ inline double block_spectrum(const blk_ws& s, int n, double ghi) {
+__device__ inline __attribute__((always_inline)) double block_spectrum(const blk_ws& s, int n, double ghi) {
   const int r = (int)threadIdx.x >> 3, q = threadIdx.x & 7;
   const double top = log10(fmax(ghi, 1e-300));
   double lo = top - 15.0, hi = top;
@@ -312,6 +320,9 @@ template <int C, int I0, bool Q>
 __device__ inline __attribute__((always_inline)) void block_reflectors(const blk_ws& s, int n, c64* a, c64* w, c64& el) {
   const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6, r = tid >> 3, q = tid & 7;
   const int o1 = min(8 * I0 + 8, n - 1);
+  // rows below 8 I0 are reduced: their waves (one of them at least live) take
+  // part in Q alone, with no share in u^H p
+  const bool live_rows = __builtin_amdgcn_readfirstlane(wv) >= I0;
 #pragma unroll 1
   for (int o = I0 ? 8 * I0 : 1; o < o1; ++o) {
     __syncthreads();
@@ -338,31 +349,37 @@ __device__ inline __attribute__((always_inline)) void block_reflectors(const blk
     c64 p = {0.0, 0.0}, z = {0.0, 0.0};
 #pragma unroll
     for (int i = I0; i < C; ++i) {
-      p = cfma(a[i], u[i], p);
+      if (live_rows) p = cfma(a[i], u[i], p);
       if (Q) z = cfma(w[i], u[i], z);
     }
-    p = sum8(p);
-    p = {beta * p.re, beta * p.im};
-    s.v1[r] = p;
-    s.part[wv] = sum_rows(cdotr(ur, p));
+    if (live_rows) {
+      p = sum8(p);
+      p = {beta * p.re, beta * p.im};
+      s.v1[r] = p;
+      s.part[wv] = sum_rows(cdotr(ur, p));
+    } else {
+      s.part[wv] = 0.0;
+    }
     if (Q) {
       z = sum8(z);
       z = {beta * z.re, beta * z.im};
     }
     __syncthreads();
-    c64 wc[C];
+    if (live_rows) {
+      c64 wc[C];
 #pragma unroll
-    for (int i = I0; i < C; ++i) wc[i] = s.v1[q + 8 * i];
-    const double g = 0.5 * beta * wave_parts<C>(s.part);
-    const c64 wr = crfms(g, ur, p);
-    // A -= u w^H + w u^H, Q -= z u^H; the next column first
+      for (int i = I0; i < C; ++i) wc[i] = s.v1[q + 8 * i];
+      const double g = 0.5 * beta * wave_parts<C>(s.part);
+      const c64 wr = crfms(g, ur, p);
+      // A -= u w^H + w u^H, Q -= z u^H; the next column first
 #pragma unroll
-    for (int i = I0; i < C; ++i) {
-      wc[i] = crfms(g, u[i], wc[i]);
-      a[i] = cfms_bc(wr, u[i], cfms_bc(ur, wc[i], a[i]));
-      if (i == I0) {
-        c64* at = q + 8 * I0 == o ? s.v0 + r : s.dump + l;
-        *at = csel(r > o, a[I0], c64{0.0, 0.0});
+      for (int i = I0; i < C; ++i) {
+        wc[i] = crfms(g, u[i], wc[i]);
+        a[i] = cfms_bc(wr, u[i], cfms_bc(ur, wc[i], a[i]));
+        if (i == I0) {
+          c64* at = q + 8 * I0 == o ? s.v0 + r : s.dump + l;
+          *at = csel(r > o, a[I0], c64{0.0, 0.0});
+        }
       }
     }
     if (Q) {
@@ -425,8 +442,8 @@ __device__ inline __attribute__((always_inline)) double block_extreme_ratio(cons
 // Called by every thread of a workgroup of C waves, 8 C >= n.  acc.get(i, j):
 // G in double-double.  Leaves the unit eigenvector in s.x (zero beyond n), the
 // number of refinement steps in *steps and T in s.ab with *ghi its scaled
-// Gershgorin bound; want_diag as in small_eig (the second eigenvalue in *lam1
-// and mu = x^H G x returned, else NaN).  ge: a power of two near G's largest
+// Gershgorin bound; want_diag as in small_eig (the second eigenvalue in the first
+// wave's *lam1 and mu = x^H G x returned, else NaN).  ge: a power of two near G's largest
 // entry (frexp's exponent); the reduction takes G 2^-ge, so that its squares
 // and reciprocals stay in range down to the roundings of a G that is singular.
 template <int C, class Acc>
@@ -498,19 +515,23 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
     const c64 v = s.M[in ? (size_t)c * ldw + r : 0];
     wt[i] = csel(in, conj(v), c64{0.0, 0.0});
   }
-  // 2. the smallest eigenvalue (and with diagnostics the second)
-  double lo0, hi0;
-  bisect_minors<true>(s, n, 1, glo, *ghi, tn, &lo0, &hi0);
-  if (want_diag) {
-    double lo1, hi1;
-    bisect_minors(s, n, 2, glo, *ghi, tn, &lo1, &hi1);
-    *lam1 = __builtin_amdgcn_ldexp(0.5 * (lo1 + hi1), gx);
-  }
-  // 3. sigma, the LDL^T factors of T - sigma I (every lane in step, entries
-  // eight at a time; lane k keeps pivot k)
-  const double sigma = lo0 - 16.0 * n * 2.2e-16 * tn;
-  const double pivmin = 1e-300 + 2.2e-16 * 2.2e-16 * tn;
-  {
+  __syncthreads();   // X takes the place of W
+  // The first wave alone (the others wait at the barrier after X, where they
+  // leave the SIMDs to other workgroups):
+  double* X = (double*)s.M;
+  if (__builtin_amdgcn_readfirstlane(wv) == 0) {
+    // 2. the smallest eigenvalue (and with diagnostics the second)
+    double lo0, hi0;
+    bisect_minors<true>(s, n, 1, glo, *ghi, tn, &lo0, &hi0);
+    if (want_diag) {
+      double lo1, hi1;
+      bisect_minors(s, n, 2, glo, *ghi, tn, &lo1, &hi1);
+      *lam1 = __builtin_amdgcn_ldexp(0.5 * (lo1 + hi1), gx);
+    }
+    // 3. sigma, the LDL^T factors of T - sigma I (every lane in step, entries
+    // eight at a time; lane k keeps pivot k)
+    const double sigma = lo0 - 16.0 * n * 2.2e-16 * tn;
+    const double pivmin = 1e-300 + 2.2e-16 * 2.2e-16 * tn;
     double2 f[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) f[u] = s.ab[u];
@@ -533,17 +554,13 @@ __device__ inline __attribute__((always_inline)) dd block_eig(const blk_ws& s, c
     }
     const double bs = __builtin_amdgcn_ldexp(bl_, -ex);
     if (l >= n) idl = 0.0;
-    s.fac[l] = double2{idl, l + 1 < n ? bs * idl : 0.0};   // every wave stores the same values
-  }
-  __syncthreads();
-  // X = (T - sigma I)^{-1}, column c in lane c of the first wave: L y = e_c,
-  // then L^T z = D^{-1} y, eight rows at a time (rows past n are zero)
-  double* X = (double*)s.M;
-  if (tid < 64) {
+    s.fac[l] = double2{idl, l + 1 < n ? bs * idl : 0.0};
+    wave_sync();
+    // X = (T - sigma I)^{-1}, column c in lane c: L y = e_c, then L^T z =
+    // D^{-1} y, eight rows at a time (rows past n are zero)
     const int nb = (n + 7) >> 3;
     double* col = l < n ? X + l : (double*)(s.dump + l);
     const int ldc = l < n ? ldw : 0;
-    double2 f[8];
     double v = 0.0, lp = 0.0;
 #pragma unroll 1
     for (int k0 = 0; k0 < 8 * nb; k0 += 8) {

@@ -26,6 +26,8 @@ enum queue_id {
   Q_ROW_INV, Q_TWID, Q_KRDFT, Q_ROWS, Q_COUNT
 };
 
+constexpr int kComputeUnits = 256;
+
 // Frames per batched launch (the item prefix sums of one launch sit in LDS).
 constexpr int BATCH_CHUNK = 256;
 

@@ -230,9 +230,12 @@ __global__ __launch_bounds__(SMALL_NT) void k_sample(batch_ref br) {
 
 // The same for the forms with a double-double Gram (FP64, MIXED): one
 // workgroup of C waves per item (eigblock.h), Newton refined.
-// Bound by the dependent chain of the reduction's n - 2 reflectors.
-template <int C>
-__global__ __launch_bounds__(64 * C) void k_sample_dd(batch_ref br) {
+// Bound by the dependent chain of the reduction's n - 2 reflectors.  OCC: waves
+// a SIMD is to hold.  Five waves of 256 registers leave a CU one workgroup; with
+// 128, three share it, their registers spilled: one solve takes longer, many take
+// less together (see many_solves).
+template <int C, int OCC>
+__global__ __launch_bounds__(64 * C, OCC) void k_sample_dd(batch_ref br) {
   extern __shared__ __attribute__((aligned(16))) char sm_sdd[];
   __shared__ c64 twq[CBP_MAX_S];
   __shared__ double lmax_s;
@@ -1093,21 +1096,34 @@ hipError_t launch_gram(const batch_ref& br, int grid, hipStream_t st) {
 // Waves of the double-double solves of a launch whose largest order is n:
 // eight rows per wave, so the smallest built instance that holds it (more
 // waves would only wait at the barriers: order 20 takes 26 us on three waves
-// and 33 on four); a solve's result does not depend on which one runs it.
+// and 33 on four, a call of 400 frames of order 41 6.4 ms on six and 7.9 on
+// eight); a solve's result does not depend on which one runs it.
 template <template <int> class K>
 static void pick_waves(int n, dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int arg) {
   if (n <= 16) K<2>::run(grid, lds, st, br, arg);
   else if (n <= 24) K<3>::run(grid, lds, st, br, arg);
   else if (n <= 32) K<4>::run(grid, lds, st, br, arg);
   else if (n <= 40) K<5>::run(grid, lds, st, br, arg);
+  else if (n <= 48) K<6>::run(grid, lds, st, br, arg);
   else K<8>::run(grid, lds, st, br, arg);
 }
 
+// Sample solves of a launch from which the instance with more workgroups a CU
+// is the faster one, eight a CU (orders 33 to 40).  Calls of 48x40 FP64 frames,
+// order 35, one wave of 256 / 128 registers a lane: 20 frames (720 solves) 348 /
+// 369 us, 60 frames (2160) 806 / 800, 400 frames (two launches of 7200) 4497 / 4149.
+constexpr unsigned many_solves = 8 * kComputeUnits;
+
 template <int C>
 struct run_sample_dd {
-  static const void* kernel() { return (const void*)k_sample_dd<C>; }
+  static constexpr bool two = C == 5;
+  static const void* kernel(bool many) {
+    return many && two ? (const void*)k_sample_dd<C, two ? 4 : 1> : (const void*)k_sample_dd<C, 1>;
+  }
   static void run(dim3 grid, size_t lds, hipStream_t st, const batch_ref& br, int) {
-    hipLaunchKernelGGL(k_sample_dd<C>, grid, dim3(64 * C), lds, st, br);
+    batch_ref b = br;
+    void* args[] = {(void*)&b};
+    (void)hipLaunchKernel(kernel(grid.x >= many_solves), grid, dim3(64 * C), args, lds, st);
   }
 };
 
@@ -1145,10 +1161,12 @@ hipError_t launch_finalize(const batch_ref& br, int grid, int maxS, int learned,
 
 void set_recover_attrs() {
   const void* fns[] = {(const void*)k_sample, (const void*)k_finalize<4, false>,
-                       run_sample_dd<2>::kernel(), run_sample_dd<3>::kernel(), run_sample_dd<4>::kernel(),
-                       run_sample_dd<5>::kernel(), run_sample_dd<8>::kernel(),
+                       run_sample_dd<2>::kernel(false), run_sample_dd<3>::kernel(false),
+                       run_sample_dd<4>::kernel(false), run_sample_dd<5>::kernel(false),
+                       run_sample_dd<5>::kernel(true), run_sample_dd<6>::kernel(false),
+                       run_sample_dd<8>::kernel(false),
                        run_finalize_dd<2>::kernel(), run_finalize_dd<3>::kernel(), run_finalize_dd<4>::kernel(),
-                       run_finalize_dd<5>::kernel(), run_finalize_dd<8>::kernel()};
+                       run_finalize_dd<5>::kernel(), run_finalize_dd<6>::kernel(), run_finalize_dd<8>::kernel()};
   for (const void* f : fns) hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 }
 
