@@ -501,18 +501,29 @@ __global__ __launch_bounds__(256) void k_dequantize(const unsigned char* src, in
 
 }  // namespace
 
+// Frames of one turn of the launches: a launch holds fewer than 2^32 threads,
+// and a frame has 2S probes of 128 and two first draws of 256.  Half of that.
+constexpr int draw_slice(int S) { return (1 << 23) / std::max(S, 2); }
+
 hipError_t launch_draw_pairs(unsigned long long seed, long long frame0, int nframes, int k1, int k2, int S,
                              double* K1s, double* K2s, int* attempts, double* min_ratio, hipStream_t st) {
   const size_t lds = draw_lds_bytes(k1, k2);
-  hipLaunchKernelGGL(k_draw_first, dim3(2 * (unsigned)nframes), dim3(256), 0, st, seed, frame0, k1, k2, K1s, K2s, attempts,
-                     min_ratio);
-  if (k1 + k2 > 2) {   // two 1 x 1 kernels have no Sylvester system
-    hipLaunchKernelGGL(k_draw_probe, dim3((unsigned)nframes * 2 * S), dim3(128), lds, st, k1, k2, S, K1s, K2s,
-                       attempts, min_ratio);
-    hipLaunchKernelGGL(k_draw_again, dim3(nframes), dim3(SMALL_NT), lds, st, seed, frame0, k1, k2, S, K1s, K2s,
-                       attempts, min_ratio);
+  for (int f = 0; f < nframes;) {
+    const int n = std::min(nframes - f, draw_slice(S));
+    double* K1 = K1s + (size_t)f * k1 * k1;
+    double* K2 = K2s + (size_t)f * k2 * k2;
+    int* at = attempts + f;
+    double* mr = min_ratio ? min_ratio + f : nullptr;
+    hipLaunchKernelGGL(k_draw_first, dim3(2 * n), dim3(256), 0, st, seed, frame0 + f, k1, k2, K1, K2, at, mr);
+    if (k1 + k2 > 2) {   // two 1 x 1 kernels have no Sylvester system
+      hipLaunchKernelGGL(k_draw_probe, dim3(n * 2 * S), dim3(128), lds, st, k1, k2, S, K1, K2, at, mr);
+      hipLaunchKernelGGL(k_draw_again, dim3(n), dim3(SMALL_NT), lds, st, seed, frame0 + f, k1, k2, S, K1, K2, at, mr);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    f += n;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 void set_encoder_attrs() {
