@@ -70,20 +70,22 @@ __device__ inline double draw_entry(unsigned long long seed, unsigned long long 
   return ((double)(x >> 11) + 0.5) * 0x1p-53;
 }
 
-// One kernel into K (LDS, k x k): entries in parallel, the sum in entry order
-// on lane 0, then the division.
+// One kernel into K (LDS, k x k) by threads tid of nt: entries in parallel, the
+// sum in entry order on thread 0, then the division.  Every thread of the
+// workgroup calls it (barriers); !on: a share without a kernel.
 __device__ inline void draw_kernel(double* K, int k, unsigned long long seed, unsigned long long frame, int stream,
-                                   int attempt, double* sum_slot) {
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) K[e] = draw_entry(seed, frame, stream, attempt, e);
+                                   int attempt, double* sum_slot, int tid, int nt, bool on = true) {
+  const int kk = on ? k * k : 0;
+  for (int e = tid; e < kk; e += nt) K[e] = draw_entry(seed, frame, stream, attempt, e);
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     double s = 0.0;
-    for (int e = 0; e < k * k; ++e) s += K[e];
+    for (int e = 0; e < kk; ++e) s += K[e];
     *sum_slot = s;
   }
   __syncthreads();
   const double s = *sum_slot;
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) K[e] = K[e] / s;
+  for (int e = tid; e < kk; e += nt) K[e] = K[e] / s;
   __syncthreads();
 }
 
@@ -172,18 +174,26 @@ __device__ inline void sylvester_gram(const draw_lds& d, int k1, int k2, int S, 
 
 constexpr int DRAW_FAILED = 0x40000000;   // in attempts[f] between the launches
 
-// Attempt 0 of every frame.  One workgroup per kernel (2 f + stream - 1),
-// bound by the ordered sum of its entries.
-__global__ __launch_bounds__(256) void k_draw_first(unsigned long long seed, long long frame0, int k1, int k2,
+// Attempt 0 of every frame: kernels 2 f + stream - 1 < n2, W waves each, 4 / W to
+// a workgroup, bound by the ordered sum of their entries.  W = 1 serves kernels
+// of at most 64 entries: a million pairs of 2x2 and 1x1 are bound by the number
+// of workgroups.
+constexpr int kDrawWave = 8;   // largest kernel of one wave
+template <int W>
+__global__ __launch_bounds__(256) void k_draw_first(unsigned long long seed, long long frame0, int n2, int k1, int k2,
                                                     double* K1s, double* K2s, int* attempts, double* min_ratio) {
-  __shared__ double K[CBP_MAX_K * CBP_MAX_K];
-  __shared__ double sum_slot;
-  const int f = blockIdx.x >> 1, s = 1 + (blockIdx.x & 1);
+  constexpr int PER = 4 / W, NT = 64 * W;
+  __shared__ double K[PER][W == 1 ? kDrawWave * kDrawWave : CBP_MAX_K * CBP_MAX_K];
+  __shared__ double sum_slot[PER];
+  const int h = (int)threadIdx.x / NT, tid = (int)threadIdx.x - h * NT;
+  const int i = (int)blockIdx.x * PER + h, f = i >> 1, s = 1 + (i & 1);
+  const bool on = i < n2;
   const int k = s == 1 ? k1 : k2;
-  draw_kernel(K, k, seed, (unsigned long long)(frame0 + f), s, 0, &sum_slot);
+  draw_kernel(K[h], k, seed, (unsigned long long)(frame0 + f), s, 0, &sum_slot[h], tid, NT, on);
+  if (!on) return;
   double* out = s == 1 ? K1s + (size_t)f * k1 * k1 : K2s + (size_t)f * k2 * k2;
-  for (int e = threadIdx.x; e < k * k; e += blockDim.x) out[e] = K[e];
-  if (s == 1 && threadIdx.x == 0) {
+  for (int e = tid; e < k * k; e += NT) out[e] = K[h][e];
+  if (s == 1 && tid == 0) {
     attempts[f] = 0;
     if (min_ratio) min_ratio[f] = 1.0;
   }
@@ -220,36 +230,42 @@ __global__ __launch_bounds__(128) void k_draw_probe(int k1, int k2, int S, const
   }
 }
 
-// Attempts 1, 2, ... of the frames whose first pair failed, one wave each.
+// Attempts 1, 2, ... of the frames whose first pair failed, one wave each; a
+// workgroup looks `per` <= 64 frames over.
 __global__ __launch_bounds__(SMALL_NT) void k_draw_again(unsigned long long seed, long long frame0, int k1, int k2,
                                                           int S, double* K1s, double* K2s, int* attempts,
-                                                          double* min_ratio) {
+                                                          double* min_ratio, int nframes, int per) {
   extern __shared__ __attribute__((aligned(16))) char sm_draw[];
-  const int f = blockIdx.x, l = threadIdx.x;
-  if (!(attempts[f] & DRAW_FAILED)) return;
-  const unsigned long long frame = (unsigned long long)(frame0 + f);
-  draw_lds d = draw_carve(sm_draw, k1, k2);
-  const int n = k1 + k2 - 2;
-  int found = -1;
-  double worst = 1.0;
-  for (int a = 1; a < kMaxAttempts && found < 0; ++a) {
-    draw_kernel(d.K1, k1, seed, frame, 1, a, d.sum_slot);
-    draw_kernel(d.K2, k2, seed, frame, 2, a, d.sum_slot);
-    worst = 1.0;
-    for (int pass = 0; pass < 2; ++pass)
-      for (int j = 0; j < S; ++j) {
-        sylvester_gram(d, k1, k2, S, pass, j);
-        const double r = small_extreme_ratio(d.w, n);
-        worst = fmin(worst, r);
-        __syncthreads();
-      }
-    if (worst > kSylvMin) found = a;
-  }
-  for (int e = l; e < k1 * k1; e += SMALL_NT) K1s[(size_t)f * k1 * k1 + e] = d.K1[e];
-  for (int e = l; e < k2 * k2; e += SMALL_NT) K2s[(size_t)f * k2 * k2 + e] = d.K2[e];
-  if (l == 0) {
-    attempts[f] = found;
-    if (min_ratio) min_ratio[f] = worst;
+  const int l = threadIdx.x, f0 = (int)blockIdx.x * per;
+  const bool mine = l < per && f0 + l < nframes;
+  unsigned long long failed = __builtin_amdgcn_ballot_w64(mine && (attempts[mine ? f0 + l : f0] & DRAW_FAILED));
+  for (; failed; failed &= failed - 1) {
+    const int f = f0 + __builtin_ctzll(failed);
+    const unsigned long long frame = (unsigned long long)(frame0 + f);
+    draw_lds d = draw_carve(sm_draw, k1, k2);
+    const int n = k1 + k2 - 2;
+    int found = -1;
+    double worst = 1.0;
+    for (int a = 1; a < kMaxAttempts && found < 0; ++a) {
+      draw_kernel(d.K1, k1, seed, frame, 1, a, d.sum_slot, l, SMALL_NT);
+      draw_kernel(d.K2, k2, seed, frame, 2, a, d.sum_slot, l, SMALL_NT);
+      worst = 1.0;
+      for (int pass = 0; pass < 2; ++pass)
+        for (int j = 0; j < S; ++j) {
+          sylvester_gram(d, k1, k2, S, pass, j);
+          const double r = small_extreme_ratio(d.w, n);
+          worst = fmin(worst, r);
+          __syncthreads();
+        }
+      if (worst > kSylvMin) found = a;
+    }
+    for (int e = l; e < k1 * k1; e += SMALL_NT) K1s[(size_t)f * k1 * k1 + e] = d.K1[e];
+    for (int e = l; e < k2 * k2; e += SMALL_NT) K2s[(size_t)f * k2 * k2 + e] = d.K2[e];
+    if (l == 0) {
+      attempts[f] = found;
+      if (min_ratio) min_ratio[f] = worst;
+    }
+    __syncthreads();   // the next frame's draw fills the same LDS
   }
 }
 
@@ -514,10 +530,17 @@ hipError_t launch_draw_pairs(unsigned long long seed, long long frame0, int nfra
     double* K2 = K2s + (size_t)f * k2 * k2;
     int* at = attempts + f;
     double* mr = min_ratio ? min_ratio + f : nullptr;
-    hipLaunchKernelGGL(k_draw_first, dim3(2 * n), dim3(256), 0, st, seed, frame0 + f, k1, k2, K1, K2, at, mr);
+    if (std::max(k1, k2) <= kDrawWave)
+      hipLaunchKernelGGL(k_draw_first<1>, dim3((n + 1) / 2), dim3(256), 0, st, seed, frame0 + f, 2 * n, k1, k2, K1, K2,
+                         at, mr);
+    else
+      hipLaunchKernelGGL(k_draw_first<4>, dim3(2 * n), dim3(256), 0, st, seed, frame0 + f, 2 * n, k1, k2, K1, K2, at, mr);
     if (k1 + k2 > 2) {   // two 1 x 1 kernels have no Sylvester system
       hipLaunchKernelGGL(k_draw_probe, dim3(n * 2 * S), dim3(128), lds, st, k1, k2, S, K1, K2, at, mr);
-      hipLaunchKernelGGL(k_draw_again, dim3(n), dim3(SMALL_NT), lds, st, seed, frame0 + f, k1, k2, S, K1, K2, at, mr);
+      // (65536 frames and more: workgroups that only look cost more than the looking)
+      const int per = (n + 65535) / 65536;
+      hipLaunchKernelGGL(k_draw_again, dim3((n + per - 1) / per), dim3(SMALL_NT), lds, st, seed, frame0 + f, k1, k2, S,
+                         K1, K2, at, mr, n, per);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
