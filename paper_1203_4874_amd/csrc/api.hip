@@ -155,13 +155,20 @@ constexpr tuning kDefaultTuning = {0, 0, 0, 3};
 constexpr int kRowItemsPerFrame = 384;
 constexpr int kRowWgPerCu = 4;   // workgroups per CU of the split row pass
 
-// A call with fewer fused row-pass items than this runs the split row pass:
-// single rows spread over the chip and the column fold reads the frames again
-// (they sit in the caches), instead of items of several rows in turn on part
-// of the chip.  Whole calls, fused / split: 1000x180 FP32 112 / 86 us, 480x640
-// RGB 134 / 125, 1080p RGB FP32 (411 items) 313 / 305, two of them 404 / 416;
-// 1080p RGB FP64 (429) 371 / 381.
-constexpr int split_row_items(int esize) { return esize == 4 ? 512 : 400; }
+// Does a call run the split row pass?  Single rows then spread over the chip and
+// the column fold reads the frames again (from the caches), instead of items of
+// several rows in turn on part of the chip.  FP32 calls turn on the items there
+// are to fill the chip with (1024 row workgroups at once), FP64 calls, whose
+// second reading is twice the bytes, on the pixels.  Time fused / split of whole
+// calls, one to sixteen frames from 240x320 to 2000x2000 and 2000x100, grey and
+// RGB, k 5 and 13, mean (least .. most): FP32, under 512 items 1.14 (1.02 .. 1.36),
+// 512 to 800 1.04 (0.98 .. 1.09), 800 to 1600 1.01 (0.96 .. 1.08), 1600 to 3000 0.98
+// (0.95 .. 1.02), more 0.93.  FP64, under 2 Mi pixels 1.09 (0.99 .. 1.37), 2 to 4 Mi
+// 1.05 (0.98 .. 1.17), 4 to 6 Mi 1.03 (0.94 .. 1.10), more 0.99 (0.92 .. 1.08), frames
+// of 6 Mi and more alone 0.96.
+bool split_rows(int esize, int64_t items, int64_t pixels) {
+  return esize == 4 ? items < 800 : pixels < (int64_t)4 << 20;
+}
 
 // Does a strip of cw columns of length Py fit the column pass?
 bool col_fits(int Py, int cw, int twn, int esize) {
@@ -484,7 +491,7 @@ struct chunk_view {
   int colGroups;        // the column filter's row groups of the frames (bit g set for group g)
   int gram_fmt;   // gram_format() of the call's precision
   int maxStride;  // largest Hmax / Wmax (matrix-core Gram staging)
-  bool split;     // the row pass takes single rows and the first launch folds (split_row_items)
+  bool split;     // the row pass takes single rows and the first launch folds (split_rows)
   front_grid front;   // the first launch
   bool finLean;   // no frame's scale solve refines or records diagnostics
   const void* mlp;  // the learned form's network (device mlp blob) or NULL
@@ -657,10 +664,12 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
     cv.gram_fmt = gram_format(o->precision);
     cv.mlp = o->learned ? o->mlp_blob : nullptr;
     cv.finLean = true;
+    int64_t pixels = 0;
     for (int i = 0; i < cnt; ++i) {
       const frame_desc& fd = descs[f0 + i];
       cv.finLean = cv.finLean && solve_refine_max(fd.variant) == 0 && fd.diag == nullptr && !(fd.variant & VAR_ONE_AXIS);
       const frame_plan& p = bb->plans[f0 + i];
+      pixels += (int64_t)p.nch * p.Hmax * p.Wmax;
       cv.maxStride = std::max({cv.maxStride, p.Hmax, p.Wmax});
       cv.maxN = std::max(cv.maxN, p.N);
       cv.maxS = std::max(cv.maxS, p.S);
@@ -672,7 +681,7 @@ cbp_status build_batch(const std::vector<frame_req>& reqs, const cbp_options* o,
       cv.colGroups |= 1 << col_group_size(p.Py);
     }
     const int esize = dtype == CBP_F32 ? 4 : 8;
-    cv.split = bb->latent && cv.items[Q_ROW_FWD] < split_row_items(dtype == CBP_F32 ? 4 : 8);
+    cv.split = bb->latent && split_rows(esize, cv.items[Q_ROW_FWD], pixels);
     {
       // four fold items per workgroup
       auto grid4 = [&](int items) { return grid_for((items + 3) / 4, cap); };

@@ -462,8 +462,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
   }
 }
 
-// The split row pass, a call's first launch (a small call, see split_row_items
-// in api.hip): g.rows workgroups take single rows (channel, y), g.fold fold the
+// The split row pass, a call's first launch (a small call, see split_rows in
+// api.hip): g.rows workgroups take single rows (channel, y), g.fold fold the
 // columns from the frames themselves (k_front's fold, the same bits), g.twid
 // fill the twiddle tables.  A row is a workgroup of its own instead of a
 // turn of one residue's: 480x640 (168 items of three rows) 22.7 us and 4.7 for
