@@ -355,8 +355,8 @@ cbp_status cbp_estimate_kernel_sizes(const cbp_image* b1, const cbp_image* b2, c
  * nearly share a root); at most 64 attempts.  K1s (nframes * k1 * k1 doubles)
  * and K2s receive the pairs, attempts[f] (device int32) the attempt used or
  * -1 when none passed (the last draw is kept), min_ratio[f] (device, nullable)
- * the smallest ratio of the kept pair.  One wave per frame; asynchronous on
- * `stream`.  Errors: CBP_E_INVALID (NULL buffers, nframes < 1, frame0 < 0,
+ * the smallest ratio of the kept pair.  The first attempt's systems run side by
+ * side, further attempts one wave per frame; asynchronous on `stream`.  Errors: CBP_E_INVALID (NULL buffers, nframes < 1, frame0 < 0,
  * S outside 1..32), CBP_E_SHAPE (k outside 1..32). */
 cbp_status cbp_draw_kernel_pairs(uint64_t seed, int64_t frame0, int32_t nframes, int32_t k1, int32_t k2,
                                  int32_t samples, double* K1s, double* K2s, int32_t* attempts, double* min_ratio,

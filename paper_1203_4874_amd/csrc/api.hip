@@ -518,7 +518,7 @@ hipError_t enqueue_chunk(dev_state& ds, const chunk_view& cv, bool latent, bool 
   else if (cv.split) CBP_TRY(launch_rows_front<T>(br(Q_ROWS), cv.front, cv.maxPx, cv.maxTwx, ih, st));
   else CBP_TRY(launch_front<T>(br(Q_TWID), cv.front, ih, st));
   if (diag) CBP_TRY(launch_diag_init(br(Q_DIAG), cv.grid[Q_DIAG], st));
-  if (latent && !cv.split) CBP_TRY(launch_row_fwd<T>(br(Q_ROW_FWD), cv.grid[Q_ROW_FWD], cv.maxPx, cv.maxTwx, 1, st));
+  if (latent && !cv.split) CBP_TRY(launch_row_fwd<T>(br(Q_ROW_FWD), cv.grid[Q_ROW_FWD], cv.maxPx, cv.maxTwx, st));
   CBP_TRY(launch_eval_cols(br(Q_EVAL_COLS), cv.grid[Q_EVAL_COLS], st));
   // join: the Gram needs the row evaluation (and the column pass the row spectra)
   if (cv.gram_fmt < 0) CBP_TRY(launch_gram(br(Q_GRAM), cv.grid[Q_GRAM], st));

@@ -44,7 +44,6 @@ template <typename T> CBP_HD T norm2(cplx<T> a) { return a.re * a.re + a.im * a.
 template <typename T> CBP_HD cplx<T> cmulc(cplx<T> a, cplx<T> b) {
   return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
 }
-template <typename T, typename U> CBP_HD cplx<T> cast(cplx<U> a) { return {T(a.re), T(a.im)}; }
 
 using c64 = cplx<double>;
 using c32 = cplx<float>;
@@ -121,10 +120,8 @@ struct cdd {
   dd re, im;
 };
 
-CBP_HD cdd cdd_add(cdd a, cdd b) { return {dd_add(a.re, b.re), dd_add(a.im, b.im)}; }
 CBP_HD cdd cdd_conj(cdd a) { return {a.re, dd_neg(a.im)}; }
 CBP_HD cdd cdd_neg(cdd a) { return {dd_neg(a.re), dd_neg(a.im)}; }
-CBP_HD c64 cdd_val(cdd a) { return {dd_val(a.re), dd_val(a.im)}; }
 
 // ---------------------------------------------------------------- small DFT constants
 // cos and sin of 2 pi k / R for the odd radices (values of the circular

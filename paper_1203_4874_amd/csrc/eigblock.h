@@ -15,8 +15,10 @@
 //    product instead of n - 2 reflectors with a wave sum each.
 //  * The Sturm counts use the leading principal minors' two-term recurrence
 //    p_k = (a_k - t) p_{k-1} - b_{k-1}^2 p_{k-2} (one dependent FMA per step
-//    and no reciprocal), rescaled by a power of two every four steps; the
-//    number of sign changes is the number of eigenvalues below t.  The
+//    and no reciprocal), rescaled by a power of two every eight steps (T has a
+//    norm near 1 and b^2 is kept above 2^-200, so eight steps shrink the pair by
+//    2^-800 at most); the number of sign changes is the number of eigenvalues
+//    below t.  The
 //    bracket starts at [0, min a_k] (Rayleigh; the matrix is positive
 //    semidefinite) instead of the Gershgorin interval, with a graded first
 //    round: a pair of noiseless frames' smallest eigenvalues sit at rounding

@@ -435,54 +435,6 @@ __device__ inline double small_spectrum(const small_ws& s, int n) {
   return exp10(0.5 * (lo + hi));
 }
 
-// ---------------------------------------------------------------- Gauss-Jordan inverse
-// (used by the learned form's assembly)
-// s.A <- s.A^{-1} for a Hermitian positive definite matrix (Gauss-Jordan, no
-// pivoting; row and column k are staged in s.u / s.w before the update).
-__device__ inline void small_gj_inverse(small_ws& s, int n) {
-  const int l = threadIdx.x;
-  const float rn = 1.0f / (float)n;
-  const int nn = n * n;
-  c64* __restrict__ A = s.A;
-  c64* __restrict__ col = s.w;
-  c64* __restrict__ row = s.u;
-  for (int k = 0; k < n; ++k) {
-    if (l < n) {
-      col[l] = A[l * n + k];
-      row[l] = A[k * n + l];
-    }
-    wave_sync();
-    const double ip = rcp_nr(row[k].re);
-    for (int e0 = 0; e0 < nn; e0 += 8 * SMALL_NT) {
-      c64 av[8], cv[8], rv[8];
-      int ii[8], jj[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int e = e0 + l + t * SMALL_NT;
-        split_index(e, n, rn, ii[t], jj[t]);
-        if (e < nn) {
-          av[t] = A[e];
-          cv[t] = col[ii[t]];
-          rv[t] = row[jj[t]];
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int e = e0 + l + t * SMALL_NT;
-        if (e < nn) {
-          c64 v;
-          if (ii[t] == k && jj[t] == k) v = {ip, 0.0};
-          else if (ii[t] == k) v = ip * rv[t];
-          else if (jj[t] == k) v = -ip * cv[t];
-          else v = av[t] - ip * (cv[t] * rv[t]);
-          A[e] = v;
-        }
-      }
-    }
-    wave_sync();
-  }
-}
-
 // ---------------------------------------------------------------- 3. tridiagonal solves
 // The recurrences below are serial in k.  Every lane runs them in step on the
 // same values read from LDS (broadcast reads, eight entries per batch, so the

@@ -269,7 +269,7 @@ __device__ __attribute__((always_inline)) inline void fetch_rows(const frame_des
 
 // Rows y of both frames of channel ch, packed as B1 + i B2 in a (LDS, zero
 // beyond each frame; a barrier since its store): the FFT and the two half
-// spectra, and with gy the fold of both rows modulo S into gy[frame][S] by the
+// spectra, and the fold of both rows modulo S into gy[frame][S] by the
 // last wave (the caller's DFT of it, row_eval, needs no more).  twf: the plan's
 // pass tables.  Ends with a barrier.
 //
@@ -286,7 +286,7 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
   const int N = px.N, hx = d.hx, S = d.S;
   const bool in1 = y < d.H1, in2 = y < d.H2;
   const int G = 128 / S;
-  if (gy) {
+  {
     const int fr = threadIdx.x >> 7, l = threadIdx.x & 127;
     double acc = 0.0;
     if ((fr ? in2 : in1) && l < G * S) acc = fold_strided((const T*)a + fr, 2, l, S * G, fr ? d.W2 : d.W1);
@@ -294,7 +294,7 @@ __device__ __attribute__((always_inline)) inline void row_transform(const frame_
     if (px.npass == 0) __syncthreads();   // N = 1
   }
   ip_fft<-1, 256, ROW_MAXE>(a, N, px, twf, 0);
-  if (gy) {
+  {
     const int lane = (int)threadIdx.x - 192, fr = lane >= S, l = fr ? lane - S : lane;
     if (lane >= 0 && lane < 2 * S) {
       double sr = fpart_l[fr][l];
@@ -333,8 +333,8 @@ __device__ __attribute__((always_inline)) inline void row_eval(const frame_desc&
 // as B1 + i B2 and transformed; while the rows pass, the workgroup folds them
 // (the column fold of fold_item: the same rows of the same residue and
 // group, summed in increasing y in FP64, hence the same bits) and writes
-// the group's partial sums, so the frames are read once.  With with_ey, the
-// unit-circle evaluation of both rows (fold modulo S and S-point DFT, as
+// the group's partial sums, so the frames are read once.  The unit-circle
+// evaluation of both rows (fold modulo S and S-point DFT, as
 // eval_rows_item: the same lanes, the same order, hence the same bits) is taken
 // from the row in LDS; the DFTs of up to EY_ROWS rows run together, over all
 // threads, instead of on 2 S of them while the row waits, with two barriers of
@@ -346,7 +346,7 @@ static_assert(CBP_MAX_FFT_F32 <= 8 * 256 && CBP_MAX_FFT_F64 <= 8 * 256, "one row
 constexpr int EY_ROWS = 8;
 
 template <typename T>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_ref br, int with_ey) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_ref br) {
   extern __shared__ __attribute__((aligned(16))) char sm_rf[];
   __shared__ double gy[EY_ROWS][2][CBP_MAX_S];
   __shared__ double fpart_l[2][128];
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
     for (int i = 0; i < q.nv; ++i) {
       const int y = q.y0 + S * i;
       row_twiddles(a, twf, px, tabN, tabCode);
-      if (with_ey && S != tabS) {
+      if (S != tabS) {
         // w_t for the row evaluation (made again only when S changes: behind
         // the last item's evaluation, and the barrier after the row's store
         // orders it before its use)
@@ -447,8 +447,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_row_fwd(batch_r
       if (i + 1 < q.nv) fetch(d, ch, y + S);
       else fetch_from(it + step);
       const int e = i % EY_ROWS;
-      row_transform<T>(d, ch, y, a, twf, with_ey ? gy[e] : nullptr, fpart_l);
-      if (with_ey && (e == EY_ROWS - 1 || i + 1 == q.nv)) row_eval(d, ch, y - e * S, e + 1, threadIdx.x, 256, gy, twS);
+      row_transform<T>(d, ch, y, a, twf, gy[e], fpart_l);
+      if (e == EY_ROWS - 1 || i + 1 == q.nv) row_eval(d, ch, y - e * S, e + 1, threadIdx.x, 256, gy, twS);
     }
     // the group's column-fold partials (fold_item's layout), for x < W
     const auto fp1 = raw_buffer(d.fpart + (((size_t)q.g * d.ncf + 2 * ch) * S + q.r) * (size_t)d.Wmax, d.W1 * 8);
@@ -511,8 +511,8 @@ __global__ __launch_bounds__(256) void k_rows_front(batch_ref br_ws, front_grid 
 }
 
 // ---------------------------------------------------------------- pass 2
-// The column pass keeps one strip of cw columns (cw up to 8: up to 64-byte
-// row segments of T) in LDS, column-major with an odd leading dimension, and
+// The column pass keeps one strip of cw columns (cw up to 8: row
+// segments of up to 64 bytes, 128 in FP64) in LDS, column-major with an odd leading dimension, and
 // transforms it in place.  One buffer per strip instead of two frames'
 // ping-pong pairs is what makes wide strips fit; frame 2's spectrum waits in
 // registers while frame 1 is transformed.  The workgroup has NT = 256 or 512
@@ -1079,10 +1079,9 @@ void set_fft_attrs() {
 }
 
 template <typename T>
-hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, int with_ey, hipStream_t st) {
+hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, hipStream_t st) {
   prof_begin(PH_ROW_FWD, st);
-  hipLaunchKernelGGL(k_row_fwd<T>, dim3(grid), dim3(256), row_lds_bytes(maxPx, maxTw, (int)sizeof(T)), st, br,
-                     with_ey);
+  hipLaunchKernelGGL(k_row_fwd<T>, dim3(grid), dim3(256), row_lds_bytes(maxPx, maxTw, (int)sizeof(T)), st, br);
   prof_end(PH_ROW_FWD, st);
   return hipGetLastError();
 }
@@ -1136,8 +1135,8 @@ template hipError_t launch_rows_front<float>(const batch_ref&, const front_grid&
                                              hipStream_t);
 template hipError_t launch_rows_front<double>(const batch_ref&, const front_grid&, int, int, const inline_head*,
                                               hipStream_t);
-template hipError_t launch_row_fwd<float>(const batch_ref&, int, int, int, int, hipStream_t);
-template hipError_t launch_row_fwd<double>(const batch_ref&, int, int, int, int, hipStream_t);
+template hipError_t launch_row_fwd<float>(const batch_ref&, int, int, int, hipStream_t);
+template hipError_t launch_row_fwd<double>(const batch_ref&, int, int, int, hipStream_t);
 template hipError_t launch_col<float>(const batch_ref&, int, int, int, int, int, int, hipStream_t);
 template hipError_t launch_col<double>(const batch_ref&, int, int, int, int, int, int, hipStream_t);
 template hipError_t launch_kernel_dft<float>(const batch_ref&, int, hipStream_t);

@@ -134,10 +134,9 @@ struct batch_ref {
   int* ctr;                 // [CTR_COUNT] item counters of the dynamic launches (zeroed by the first launch)
 };
 
-// Item counters of a chunk's dynamically scheduled launches, eight each (one
-// per XCD): the row pass, the inverse rows, and the column pass per filter
-// group.
-constexpr int CTR_ROW_FWD = 0, CTR_ROW_INV = 8, CTR_COL = 16, CTR_COUNT = 64;
+// Item counters of a chunk's dynamically scheduled launches: the column pass per
+// filter group, eight each (one per XCD).
+constexpr int CTR_COL = 16, CTR_COUNT = 64;
 
 // Rows per group of the column filter's kernel-spectrum evaluation: rows
 // y + j N/g, j < g, share one Horner chain in w_N^(g y), so an entry costs
@@ -568,10 +567,10 @@ size_t gram_mfma_lds_bytes(int maxStride, int fmt);
 void set_gram_mfma_attrs();
 
 // fft.hip.  The row pass also writes the column fold's partials (the
-// result of fold_item, bit for bit) and, with with_ey, the row evaluation EY
-// (the result of k_front, bit for bit) from the rows it already holds.
+// result of fold_item, bit for bit) and the row evaluation EY (the result of
+// k_front, bit for bit) from the rows it already holds.
 template <typename T>
-hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, int with_ey, hipStream_t st);
+hipError_t launch_row_fwd(const batch_ref& br, int grid, int maxPx, int maxTw, hipStream_t st);
 // The first launch of a deblurring call with the split row pass: every row of
 // both frames transformed and evaluated by a workgroup of its own, the column
 // fold and the twiddle tables beside them.

@@ -249,7 +249,7 @@ __device__ inline void store4(unsigned short* p, const unsigned short* v) {
 
 __global__ __launch_bounds__(256) void k_mlp_step(step_args a) {
   __shared__ __attribute__((aligned(16))) step_lds L;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int tid = threadIdx.x, w = tid >> 6;
   const int nb = (a.n + RB - 1) / RB;
   // both layouts of the second layer in registers (128 x 16 groups of eight)
   v4u r2[8], r2t[8];
@@ -443,7 +443,6 @@ __global__ __launch_bounds__(256) void k_mlp_step(step_args a) {
   }
   if (tid < 2) p[MLP_OFF_B3 + tid] = db3;
   if (tid == 2) p[MLP_NPARAM] = loss;
-  (void)l;
 }
 
 struct update_args {

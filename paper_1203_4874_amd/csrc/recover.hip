@@ -39,8 +39,8 @@ namespace {
 struct gram_acc {
   const cdd* rho;
   int k1, k2;
-  // Row i varies across lanes, column j is uniform: one index and two sign
-  // choices, no divergent branches.
+  // One index and two sign choices, no divergent branches (rows vary across the
+  // lanes, in the workgroup solver columns too).
   __device__ cdd get(int i, int j) const {
     const bool ia = i < k2, ja = j < k2;
     const int lag = i - j;
