@@ -161,16 +161,17 @@ __device__ inline double wave_parts(const double* p) {
   return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
 }
 
-// The same in double-double: high parts in hi, low parts in lo.
+// The same in double-double (high parts in hi, low parts in lo), without the
+// missing slots: a zero added to a normalised double-double changes nothing.
 template <int C>
 __device__ inline dd wave_parts(const double* hi, const double* lo) {
-  dd v[8];
+  dd v[C];
 #pragma unroll
-  for (int w = 0; w < 8; ++w) v[w] = w < C ? dd{hi[w], lo[w]} : dd{0.0, 0.0};
+  for (int w = 0; w < C; ++w) v[w] = {hi[w], lo[w]};
 #pragma unroll
-  for (int n = 4; n > 0; n >>= 1)
+  for (int n = 1; n < C; n *= 2)
 #pragma unroll
-    for (int w = 0; w < n; ++w) v[w] = dd_add(v[2 * w], v[2 * w + 1]);
+    for (int w = 0; w + n < C; w += 2 * n) v[w] = dd_add(v[w], v[w + n]);
   return v[0];
 }
 
