@@ -445,8 +445,10 @@ cbp_status cbp_mlp_forward(const void* blob, const float* X, int32_t n, float* o
 /* Phase timing.  While enabled, every call records a HIP event pair around
  * each phase on its stream; cbp_profile_read() waits for the recorded events,
  * adds their elapsed times to per-phase totals and returns the number of
- * phases (at most max_phases are written to ms_total / counts).  Names come
- * from cbp_profile_phase_name().  cbp_profile_reset() clears the totals. */
+ * phases (at most max_phases are written to ms_total / counts).  A launch that
+ * serves several phases counts to one of them: the row evaluation to fold_cols
+ * (kernels only) or row_fft_fwd, the column fold of a deblurring call to
+ * row_fft_fwd.  Names come from cbp_profile_phase_name().  cbp_profile_reset() clears the totals. */
 void        cbp_profile_enable(int32_t on);
 void        cbp_profile_reset(void);
 int32_t     cbp_profile_read(double* ms_total, int64_t* counts, int32_t max_phases);

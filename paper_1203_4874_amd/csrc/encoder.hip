@@ -386,7 +386,10 @@ __global__ __launch_bounds__(256) void k_blur(blur_args<T> g) {
 // Both streams in one launch, for kernels of at most kBlurPair: their tiles
 // are short, and on small frames the second launch costs more than the
 // tiles (64x64, 3x3 / 5x5: 14.1 us in two launches, 11.7 in one), while the
-// registers of the largest instance still leave three waves per SIMD.
+// registers of the largest instance still leave three waves per SIMD.  Larger
+// ones are bound by their tiles also on small frames: calls of 16x16 to 240x320
+// FP32 with 8 / 8, 8 / 9, 9 / 11, 15 / 17, 21 / 19 taps take 15.5, 18, 18 to 21, 29
+// to 33, 39 to 43 us (20, 24, 34, 72, 107 one tap at a time in one launch).
 constexpr int kBlurPair = 8;
 
 template <typename T, int K>

@@ -44,8 +44,9 @@ namespace {
 // from one: 8 x 1080p RGB FP32 columns 409 -> 377 us, forward rows 319 -> 255,
 // inverse rows 138 -> 104 (the rows with the pass order of kDefaultTuning);
 // 719x1277 FP64 columns 47 -> 29.8, single rows 27.6 -> 22.8.  With the plans
-// of fft_costs and the strip widths and evaluations of later, 354, 248, 104;
-// 24.8 and 21.3.
+// of fft_costs and the strip widths and evaluations of later, 336, 214, 100;
+// 26.2 (with the kernels' row transforms) and 21.8.  These are launches of the
+// default shapes; an autotuned stream's differ by a few per cent.
 
 // threadIdx.x behind an empty asm statement: values derived from it are
 // recomputed where they are used instead of being hoisted out of the item
@@ -338,7 +339,8 @@ __device__ __attribute__((always_inline)) inline void row_eval(const frame_desc&
 // eval_rows_item: the same lanes, the same order, hence the same bits) is taken
 // from the row in LDS; the DFTs of up to EY_ROWS rows run together, over all
 // threads, instead of on 2 S of them while the row waits, with two barriers of
-// their own (8 x 1080p RGB 255 -> 248 us, 16 x 720p 110 -> 105).  The grid is
+// their own (8 x 1080p RGB 255 -> 248 us, 16 x 720p 110 -> 105; without a switch
+// to leave them out, and the register it spilled, 214 and 93).  The grid is
 // persistent: a workgroup loads its next row into registers while it
 // transforms the current one.
 static_assert(CBP_MAX_FFT_F32 <= 8 * 256 && CBP_MAX_FFT_F64 <= 8 * 256, "one row is eight loads per thread");

@@ -481,6 +481,7 @@ __device__ inline void eval_cols_item(const frame_desc& d, int item, double (*F)
 // Phases of one call, in launch order (also the names cbp_profile_phase_name
 // returns).
 enum phase_id {
+  // (the row evaluation has no launch of its own any more: PH_EVAL_ROWS keeps its place and counts nothing)
   PH_FOLD = 0, PH_EVAL_COLS, PH_EVAL_ROWS, PH_GRAM, PH_SAMPLE, PH_FINALIZE,
   PH_ROW_FWD, PH_COL_FILTER, PH_ROW_INV, PH_KR_DFT, PH_COUNT
 };
